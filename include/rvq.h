@@ -124,9 +124,12 @@ int rvq_get_codebooks(rvq_ctx *ctx, float *dC, void *stream);
  *             (z_{i+1} of Algorithm 1, in group order); NULL to skip
  * Nearest = smallest squared Euclidean distance; ties go to the smallest index.  A row whose std
  * is below 1e-30 is scaled by 1.
- * With dhat == 32 and encode_path RVQ_PATH_AUTO, calls of at most 4096 group vectors (N * d / 32:
- * the few rows a serving loop appends per step) run a kernel built for latency that returns the
- * codes of RVQ_PATH_EXACT bit for bit; larger calls run the matrix-core kernel.
+ * With dhat == 32 and encode_path RVQ_PATH_AUTO, calls of few group vectors (N * d / 32; at most 512
+ * with 256 CUs: the rows a serving loop appends per step) run a kernel built for latency, calls up
+ * to 128 + K / 8 (at most 512) vectors per CU a matrix-core kernel whose wavefronts share the codebook,
+ * larger calls the matrix-core kernel of RVQ_PATH_SCREEN.  Calls of at most 4096 vectors return the codes
+ * of RVQ_PATH_EXACT bit for bit; in larger ones distances that differ by less than their fp32 rounding
+ * may be decided the other way.
  * With cfg.scale == 1, N must not exceed rvq_reserved_rows(): RVQ_EWORKSPACE otherwise (nothing
  * is enqueued).
  */
@@ -143,8 +146,8 @@ int rvq_encode(rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx, int32_t sta
  * RVQ_EWORKSPACE and nothing is enqueued.  All contexts on one GPU share that array: calls that
  * may overlap on one GPU (two streams, or two contexts) race on it and must be ordered by the
  * caller.  The array needs no clearing between calls: every entry a call reads it has written
- * itself.  (Calls of at most 4096 group vectors with dhat == 32 and RVQ_PATH_AUTO take the
- * latency kernel, which keeps the std inside the kernel and does not touch the array.)
+ * itself.  (Calls of at most 4096 group vectors with dhat == 32 and RVQ_PATH_AUTO take kernels
+ * that keep the std inside and do not touch the array.)
  */
 int rvq_encode_static(rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx, int32_t stage_begin,
                       int32_t stage_end, int16_t *dCodes, void *dStd, float *dResidual,

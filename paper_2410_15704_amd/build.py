@@ -34,9 +34,9 @@ def stale() -> bool:
     return any(os.path.getmtime(p) > t for p in deps)
 
 
-# Per-file extra flags.  The screen kernel reduces matrix-core results with min3 / med3 chains;
+# Per-file extra flags.  The screen kernels reduce matrix-core results with min3 / med3 chains;
 # without -fno-honor-nans every operand would first be re-quieted by an extra VALU instruction.
-EXTRA = {"rvq_encode_screen.hip": ["-fno-honor-nans"]}
+EXTRA = {"rvq_encode_screen.hip": ["-fno-honor-nans"], "rvq_encode_share.hip": ["-fno-honor-nans"]}
 
 
 def build(force: bool = False, verbose: bool = True) -> str:

@@ -62,11 +62,22 @@ int encode_enqueue(rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx, int sta
                    int stage_end, int16_t *dCodes, void *dStd, float *dResidual, float *std32,
                    hipStream_t s) {
   const rvq_config &c = ctx->cfg;
-  if (c.dhat == 32 && c.encode_path == RVQ_PATH_AUTO && N * ctx->G <= RVQ_SMALL_MAX_VECTORS) {
-    // a few rows: one kernel, which computes the rows' std itself
-    RVQ_HIP(ctx, rvq_launch_encode_small(ctx, dX, N, ldx, stage_begin, stage_end, dCodes,
-                                         dResidual, dStd, s));
-    return RVQ_OK;
+  const int64_t V = N * ctx->G;
+  if (c.dhat == 32 && c.encode_path == RVQ_PATH_AUTO) {
+    if (V <= RVQ_SMALL_PER_CU * ctx->num_cus) {
+      // a few rows: one kernel, which computes the rows' std itself
+      RVQ_HIP(ctx, rvq_launch_encode_small(ctx, dX, N, ldx, stage_begin, stage_end, dCodes,
+                                           dResidual, dStd, s));
+      return RVQ_OK;
+    }
+    // (a lowered poll limit is meant for the kernel that has bounded waits: the call goes there)
+    if (rvq_share_fits(ctx, V) && ctx->wait_polls == RVQ_WAIT_POLLS_DEFAULT) {
+      if (rvq_share_needs_std(ctx, N))
+        RVQ_HIP(ctx, rvq_launch_row_std(ctx, dX, N, ldx, dStd, std32, s));
+      RVQ_HIP(ctx, rvq_launch_encode_share(ctx, dX, N, ldx, stage_begin, stage_end, dCodes, dResidual,
+                                           dStd, std32, s));
+      return RVQ_OK;
+    }
   }
   if (c.scale) RVQ_HIP(ctx, rvq_launch_row_std(ctx, dX, N, ldx, dStd, std32, s));
   if (c.dhat == 32 && c.encode_path != RVQ_PATH_EXACT)
@@ -113,6 +124,7 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
   ctx->C = nullptr;
   ctx->norms = nullptr;
   ctx->C16 = nullptr;
+  ctx->C16s = nullptr;
   ctx->normp = nullptr;
   ctx->stats = nullptr;
   ctx->groupA = nullptr;
@@ -145,6 +157,7 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
   if (e == hipSuccess) e = hipMalloc((void **)&ctx->norms, (size_t)cfg->depth * cfg->K * sizeof(float));
   if (e == hipSuccess && cfg->dhat == 32) {  // operands of the matrix-core screen
     e = hipMalloc((void **)&ctx->C16, (size_t)cfg->depth * ctx->Kpad * 32 * sizeof(uint16_t));
+    if (e == hipSuccess) e = hipMalloc((void **)&ctx->C16s, (size_t)cfg->depth * ctx->Kpad * 32 * sizeof(uint16_t));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->normp, (size_t)cfg->depth * ctx->Kpad * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->stats, (size_t)cfg->depth * 8 * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->dup, (size_t)cfg->depth * cfg->K * sizeof(int32_t));
@@ -173,6 +186,7 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
     if (ctx->C) (void)hipFree(ctx->C);
     if (ctx->norms) (void)hipFree(ctx->norms);
     if (ctx->C16) (void)hipFree(ctx->C16);
+    if (ctx->C16s) (void)hipFree(ctx->C16s);
     if (ctx->normp) (void)hipFree(ctx->normp);
     if (ctx->stats) (void)hipFree(ctx->stats);
     if (ctx->groupA) (void)hipFree(ctx->groupA);
@@ -197,6 +211,7 @@ int rvq_destroy(rvq_ctx *ctx) {
   if (ctx->C) (void)hipFree(ctx->C);
   if (ctx->norms) (void)hipFree(ctx->norms);
   if (ctx->C16) (void)hipFree(ctx->C16);
+  if (ctx->C16s) (void)hipFree(ctx->C16s);
   if (ctx->normp) (void)hipFree(ctx->normp);
   if (ctx->stats) (void)hipFree(ctx->stats);
   if (ctx->groupA) (void)hipFree(ctx->groupA);

@@ -303,26 +303,19 @@ hipError_t rvq_launch_encode_small(const rvq_ctx *ctx, const void *dX, int64_t N
   const rvq_config &c = ctx->cfg;
   const int64_t V = N * ctx->G;
   if (V < 1) return hipSuccess;
-  if (c.dhat != 32 || V > RVQ_SMALL_MAX_VECTORS) return hipErrorInvalidValue;
+  if (c.dhat != 32 || V > RVQ_SMALL_PER_CU * ctx->num_cus) return hipErrorInvalidValue;
   const bool vec_rows = rvq_rows_vectorizable(dX, ldx, c.d, c.in_dtype);
   // one workgroup fills a CU: a workgroup takes a second vector only when every CU has one
-  int vpw = 1;
-  while (vpw < 16 && V > (int64_t)ctx->num_cus * vpw) vpw *= 2;
+  const int vpw = V > ctx->num_cus ? 2 : 1;
   const dim3 grid((unsigned)((V + vpw - 1) / vpw)), block(SM_THREADS);
 #define RVQ_LAUNCH_SMALL(VPW, LPC)                                                               \
   hipLaunchKernelGGL((encode_small_kernel<VPW, LPC>), grid, block, 0, s, dX, c.in_dtype, N, ldx, \
                      ctx->G, c.grouping, c.scale, c.std_ddof, vec_rows, dStd, c.std_dtype,       \
                      ctx->C, c.K, c.depth, stage_begin, stage_end, dCodes, dResidual)
-  // lanes per codeword, measured: four while a workgroup has up to four vectors (a wavefront's
-  // load instruction then covers sixteen rows half a line at a time, and two of the three tree
-  // levels between lanes remain), two when there is more arithmetic per fetched codeword
-  switch (vpw) {
-    case 1: RVQ_LAUNCH_SMALL(1, 4); break;
-    case 2: RVQ_LAUNCH_SMALL(2, 4); break;
-    case 4: RVQ_LAUNCH_SMALL(4, 4); break;
-    case 8: RVQ_LAUNCH_SMALL(8, 2); break;
-    default: RVQ_LAUNCH_SMALL(16, 2); break;
-  }
+  // four lanes per codeword, measured: a wavefront's load instruction then covers sixteen rows half a
+  // line at a time, and two of the three tree levels between lanes remain
+  if (vpw == 1) RVQ_LAUNCH_SMALL(1, 4);
+  else RVQ_LAUNCH_SMALL(2, 4);
 #undef RVQ_LAUNCH_SMALL
   return hipGetLastError();
 }

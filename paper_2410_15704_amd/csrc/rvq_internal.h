@@ -27,6 +27,7 @@ struct rvq_ctx {
   // Within a stage the codewords are ordered by norm ("position"), so that the 16 codewords a
   // lane reduces together have similar norms and share a tight error bound.
   uint16_t *C16;       // [depth][Kpad/32][2][64][8] fp16(-2 c), matrix-core A-operand order
+  uint16_t *C16s;      // [depth][Kpad/16][64][8] the same values as 16-row A operands
   float *normp;        // [depth][Kpad/32][2][16] ||c||^2 minus the group's second-order error
                        //   term, in accumulator-register order
   float *groupA;       // [depth][Kpad/16] largest ||2c|| of each (tile, half) group
@@ -182,13 +183,21 @@ hipError_t rvq_launch_row_std(const rvq_ctx *ctx, const void *dX, int64_t N, int
 hipError_t rvq_launch_encode_exact(const rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx,
                                    int stage_begin, int stage_end, int16_t *dCodes,
                                    float *dResidual, const float *std32, hipStream_t s);
-// dhat == 32 and at most RVQ_SMALL_MAX_VECTORS group vectors: the codes of the exact kernel, with
+// dhat == 32 and at most RVQ_SMALL_PER_CU group vectors per CU: the codes of the exact kernel, with
 // the codebook of a stage split over the threads of a workgroup (latency of a few rows)
-constexpr int64_t RVQ_SMALL_MAX_VECTORS = 4096;
+constexpr int64_t RVQ_SMALL_PER_CU = 2;
 // (computes the rows' std itself when cfg.scale is set and writes it to dStd; no row_std launch)
 hipError_t rvq_launch_encode_small(const rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx,
                                    int stage_begin, int stage_end, int16_t *dCodes,
                                    float *dResidual, void *dStd, hipStream_t s);
+// dhat == 32: the wavefronts of a workgroup share the stage's codewords and sweep the same tokens.
+// Computes the rows' std itself (and writes dStd), except where rvq_share_needs_std says that
+// row_std has to have filled std32 and dStd before.  rvq_share_fits: the vector counts it is for
+bool rvq_share_fits(const rvq_ctx *ctx, int64_t V);
+bool rvq_share_needs_std(const rvq_ctx *ctx, int64_t N);
+hipError_t rvq_launch_encode_share(const rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx,
+                                   int stage_begin, int stage_end, int16_t *dCodes, float *dResidual,
+                                   void *dStd, const float *std32, hipStream_t s);
 hipError_t rvq_launch_encode_screen(const rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx,
                                     int stage_begin, int stage_end, int16_t *dCodes,
                                     float *dResidual, const float *std32, hipStream_t s);

@@ -138,7 +138,8 @@ __global__ __launch_bounds__(256) void rank_kernel(const float *__restrict__ nor
 __global__ __launch_bounds__(1024) void screen_tile_kernel(
     const float *__restrict__ C, const int32_t *__restrict__ perm,
     const float *__restrict__ rowmax, int K, int Kpad, int stage_begin, float kappa,
-    uint16_t *__restrict__ C16, uint16_t *__restrict__ perm16, float *__restrict__ normp,
+    uint16_t *__restrict__ C16, uint16_t *__restrict__ C16s, uint16_t *__restrict__ perm16,
+    float *__restrict__ normp,
     float *__restrict__ groupA, float *__restrict__ stats) {
   __shared__ float red[16];
   __shared__ float nrm[32], len[32], rho_s[32], drop_s[32];
@@ -187,6 +188,9 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
   // no longer collide on one LDS bank
   uint16_t *dst = C16 + ((int64_t)stage * Kpad + (int64_t)t * 32) * 32;
   dst[((((q * 2 + (e >> 2)) * 64) + h * 32 + (m ^ (t & 31))) * 4) + (e & 3)] = __half_as_ushort(hv);
+  // and as the two 16-row A operands of v_mfma_f32_16x16x32_f16: lane (channel group, row)
+  C16s[((int64_t)stage * Kpad + (int64_t)t * 32) * 32 + (((m >> 4) * 64 + (j >> 3) * 16 + (m & 15)) * 8) + e] =
+      __half_as_ushort(hv);
   if (j == 0) {
     perm16[(int64_t)stage * Kpad + pos] = k < 0 ? (uint16_t)0xffff : (uint16_t)k;
     if (k >= 0) {
@@ -243,6 +247,6 @@ hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int 
                      (int)K, ctx->Kpad, stage_begin, ctx->perm);
   hipLaunchKernelGGL(screen_tile_kernel, dim3((unsigned)(ns * (ctx->Kpad / 32))), dim3(1024), 0, s,
                      ctx->C, ctx->perm, ctx->rowmax, (int)K, ctx->Kpad, stage_begin, ctx->kappa,
-                     ctx->C16, ctx->perm16, ctx->normp, ctx->groupA, ctx->stats);
+                     ctx->C16, ctx->C16s, ctx->perm16, ctx->normp, ctx->groupA, ctx->stats);
   return hipGetLastError();
 }

@@ -283,6 +283,76 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
         assert torch.equal(small[4], small[2])
 
 
+@pytest.mark.parametrize("case", [
+    # V, G, K, depth, grouping, dtype, scale, kind   (between the small-batch kernel and a full chip)
+    (513, 1, 2048, 3, oracle.CONTIGUOUS, "fp32", 0, "plain"),       # three tokens per workgroup
+    (4096, 4, 2048, 3, oracle.STRIDED, "bf16", 1, "plain"),         # one full tile of 16
+    (4100, 4, 2048, 3, oracle.STRIDED, "fp16", 1, "plain"),         # two tiles
+    (12285, 3, 1000, 2, oracle.STRIDED, "fp32", 1, "plain"),        # three tiles, rows across workgroups
+    (33025, 1, 2048, 2, oracle.CONTIGUOUS, "bf16", 1, "plain"),     # std computed beforehand
+    (98304, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # 384 tokens per CU, the most at K = 2048
+    (98336, 32, 2048, 1, oracle.STRIDED, "bf16", 1, "plain"),       # one row more: the large kernel
+    (131072, 128, 4096, 1, oracle.STRIDED, "fp16", 1, "plain"),     # 512 tokens, two pieces
+    (1000, 1, 33, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),        # a padded tile
+    (1000, 1, 512, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),       # the codebook splits of the wavefronts
+    (1000, 1, 513, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),
+    (1000, 1, 1025, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),
+    (1000, 1, 5000, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),      # three pieces, the last ragged
+    (3000, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "crowded"),    # many candidates per token
+    (3000, 1, 4096, 2, oracle.CONTIGUOUS, "fp32", 0, "crowded"),    # ... in two pieces
+    (3000, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "repeats"),    # repeated and zero codewords
+    (3000, 1, 700, 2, oracle.CONTIGUOUS, "fp32", 0, "huge"),        # residuals beyond fp16: exact search
+    (3000, 1, 4096, 2, oracle.CONTIGUOUS, "fp32", 0, "nan"),
+])
+def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
+    """The kernel whose wavefronts share a stage's codebook, at the edges of its tiles, pieces and vector
+    counts, with crowded and repeated codewords, and for rows it cannot screen.  Up to 4096 vectors its
+    codes, std and residuals are the exact path's bit for bit (the distances that decide are the same
+    fp32 sums in the same order); beyond that near-ties are decided by the sums of the large matrix-core
+    kernel, and its results are those (vectors with more candidates than that kernel lists excepted:
+    their near-ties, below 1e-5 of the codes, may fall either way)."""
+    torch, b = _torch(), _b()
+    V, G, K, depth, grouping, dtype, scale, kind = case
+    d, N = 32 * G, V // G
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V + K)
+    X = torch.randn((N, d), device="cuda", generator=gen)
+    C = torch.randn((depth, K, 32), device="cuda", generator=gen)
+    C *= (0.7 ** torch.arange(depth, device="cuda"))[:, None, None]
+    if kind == "crowded":  # clusters of 64 codewords 1e-3 wide
+        C = C[:, torch.arange(K, device="cuda") // 64] + 1e-3 * torch.randn(C.shape, device="cuda", generator=gen)
+    elif kind == "repeats":
+        C[:, K // 2:] = C[:, :K - K // 2]
+        C[:, 5:40] = 0.0
+    elif kind == "huge":
+        X[::7] *= 1e6
+        X[3] = 3e38
+    elif kind == "nan":
+        X[5, 3], X[6, 0], X[N - 1, 31] = float("nan"), float("inf"), -float("inf")
+    X = X.to({"fp32": torch.float32, "bf16": torch.bfloat16, "fp16": torch.float16}[dtype])
+    C = C.contiguous()
+    got = {}
+    other = b.PATH_EXACT if V <= 4096 else b.PATH_SCREEN
+    for path in (b.PATH_AUTO, other):
+        q = b.Quantizer(d=d, dhat=32, depth=depth, K=K, grouping=grouping, in_dtype=b.DTYPES[dtype],
+                        std_dtype=b.F16, scale=scale, encode_path=path)
+        q.set_codebooks(C)
+        got[path] = q.encode(X, want_residual=True)
+        torch.cuda.synchronize()
+        assert b.rvq_check_kernels(q.ctx) == 0
+        q.close()
+    auto, ref = got[b.PATH_AUTO], got[other]
+    assert int(auto[0].min()) >= 0 and int(auto[0].max()) < K
+    rows = torch.ones(N, dtype=torch.bool, device="cuda")
+    if V > 4096:
+        differ = auto[0] != ref[0]
+        assert float(differ.float().mean()) <= 1e-5
+        rows = ~differ.flatten(1).any(1)
+    for name, x, y in zip(("codes", "std", "residual"), auto, ref):
+        if x is not None:
+            assert torch.equal(x[rows].view(torch.uint8), y[rows].view(torch.uint8)), name
+
+
 def test_encode_chunks_of_512_and_of_1024_agree(gpu_device):
     """A call with at most 512 vectors per CU runs the matrix-core kernel with one token per lane
     (chunks of 512), a larger one with two (chunks of 1024).  A token's codes do not depend on
