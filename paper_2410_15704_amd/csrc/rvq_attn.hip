@@ -13,6 +13,8 @@
 // Each half-wavefront keeps its own running maximum, sum and weighted value sum (online softmax,
 // base 2); the eight of a workgroup are merged through LDS into one partial result per
 // (kv head, split of the cache), and a second small kernel merges the splits.
+#include <type_traits>
+
 #include "rvq_internal.h"
 
 namespace {
@@ -154,6 +156,10 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   __shared__ float sm_m[2 * ATT_WAVES][REP];
   __shared__ float sm_l[2 * ATT_WAVES][REP];
   __shared__ float sm_acc[2 * ATT_WAVES][REP][ATT_HD];
+  // FAST: what comes from HBM passes through these, one area per wavefront
+  __shared__ __align__(16) i32x4 sm_codes[FAST ? ATT_WAVES : 1][2][64];       // [K, V][half][trip of 8][group]
+  __shared__ float sm_std[FAST ? ATT_WAVES : 1][2][16];                       // [K, V][half][trip of 8]
+  __shared__ __align__(16) float sm_tab[FAST ? ATT_WAVES : 1][2][ATT_HD];     // [half][64 cos, 64 sin]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -203,7 +209,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   const uint32_t last = (uint32_t)(nend - nbeg) - 1u;         // last token of the split, relative
   const uint32_t row_recs = (uint32_t)(a.Hkv * ATT_G);        // (row, group) records between tokens
 
-  // what a token needs from HBM, fetched one trip ahead (the gathers depend on the codes)
+  // what a token needs from HBM; the general path fetches it one trip ahead (the gathers depend on the
+  // codes)
   struct Pre {
     AttCodes kc, vc;
     float ks, vs, cs[4], sn[4];
@@ -214,37 +221,14 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
     p.kc = att_load_codes<D8, PK>(kcb, rec, a.depth);
     p.vc = att_load_codes<D8, PK>(vcb, rec, a.depth);
     const uint32_t ro = tc * (uint32_t)a.Hkv;
-    if constexpr (FAST) {
-      p.ks = rvq_f16_bits_to_f32(((const uint16_t *)ksb)[ro]);
-      p.vs = rvq_f16_bits_to_f32(((const uint16_t *)vsb)[ro]);
-      // the lane's four channels lie in the pairs 8 q8 + 2 e + (g >> 1) (strided: two 16-byte
-      // loads per table and a pick) or in the two pairs 16 g + 2 q8, + 1 (contiguous: one 8-byte load)
-      if constexpr (KS) {
-        const f32x4 *cp = reinterpret_cast<const f32x4 *>(cosb + tc * (ATT_HD / 2) + 8 * q8);
-        const f32x4 *sp_ = reinterpret_cast<const f32x4 *>(sinb + tc * (ATT_HD / 2) + 8 * q8);
-        const f32x4 c0 = cp[0], c1 = cp[1], s0 = sp_[0], s1 = sp_[1];
-        const bool hi = (g >> 1) != 0;
-        p.cs[0] = hi ? c0[1] : c0[0]; p.cs[1] = hi ? c0[3] : c0[2];
-        p.cs[2] = hi ? c1[1] : c1[0]; p.cs[3] = hi ? c1[3] : c1[2];
-        p.sn[0] = hi ? s0[1] : s0[0]; p.sn[1] = hi ? s0[3] : s0[2];
-        p.sn[2] = hi ? s1[1] : s1[0]; p.sn[3] = hi ? s1[3] : s1[2];
-      } else {
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-        const f32x2 c2 = *reinterpret_cast<const f32x2 *>(cosb + tc * (ATT_HD / 2) + 16 * g + 2 * q8);
-        const f32x2 s2 = *reinterpret_cast<const f32x2 *>(sinb + tc * (ATT_HD / 2) + 16 * g + 2 * q8);
-        p.cs[0] = p.cs[1] = c2[0]; p.cs[2] = p.cs[3] = c2[1];
-        p.sn[0] = p.sn[1] = s2[0]; p.sn[2] = p.sn[3] = s2[1];
-      }
-    } else {
-      p.ks = !ksb ? 1.0f : (a.kstd_dtype == RVQ_F32 ? ((const float *)ksb)[ro]
-                                                    : rvq_f16_bits_to_f32(((const uint16_t *)ksb)[ro]));
-      p.vs = !vsb ? 1.0f : (a.vstd_dtype == RVQ_F32 ? ((const float *)vsb)[ro]
-                                                    : rvq_f16_bits_to_f32(((const uint16_t *)vsb)[ro]));
+    p.ks = !ksb ? 1.0f : (a.kstd_dtype == RVQ_F32 ? ((const float *)ksb)[ro]
+                                                  : rvq_f16_bits_to_f32(((const uint16_t *)ksb)[ro]));
+    p.vs = !vsb ? 1.0f : (a.vstd_dtype == RVQ_F32 ? ((const float *)vsb)[ro]
+                                                  : rvq_f16_bits_to_f32(((const uint16_t *)vsb)[ro]));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        p.cs[e] = cosb ? cosb[tc * (ATT_HD / 2) + (ck[e] >> 1)] : 1.0f;
-        p.sn[e] = cosb ? sinb[tc * (ATT_HD / 2) + (ck[e] >> 1)] : 0.0f;
-      }
+    for (int e = 0; e < 4; ++e) {
+      p.cs[e] = cosb ? cosb[tc * (ATT_HD / 2) + (ck[e] >> 1)] : 1.0f;
+      p.sn[e] = cosb ? sinb[tc * (ATT_HD / 2) + (ck[e] >> 1)] : 0.0f;
     }
   };
   // A wavefront's loads come back in the order they were issued.  So a trip first issues the
@@ -293,20 +277,106 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
 
   const int64_t span = nend - nbeg;
   const int trips = span > 0 ? (int)((span + 2 * ATT_WAVES - 1) / (2 * ATT_WAVES)) : 0;  // uniform
-  Pre pa, pb;
+  constexpr uint32_t STEP = 2 * ATT_WAVES;
   Rows R;
   uint32_t t = (uint32_t)hw;  // token of this half-wavefront, relative to nbeg
-  if (trips > 0) fetch(t, pa);
-  for (int it = 0; it < trips; it += 2) {
-    issue(pa, R);
-    fetch(t + 2 * ATT_WAVES, pb);
-    work(t, pa, R);
-    t += 2 * ATT_WAVES;
-    if (it + 1 >= trips) break;
-    issue(pb, R);
-    fetch(t + 2 * ATT_WAVES, pa);
-    work(t, pb, R);
-    t += 2 * ATT_WAVES;
+  if constexpr (FAST) {
+    // The L1's address path is what bounds the loop (93 % busy): a load instruction takes it 16 cycles
+    // for 16 bytes a lane, whether or not lanes ask for the same bytes.  The eight lanes of a group
+    // share their codes and the four groups of a token their tables, so with a load per lane for each
+    // of them 176 of a trip's 432 accesses were repeats.  Here the 64 lanes fetch 64 different records,
+    // the codes of eight trips of both half-wavefronts, and the 32 lanes of a token its 512 bytes
+    // of tables, a piece each; both go through LDS, which is idle otherwise (a wavefront's own
+    // area: its LDS operations run in order, so nothing has to be waited for).  131072 tokens x 8 kv
+    // heads: 542 -> 481 us.
+    i32x4 *codes_k = sm_codes[wave][0], *codes_v = sm_codes[wave][1];
+    float *tab = sm_tab[wave][half];
+    AttCodes kn, vn;             // the next eight trips' record of this lane (trip q8, group g) ...
+    float ksn = 0.f, vsn = 0.f;  // ... and that token's std
+    auto fetch8 = [&](int it) {
+      const uint32_t tt = (uint32_t)hw + STEP * (uint32_t)(it + q8), tc = tt < last ? tt : last;
+      kn = att_load_codes<true, PK>(kcb, tc * row_recs + (uint32_t)g, 8);
+      vn = att_load_codes<true, PK>(vcb, tc * row_recs + (uint32_t)g, 8);
+      ksn = rvq_f16_bits_to_f32(((const uint16_t *)ksb)[tc * (uint32_t)a.Hkv]);
+      vsn = rvq_f16_bits_to_f32(((const uint16_t *)vsb)[tc * (uint32_t)a.Hkv]);
+    };
+    auto store8 = [&]() {
+      codes_k[half * 32 + q8 * 4 + g] = kn.w;
+      codes_v[half * 32 + q8 * 4 + g] = vn.w;
+      sm_std[wave][0][half * 8 + q8] = ksn;
+      sm_std[wave][1][half * 8 + q8] = vsn;
+    };
+    // this lane's piece of a token's tables: lanes 0..15 of the half cos, 16..31 sin
+    const int l32 = lane & 31;
+    const float *tab_src = (l32 < 16 ? cosb : sinb) + (l32 & 15) * 4;
+    auto fetch_tab = [&](uint32_t tt) -> f32x4 {
+      const uint32_t tc = tt < last ? tt : last;
+      typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+      return *reinterpret_cast<const f32x4a4 *>(tab_src + tc * (ATT_HD / 2));
+    };
+    f32x4 tabn = {0.f, 0.f, 0.f, 0.f};
+    if (trips > 0) {
+      fetch8(0);
+      tabn = fetch_tab(t);
+      store8();
+    }
+    // trip j of a block of eight; the first one of a block requests the next block's codes, in code of
+    // its own so that the other trips do not wait for them
+    auto trip = [&](int it0, int j, auto first) {
+      Pre p;
+      __builtin_amdgcn_wave_barrier();
+      p.kc.w = codes_k[half * 32 + j * 4 + g];
+      p.vc.w = codes_v[half * 32 + j * 4 + g];
+      p.ks = sm_std[wave][0][half * 8 + j];
+      p.vs = sm_std[wave][1][half * 8 + j];
+      issue(p, R);
+      if constexpr (first) fetch8(it0 + 8);
+      __builtin_amdgcn_wave_barrier();
+      *reinterpret_cast<f32x4 *>(tab + l32 * 4) = tabn;
+      __builtin_amdgcn_wave_barrier();
+      tabn = fetch_tab(t + STEP);
+      // the lane's four channels lie in the pairs 8 q8 + 2 e + (g >> 1) (strided) or in the two pairs
+      // 16 g + 2 q8, + 1 (contiguous)
+      if constexpr (KS) {
+        const f32x4 *cp = reinterpret_cast<const f32x4 *>(tab + 8 * q8);
+        const f32x4 *sp_ = reinterpret_cast<const f32x4 *>(tab + ATT_HD / 2 + 8 * q8);
+        const f32x4 c0 = cp[0], c1 = cp[1], s0 = sp_[0], s1 = sp_[1];
+        const bool hi = (g >> 1) != 0;
+        p.cs[0] = hi ? c0[1] : c0[0]; p.cs[1] = hi ? c0[3] : c0[2];
+        p.cs[2] = hi ? c1[1] : c1[0]; p.cs[3] = hi ? c1[3] : c1[2];
+        p.sn[0] = hi ? s0[1] : s0[0]; p.sn[1] = hi ? s0[3] : s0[2];
+        p.sn[2] = hi ? s1[1] : s1[0]; p.sn[3] = hi ? s1[3] : s1[2];
+      } else {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 c2 = *reinterpret_cast<const f32x2 *>(tab + 16 * g + 2 * q8);
+        const f32x2 s2 = *reinterpret_cast<const f32x2 *>(tab + ATT_HD / 2 + 16 * g + 2 * q8);
+        p.cs[0] = p.cs[1] = c2[0]; p.cs[2] = p.cs[3] = c2[1];
+        p.sn[0] = p.sn[1] = s2[0]; p.sn[2] = p.sn[3] = s2[1];
+      }
+      work(t, p, R);
+      t += STEP;
+    };
+    for (int it = 0; it < trips; it += 8) {
+      trip(it, 0, std::true_type());
+      const int n = min(8, trips - it);
+      for (int j = 1; j < n; ++j) trip(it, j, std::false_type());
+      __builtin_amdgcn_wave_barrier();
+      store8();
+    }
+  } else {
+    Pre pa, pb;
+    if (trips > 0) fetch(t, pa);
+    for (int it = 0; it < trips; it += 2) {
+      issue(pa, R);
+      fetch(t + STEP, pb);
+      work(t, pa, R);
+      t += STEP;
+      if (it + 1 >= trips) break;
+      issue(pb, R);
+      fetch(t + STEP, pa);
+      work(t, pb, R);
+      t += STEP;
+    }
   }
 
   // merge the eight half-wavefronts of the workgroup
