@@ -130,7 +130,6 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
   ctx->groupA = nullptr;
   ctx->perm = nullptr;
   ctx->rowmax = nullptr;
-  ctx->dup = nullptr;
   ctx->perm16 = nullptr;
   ctx->counters = nullptr;
   ctx->Csplit = nullptr;
@@ -160,7 +159,6 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->C16s, (size_t)cfg->depth * ctx->Kpad * 32 * sizeof(uint16_t));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->normp, (size_t)cfg->depth * ctx->Kpad * sizeof(float));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->stats, (size_t)cfg->depth * 8 * sizeof(float));
-    if (e == hipSuccess) e = hipMalloc((void **)&ctx->dup, (size_t)cfg->depth * cfg->K * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->groupA, (size_t)cfg->depth * (ctx->Kpad / 16) * sizeof(float) + 64);  // + slack: read in 16-byte pieces
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->perm, (size_t)cfg->depth * ctx->Kpad * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void **)&ctx->perm16, (size_t)cfg->depth * ctx->Kpad * sizeof(uint16_t));
@@ -192,7 +190,6 @@ int rvq_create(rvq_ctx **out, const rvq_config *cfg) {
     if (ctx->groupA) (void)hipFree(ctx->groupA);
     if (ctx->perm) (void)hipFree(ctx->perm);
     if (ctx->rowmax) (void)hipFree(ctx->rowmax);
-    if (ctx->dup) (void)hipFree(ctx->dup);
     if (ctx->perm16) (void)hipFree(ctx->perm16);
     if (ctx->counters) (void)hipFree(ctx->counters);
     if (ctx->Csplit) (void)hipFree(ctx->Csplit);
@@ -217,7 +214,6 @@ int rvq_destroy(rvq_ctx *ctx) {
   if (ctx->groupA) (void)hipFree(ctx->groupA);
   if (ctx->perm) (void)hipFree(ctx->perm);
   if (ctx->rowmax) (void)hipFree(ctx->rowmax);
-  if (ctx->dup) (void)hipFree(ctx->dup);
   if (ctx->perm16) (void)hipFree(ctx->perm16);
   if (ctx->counters) (void)hipFree(ctx->counters);
   if (ctx->Csplit) (void)hipFree(ctx->Csplit);

@@ -16,7 +16,7 @@
 //            and the residuals are scaled by before rounding to fp16 (chosen so that the largest
 //            |S a| lies in [2^13, 2^14) and T = S / 2); [5] the largest |a|
 // A codeword that repeats an earlier one exactly can never win (ties go to the smallest index);
-// it gets no position, so exact duplicates (e.g. several dead codes at 0) cost nothing.
+// its position stays empty, like the padding at the end.
 // Ordering by norm keeps the norms inside a group close to each other, which is what makes the
 // per-group error bound of the screen tight when a few codewords are much longer than the rest.
 #include "rvq_internal.h"
@@ -80,54 +80,35 @@ __global__ __launch_bounds__(256) void prep_rows32_kernel(
   }
 }
 
-// One workgroup per codeword: is it an exact repeat of an earlier codeword of its stage?
-__global__ __launch_bounds__(256) void dup_kernel(const float *__restrict__ C,
-                                                  const float *__restrict__ norms, int K,
-                                                  int stage_begin, int32_t *__restrict__ dup) {
+// One workgroup per codeword: its position in the order (norm, index) of the stage's codewords, K^2
+// comparisons per stage spread over K workgroups, and whether it is an exact repeat of an earlier one
+// (equal rows have equal norms).  A repeat leaves its position empty.  (One kernel: with the repeats
+// found first, so that the others close ranks, an update of a stage took a launch more, and the search
+// reads whole tiles either way.)
+__global__ __launch_bounds__(256) void rank_kernel(const float *__restrict__ C,
+                                                   const float *__restrict__ norms, int K, int Kpad,
+                                                   int stage_begin, int32_t *__restrict__ perm) {
+  __shared__ int part[4];
   const int stage = stage_begin + blockIdx.x / K;
   const int k = blockIdx.x % K;
   const float *n = norms + (int64_t)stage * K;
   const float *Cs = C + (int64_t)stage * K * 32;
   const float nk = n[k];
-  int found = 0;
-  for (int j = threadIdx.x; j < k; j += blockDim.x) {
-    if (n[j] != nk) continue;  // equal rows have equal norms
-    bool same = true;
-    for (int e = 0; e < 32; ++e) same = same && Cs[(int64_t)j * 32 + e] == Cs[(int64_t)k * 32 + e];
-    if (same) {  // one earlier repeat is enough (many equal rows, e.g. dead codes at 0, stay cheap)
-      found = 1;
-      break;
-    }
-  }
-  found = __syncthreads_or(found);
-  if (threadIdx.x == 0) dup[(int64_t)stage * K + k] = found ? 1 : 0;
-}
-
-// position of codeword k in the order (norm, index) among the codewords that are no repeats:
-// one workgroup per codeword counts the ones in front of it (K^2 comparisons per stage, spread
-// over K workgroups; runs once per codebook upload or update)
-__global__ __launch_bounds__(256) void rank_kernel(const float *__restrict__ norms,
-                                                   const int32_t *__restrict__ dup, int K, int Kpad,
-                                                   int stage_begin, int32_t *__restrict__ perm) {
-  __shared__ int part[256];
-  const int stage = stage_begin + blockIdx.x / K;
-  const int k = blockIdx.x % K;
-  const float *n = norms + (int64_t)stage * K;
-  const int32_t *dp = dup + (int64_t)stage * K;
-  if (dp[k]) return;  // uniform over the workgroup
-  const float nk = n[k];
-  int cnt = 0;
+  int cnt = 0, found = 0;
   for (int j = threadIdx.x; j < K; j += blockDim.x) {
     const float nj = n[j];
-    cnt += (!dp[j] && (nj < nk || (nj == nk && j < k))) ? 1 : 0;
+    cnt += (nj < nk || (nj == nk && j < k)) ? 1 : 0;
+    if (nj == nk && j < k && !found) {  // one earlier repeat is enough
+      bool same = true;
+      for (int e = 0; e < 32; ++e) same = same && Cs[(int64_t)j * 32 + e] == Cs[(int64_t)k * 32 + e];
+      found = same ? 1 : 0;
+    }
   }
-  part[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) perm[(int64_t)stage * Kpad + part[0]] = k;
+  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = cnt;
+  found = __syncthreads_or(found);
+  if (threadIdx.x == 0)
+    perm[(int64_t)stage * Kpad + part[0] + part[1] + part[2] + part[3]] = found ? -1 : k;
 }
 
 // One workgroup per (stage, tile of 32 positions), one lane per (position, channel): the fp16
@@ -241,9 +222,7 @@ hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int 
   hipLaunchKernelGGL(prep_rows32_kernel, dim3((unsigned)((ns * K + 7) / 8)), dim3(256), 0, s, ctx->C,
                      (int)K, ctx->Kpad, ctx->cfg.depth, stage_begin, stage_end, ctx->norms,
                      ctx->rowmax, ctx->perm, ctx->stats, ctx->Csplit);
-  hipLaunchKernelGGL(dup_kernel, dim3((unsigned)(ns * K)), dim3(256), 0, s, ctx->C, ctx->norms,
-                     (int)K, stage_begin, ctx->dup);
-  hipLaunchKernelGGL(rank_kernel, dim3((unsigned)(ns * K)), dim3(256), 0, s, ctx->norms, ctx->dup,
+  hipLaunchKernelGGL(rank_kernel, dim3((unsigned)(ns * K)), dim3(256), 0, s, ctx->C, ctx->norms,
                      (int)K, ctx->Kpad, stage_begin, ctx->perm);
   hipLaunchKernelGGL(screen_tile_kernel, dim3((unsigned)(ns * (ctx->Kpad / 32))), dim3(1024), 0, s,
                      ctx->C, ctx->perm, ctx->rowmax, (int)K, ctx->Kpad, stage_begin, ctx->kappa,
