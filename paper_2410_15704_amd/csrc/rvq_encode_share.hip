@@ -629,10 +629,11 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 //   above: encode_screen_kernel's wavefronts re-use a token's operands for the whole stage and overtake
 //   once they are full, the later the larger the codebook: K = 512 at 192 tokens per CU 95 : 90, at
 //   256 97 : 109; K = 1024 at 256 132 : 119, at 320 131 : 137; K = 2048 at 375 222 : 212, at 512
-//   229 : 270; K = 4096 at 512 480 : 481, K = 8192 1374 : 786.
+//   229 : 270; K = 4096 (two pieces, each with its resolve step) at 256 454 : 280, at 500, key rows,
+//   507 : 549; K = 8192 at 512 1374 : 786.
 bool rvq_share_fits(const rvq_ctx *ctx, int64_t V) {
   const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
-  const int64_t most = 128 + ctx->Kpad / 8;
+  const int64_t most = ctx->Kpad <= 2048 ? 128 + ctx->Kpad / 8 : 256 + ctx->Kpad / 32;
   return V > 2 * cus && V <= cus * (most < SHR_TOKENS ? most : SHR_TOKENS);
 }
 

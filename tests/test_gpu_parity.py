@@ -292,7 +292,8 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
     (33025, 1, 2048, 2, oracle.CONTIGUOUS, "bf16", 1, "plain"),     # std computed beforehand
     (98304, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # 384 tokens per CU, the most at K = 2048
     (98336, 32, 2048, 1, oracle.STRIDED, "bf16", 1, "plain"),       # one row more: the large kernel
-    (131072, 128, 4096, 1, oracle.STRIDED, "fp16", 1, "plain"),     # 512 tokens, two pieces
+    (98304, 128, 4096, 1, oracle.STRIDED, "fp16", 1, "plain"),      # the most at K = 4096, two pieces
+    (131072, 1, 8192, 1, oracle.CONTIGUOUS, "fp32", 0, "plain"),    # 512 tokens per CU, four pieces
     (1000, 1, 33, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),        # a padded tile
     (1000, 1, 512, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),       # the codebook splits of the wavefronts
     (1000, 1, 513, 2, oracle.CONTIGUOUS, "fp32", 0, "plain"),
