@@ -31,8 +31,8 @@ struct rvq_ctx {
   float *normp;        // [depth][Kpad/32][2][16] ||c||^2 minus the group's second-order error
                        //   term, in accumulator-register order
   float *groupA;       // [depth][Kpad/16] largest ||2c|| of each (tile, half) group
-  int32_t *perm;       // [depth][Kpad] position -> codeword index (-1 for padding and repeats)
-  uint16_t *perm16;    // the same, 0xffff for padding
+  int32_t *perm;       // [depth][Kpad] codewords by norm (-1 for padding and in the places of repeats)
+  uint16_t *perm16;    // position -> codeword index: the same without the repeats, 0xffff for padding
   float *stats;        // [depth][8]: rounding-error bounds and scales of the fp16 operands
   float *rowmax;       // [depth][K] largest |2 c| of each codeword (infinity: not finite)
   int32_t num_cus;     // compute units of the device (persistent kernels launch one workgroup each)

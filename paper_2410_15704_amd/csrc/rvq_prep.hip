@@ -1,8 +1,10 @@
 // Derived codebook data.
 //   norms  : squared norms of the codewords, the constant term of ||c||^2 - 2 r.c
 // and, for the matrix-core screen (dhat == 32), per stage:
-//   perm   : the codewords ordered by norm (ties by index); position pos = tile * 32 + row;
-//            perm16 is the same as uint16 with 0xffff for padding (what the kernel keeps in LDS)
+//   perm   : the codewords ordered by norm (ties by index), -1 where a repeat would stand
+//   perm16 : position pos = tile * 32 + row -> codeword: the same order with the repeats left out and
+//            the others closed up, as uint16, 0xffff for the padding at the end (what the kernels keep
+//            in LDS)
 //   C16    : fp16(-2 c) of the codeword at each position, laid out exactly as the A operand of
 //            v_mfma_f32_32x32x16_f16 is read, so the kernel copies it into LDS linearly and a
 //            lane's operand is one 16-byte LDS read
@@ -15,8 +17,8 @@
 //            are below the smallest normal half; [3] S and [4] T, the powers of two the codebook
 //            and the residuals are scaled by before rounding to fp16 (chosen so that the largest
 //            |S a| lies in [2^13, 2^14) and T = S / 2); [5] the largest |a|
-// A codeword that repeats an earlier one exactly can never win (ties go to the smallest index);
-// its position stays empty, like the padding at the end.
+// A codeword that repeats an earlier one exactly can never win (ties go to the smallest index): it
+// gets no position.
 // Ordering by norm keeps the norms inside a group close to each other, which is what makes the
 // per-group error bound of the screen tight when a few codewords are much longer than the rest.
 #include "rvq_internal.h"
@@ -82,9 +84,8 @@ __global__ __launch_bounds__(256) void prep_rows32_kernel(
 
 // One workgroup per codeword: its position in the order (norm, index) of the stage's codewords, K^2
 // comparisons per stage spread over K workgroups, and whether it is an exact repeat of an earlier one
-// (equal rows have equal norms).  A repeat leaves its position empty.  (One kernel: with the repeats
-// found first, so that the others close ranks, an update of a stage took a launch more, and the search
-// reads whole tiles either way.)
+// (equal rows have equal norms).  A repeat leaves its position empty; screen_tile_kernel closes the
+// ranks.
 __global__ __launch_bounds__(256) void rank_kernel(const float *__restrict__ C,
                                                    const float *__restrict__ norms, int K, int Kpad,
                                                    int stage_begin, int32_t *__restrict__ perm) {
@@ -113,6 +114,11 @@ __global__ __launch_bounds__(256) void rank_kernel(const float *__restrict__ C,
 
 // One workgroup per (stage, tile of 32 positions), one lane per (position, channel): the fp16
 // operands, perm16, the error statistics, and per (tile, lane half) group normp and groupA.
+// The repeats' empty positions are closed up here, by a prefix sum over the stage's order in every
+// workgroup (one entry per thread and 1024 codewords).  Left open they move codewords of nearly equal norm
+// into different groups: dead codewords repeat the zero vector, a short residual's candidates then
+// lie in two groups instead of one, and the second ones overflow the search's queues (a stage of 1024
+// codewords, 3 of them repeats: 62 us for 177441 vectors closed up, 207 us with the positions left empty).
 // Operand order: tile t = pos / 32, row m = pos % 32; the lane (m, h) of matrix-core instruction
 // q holds dims 16 h + 8 q .. + 7 of row m, as two 8-byte pieces at
 // (((t * 2 + q) * 2 + piece) * 64 + h * 32 + m) * 8.
@@ -123,6 +129,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     float *__restrict__ normp,
     float *__restrict__ groupA, float *__restrict__ stats) {
   __shared__ float red[16];
+  __shared__ int wave_held[16], here[32];  // codewords of the tile's rows, -1: none
   __shared__ float nrm[32], len[32], rho_s[32], drop_s[32];
   const int tiles = Kpad / 32;
   const int stage = stage_begin + blockIdx.x / tiles;
@@ -134,6 +141,28 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
   for (int i = threadIdx.x; i < K; i += 1024) mxa = fmaxf(mxa, rowmax[(int64_t)stage * K + i]);
   for (int o = 32; o > 0; o >>= 1) mxa = fmaxf(mxa, __shfl_xor(mxa, o, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mxa;
+  // this thread's entries of the order, and how many codewords they hold
+  const int32_t *order = perm + (int64_t)stage * Kpad;
+  const int per = (Kpad + 1023) / 1024;
+  const int i0 = min((int)threadIdx.x * per, Kpad), i1 = min(i0 + per, Kpad);
+  int held = 0;
+  for (int i = i0; i < i1; ++i) held += order[i] >= 0 ? 1 : 0;
+  int before = held;  // inclusive sum over the wavefront
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(before, o, 64);
+    before += (int)(threadIdx.x & 63) >= o ? v : 0;
+  }
+  if ((threadIdx.x & 63) == 63) wave_held[threadIdx.x >> 6] = before;
+  if (threadIdx.x < 32) here[threadIdx.x] = -1;
+  __syncthreads();
+  before -= held;  // codewords in front of this thread's
+  for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) before += wave_held[w];
+  if (before < t * 32 + 32 && before + held > t * 32)
+    for (int i = i0; i < i1; ++i)
+      if (order[i] >= 0) {
+        if ((before >> 5) == t) here[before & 31] = order[i];
+        ++before;
+      }
   __syncthreads();
   mxa = red[0];
   for (int i = 1; i < 16; ++i) mxa = fmaxf(mxa, red[i]);
@@ -150,7 +179,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     stats[stage * 8 + 4] = T;
     stats[stage * 8 + 5] = finite ? mxa : 0.f;
   }
-  const int k = perm[(int64_t)stage * Kpad + pos];
+  const int k = here[m];
   float a = 0.f;
   if (k >= 0) a = -2.0f * S * C[((int64_t)stage * K + k) * 32 + j];  // exact in fp32
   // values below the smallest normal half are dropped so that the error bound does not depend

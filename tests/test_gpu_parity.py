@@ -354,6 +354,34 @@ def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
             assert torch.equal(x[rows].view(torch.uint8), y[rows].view(torch.uint8)), name
 
 
+@pytest.mark.parametrize("K, repeats", [(1024, 24), (1024, 60), (2048, 40), (64, 31)])
+def test_repeated_codewords_cost_nothing(gpu_device, K, repeats):
+    """Exact repeats of a codeword get no position in the search's order, so K codewords of which some
+    are repeats are searched with the same groups, candidates and queue entries as the others
+    alone (both sizes pad to the same number of tiles): equal codes and equal statistics.  Repeats
+    of the zero vector, as dead codewords are, and vectors near it show a difference first."""
+    torch, b = _torch(), _b()
+    V = 5000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + repeats)
+    C = torch.randn((2, K, 32), device="cuda", generator=gen) * torch.rand((2, K, 1), device="cuda", generator=gen)
+    C[:, 5] = 0.0
+    C[:, K - repeats:] = C[:, 5:6]
+    C[0, K - 1] = C[0, 7]
+    X = torch.randn((V, 32), device="cuda", generator=gen)
+    X[::3] *= 0.05
+    got = []
+    for n in (K, K - repeats):
+        q = b.Quantizer(d=32, dhat=32, depth=2, K=n, scale=0, encode_path=b.PATH_SCREEN)
+        q.set_codebooks(C[:, :n].contiguous())
+        codes, _, res = q.encode(X, want_residual=True)
+        torch.cuda.synchronize()
+        got.append((codes, res, b.rvq_get_counters(q.ctx)))
+        q.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2] == got[1][2]
+
+
 def test_encode_chunks_of_512_and_of_1024_agree(gpu_device):
     """A call with at most 512 vectors per CU runs the matrix-core kernel with one token per lane
     (chunks of 512), a larger one with two (chunks of 1024).  A token's codes do not depend on
