@@ -70,8 +70,7 @@ int encode_enqueue(rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx, int sta
                                            dResidual, dStd, s));
       return RVQ_OK;
     }
-    // (a lowered poll limit is meant for the kernel that has bounded waits: the call goes there)
-    if (rvq_share_fits(ctx, V) && ctx->wait_polls == RVQ_WAIT_POLLS_DEFAULT) {
+    if (rvq_share_fits(ctx, V)) {
       if (rvq_share_needs_std(ctx, N))
         RVQ_HIP(ctx, rvq_launch_row_std(ctx, dX, N, ldx, dStd, std32, s));
       RVQ_HIP(ctx, rvq_launch_encode_share(ctx, dX, N, ldx, stage_begin, stage_end, dCodes, dResidual,

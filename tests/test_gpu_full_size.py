@@ -384,15 +384,16 @@ def test_enqueue_calls_neither_allocate_nor_synchronize(gpu_device):
 
 
 def test_bounded_wait_reports_instead_of_hanging(gpu_device):
-    """The wavefronts of the encode kernel wait for each other through counters in LDS.  With the
-    bound on those waits set to zero polls every wait that is not already satisfied gives up: the
+    """The wavefronts of the matrix-core kernel of RVQ_PATH_SCREEN (the path is asked for: the library
+    sends a call of this size elsewhere) wait for each other through counters in LDS.  With the bound on those waits set to zero polls every wait that is not already satisfied gives up: the
     kernel must still run to its end, the context must report RVQ_EKERNEL once, and with the
     default bound the same context must encode correctly again."""
     torch, b = _torch(), _b()
     N, d, depth, K = 2048, 1024, 8, 2048
     X, _ = synth.llama_key(N, d)
     C = _codebooks_from_samples(synth.widen(X[:256], "bf16"), 32, oracle.STRIDED, depth, K, seed=9)
-    q = b.Quantizer(d=d, dhat=32, depth=depth, K=K, grouping=b.STRIDED, in_dtype=b.BF16, std_dtype=b.F32)
+    q = b.Quantizer(d=d, dhat=32, depth=depth, K=K, grouping=b.STRIDED, in_dtype=b.BF16, std_dtype=b.F32,
+                    encode_path=b.PATH_SCREEN)
     q.set_codebooks(torch.from_numpy(C).cuda())
     dX = torch.from_numpy(X.view(np.int16)).cuda().view(torch.bfloat16)
     good, _, _ = q.encode(dX)
@@ -409,6 +410,30 @@ def test_bounded_wait_reports_instead_of_hanging(gpu_device):
     assert b.rvq_check_kernels(q.ctx, check=False) == 0
     assert b.lib.rvq_debug_set_wait_polls(q.ctx, -1) == b.RVQ_EINVAL
     q.close()
+
+
+@pytest.mark.parametrize("V", [300, 513, 4096, 20000])
+def test_the_wait_bound_does_not_choose_the_kernel(gpu_device, V):
+    """rvq_debug_set_wait_polls bounds waits and nothing else: with a bound of zero, calls of few
+    vectors (whose kernels have no waits) report no expired wait and return what they return with
+    the default bound, for at most 4096 vectors the codes of the exact path."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    C = torch.randn((3, 1000, 32), device="cuda", generator=gen)
+    X = torch.randn((V, 32), device="cuda", generator=gen)
+    got = []
+    for path, polls in ((b.PATH_AUTO, None), (b.PATH_AUTO, 0), (b.PATH_AUTO, 0x7fffffff), (b.PATH_EXACT, None)):
+        q = b.Quantizer(d=32, dhat=32, depth=3, K=1000, std_dtype=b.F32, encode_path=path)
+        q.set_codebooks(C)
+        if polls is not None:
+            b.rvq_debug_set_wait_polls(q.ctx, polls)
+        got.append(q.encode(X, want_residual=True))
+        torch.cuda.synchronize()
+        assert b.rvq_check_kernels(q.ctx, check=False) == 0, (path, polls)
+        q.close()
+    for other in got[1:3] + (got[3:] if V <= 4096 else []):
+        assert all(torch.equal(x, y) for x, y in zip(got[0], other))
 
 
 # ------------------------------------------------------------------------- non-finite inputs
