@@ -27,13 +27,15 @@
 //     compared once more, summed in encode_screen_kernel's order, so that the two agree there.)
 //  A token whose residual does not fit fp16 is searched exactly over the whole stage by the workgroup.
 //
-// What bounds it: up to 16 tokens per workgroup a stage takes 5 us, a chain of latencies (the next
+// What bounds it: up to 16 tokens per workgroup (FEW) a stage takes 3.8 us, a chain of latencies (the next
 // stage's 128 KiB of operands through the CU's L1, the first rows of exact distances, four barriers
-// and their LDS round trips); beyond that the vector issue port, 80 clocks per token for sweep and pick and
-// 43 for the resolve step (matrix cores alone: 32).
+// and their LDS round trips).  With more tokens the general form: at 188 per workgroup the vector units
+// issue in 59 % of the cycles (matrix cores 15 %, L1 address path 31 %); the rest is the sixteen
+// wavefronts in step at a barrier per pair of tiles, and what a stage costs once.  At TPW = 4 its 128
+// registers do not hold everything: 21 values per lane are spilled (9 at TPW = 2, 6 at TPW = 1).
 // Measured, rows of 32 groups, K = 2048, depth 8, before (small-batch or one-token-per-lane kernel) and
-// now: 32 rows 58 -> 47 us, 48 rows 84 -> 46, 128 rows 157 -> 48, 512 rows 190 -> 71, 1500 rows
-// 206 -> 124, 3000 rows 222 -> 212 us; K = 4096, 256 rows of 128 groups 457 -> 156 us.
+// now: 32 rows 55 -> 31 us, 48 rows 83 -> 31, 128 rows 157 -> 34, 512 rows 203 -> 71, 1500 rows
+// 217 -> 123, 3000 rows 215 -> 212 us; K = 4096, 32 rows of 128 groups 156 -> 68 us, 300 rows 196 us.
 #include <type_traits>
 
 #include "rvq_internal.h"
@@ -151,16 +153,76 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
   return min(min(r0, r1), min(r2, r3));
 }
 
+typedef __attribute__((address_space(1))) const char glb_char;
+typedef __attribute__((address_space(1))) const f32x4 glb_c4;
+typedef __attribute__((address_space(3))) const f32x4 lds_c4;
+typedef __attribute__((address_space(3))) const uint16_t lds_c16;
+typedef __attribute__((address_space(3))) unsigned long long lds_u64;
+__device__ __forceinline__ void lds_min(lds_u64 *p, unsigned long long v) {
+  (void)__hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Exact search over the whole stage for the `ns` tokens listed in `slow`, by all wavefronts: each holds 128
+// codewords at a time and scores all of the tokens against them, so a codeword is fetched once for all
+// and the caller needs one barrier.  K = 2048, sixteen tokens: 27 us a stage (one token after the other with
+// two barriers each 48; the small-batch kernel, which this replaces there, 20).
+__device__ __forceinline__ void search_slow(lds_c4 *res, lds_u64 *best, lds_c16 *slow, int ns, glb_char *Cs,
+                                            int K, int wave, int lane) {
+  constexpr int SLOTS = 8;
+  // four lanes per codeword, eight channels each; the partial sums meet in the exact path's tree
+  const int pc = (lane & 3) * 2;
+  for (int k0 = wave * 16 * SLOTS; k0 < K; k0 += SHR_WAVES * 16 * SLOTS) {
+    f32x4 c0[SLOTS], c1[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+      const int k = min(k0 + 16 * j + (lane >> 2), K - 1);  // past the end: fetched, not scored
+      glb_c4 *src = (glb_c4 *)(Cs + ((uint32_t)k * 128u + (uint32_t)pc * 16u));
+      c0[j] = src[0];
+      c1[j] = src[1];
+    }
+    for (int i = 0; i < ns; ++i) {
+      const int tok = slow[i];
+      const f32x4 r0 = res[tok * 8 + pc], r1 = res[tok * 8 + pc + 1];
+      uint32_t bits = 0x7f800000u, idx = 0;
+#pragma unroll
+      for (int j = 0; j < SLOTS; ++j) {
+        float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float d0 = r0[e] - c0[j][e], d1 = r1[e] - c1[j][e];
+          p0 = fmaf(d0, d0, p0);
+          p1 = fmaf(d1, d1, p1);
+        }
+        float dist = p0 + p1;
+        dist += shr_dpp<0xB1>(dist);
+        dist += shr_dpp<0x4E>(dist);
+        const uint32_t db = __float_as_uint(dist);
+        const int k = k0 + 16 * j + (lane >> 2);
+        if (k < K && db < bits) {  // a lane's later codewords have the larger indices
+          bits = db;
+          idx = (uint32_t)k;
+        }
+      }
+      const uint32_t m = wave_min(bits);
+      const uint32_t k = wave_min(bits == m ? idx : 0xffffffffu);
+      if (lane == 0) lds_min(best + tok, ((unsigned long long)m << 32) | k);
+    }
+  }
+}
+
 // TPW: tiles of 32 codewords per wavefront; a piece of 512 TPW codewords is in registers at a time
 // (32 registers of operands and 32 of norms at TPW = 4, of the 128 that sixteen wavefronts leave
 // each other).  K <= 2048 is one piece; larger codebooks are swept and resolved piece after piece, with
 // the threshold and the best codeword carried over.
-template <int TPW>
+// FEW: at most SHR_FEW vectors in all and 16 in a workgroup, so one tile of tokens, a single step of the
+// resolve loop, no near-ties to decide another way and nothing to count.  Without those branches the
+// registers suffice, also with the rare paths in line (48 rows of 32 groups, K = 2048: 47 us in the
+// general form, 31 here).
+template <int TPW, bool FEW>
 __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareArgs a) {
   constexpr int PIECE = 512 * TPW;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ float row_sd[SHR_TOKENS + 2];
-  __shared__ unsigned long long wave_best[SHR_WAVES];
   __shared__ int slow_n[2];  // tokens for the exact search, stages of even and of odd number
   __shared__ unsigned stat[2];
   const int tid = threadIdx.x;
@@ -171,7 +233,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   const int q = lane & 7;       // resolve: this lane's four channels, 4 q .. 4 q + 3
   const int64_t v0 = (int64_t)blockIdx.x * a.vpw;
   const int nvalid = (int)min((int64_t)a.vpw, a.V - v0);
-  const int ntiles = (a.vpw + 15) >> 4;
+  const int ntiles = FEW ? 1 : (a.vpw + 15) >> 4;
   const int T = ntiles * 16;
   const ShareLds L = share_lds(T, PIECE);
   uint4 *lds_B = reinterpret_cast<uint4 *>(smem + L.B);
@@ -283,7 +345,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   if (tid < 2) stat[tid] = 0;
   // ---- the rows' std (the arithmetic of row_std_kernel), the tokens' channels, the first operands
   const int64_t n_first = v0 / a.G;
-  if (a.scale && !a.std32) {
+  if (a.scale && (FEW || !a.std32)) {
     const int nrows = (int)((v0 + nvalid - 1) / a.G - n_first) + 1;  // <= SHR_TOKENS + 1
     const int d = a.G * 32;
     for (int w = wave; w < nrows; w += SHR_WAVES) {
@@ -317,7 +379,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
     if (tok < nvalid) {
       const int64_t v = v0 + tok, n = v / a.G;
       const int g = (int)(v - n * a.G);
-      const float sd = a.std32 ? a.std32[n] : (a.scale ? row_sd[n - n_first] : 1.0f);
+      const float sd = !FEW && a.std32 ? a.std32[n] : (a.scale ? row_sd[n - n_first] : 1.0f);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int j = 4 * q + e;
@@ -403,7 +465,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
       // threshold marks its eight codewords (rows 4 lg .. + 3 and 16 + 4 lg .. + 3 of the tile)
       auto pick = [&](int s, const float (&mm)[2][TPW]) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < (FEW ? 1 : 2); ++u) {
           const int tile = 2 * s + u;
           if (u == 0 || tile < ntiles) {
             const int tok = tile * 16 + tcol;
@@ -424,7 +486,8 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
       // (Sweeping the next pair before this one is picked from, to have work on both sides of the
       // barrier, costs eight more registers per wavefront: the compiler then spills operands, and 4096
       // rows took 365 us instead of 274.)
-      const int pairs = (ntiles + 1) >> 1;
+      const int nslow = slow_n[stage & 1];
+      const int pairs = nslow < nvalid ? (ntiles + 1) >> 1 : 0;  // nothing to sweep when all of them are
       float mm[2][TPW];
       for (int s = 0; s < pairs; ++s) {
         sweep(s, mm);
@@ -444,45 +507,12 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         return __builtin_bit_cast(
             f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsC, k * 128 + piece16 * 16, sC, 0));
       };
-      // ---- exact search for the tokens that need it, by the whole workgroup
-      const int ns = piece == 0 ? slow_n[stage & 1] : 0;
+      // ---- exact search for the tokens that need it
+      const int ns = piece == 0 ? nslow : 0;
       if (ns > 0) {
-        for (int i = 0; i < ns; ++i) {
-          const int tok = lds_slow[i];
-          // four lanes per codeword, eight channels each; the partial sums meet in the exact path's tree
-          const int pc = (lane & 3) * 2;
-          const f32x4 r0 = lds_r[tok * 8 + pc], r1 = lds_r[tok * 8 + pc + 1];
-          uint32_t bits = 0x7f800000u, idx = 0;
-          for (int k0 = wave * 16; k0 < a.K; k0 += SHR_WAVES * 16) {
-            const int k = k0 + (lane >> 2);
-            const f32x4 c0 = row(min(k, a.K - 1), pc), c1 = row(min(k, a.K - 1), pc + 1);
-            float p0 = 0.f, p1 = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float d0 = r0[e] - c0[e], d1 = r1[e] - c1[e];
-              p0 = fmaf(d0, d0, p0);
-              p1 = fmaf(d1, d1, p1);
-            }
-            float dist = p0 + p1;
-            dist += shr_dpp<0xB1>(dist);
-            dist += shr_dpp<0x4E>(dist);
-            const uint32_t db = __float_as_uint(dist);
-            if (k < a.K && db < bits) {  // a lane's later codewords have the larger indices
-              bits = db;
-              idx = (uint32_t)k;
-            }
-          }
-          const uint32_t m = wave_min(bits);
-          const uint32_t k = wave_min(bits == m ? idx : 0xffffffffu);
-          if (lane == 0) wave_best[wave] = ((unsigned long long)m << 32) | k;
-          lds_barrier();
-          if (tid == 0) {
-            unsigned long long best = wave_best[0];
-            for (int w = 1; w < SHR_WAVES; ++w) best = wave_best[w] < best ? wave_best[w] : best;
-            lds_b[tok] = best;
-          }
-          lds_barrier();
-        }
+        search_slow((lds_c4 *)lds_r, (lds_u64 *)lds_b, (lds_c16 *)lds_slow, ns,
+                    (glb_char *)(a.C32 + (int64_t)stage * a.K * 32), a.K, wave, lane);
+        lds_barrier();
         if (wave == 0) n_slow += (unsigned)ns;
       }
 
@@ -542,8 +572,8 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         // Two distances that differ by less than their rounding (34 + 9 roundings of 2^-24 on either
         // side), in a call that encode_screen_kernel took before: its order of summation decides, one
         // codeword of a group per lane.
-        bool near = a.tie_serial && valid && second <= bd * 1.000006f;
-        if (__any(near)) {
+        const bool near = !FEW && a.tie_serial && valid && second <= bd * 1.000006f;
+        if (!FEW && __any(near)) {
           const int k0 = (int)(best0 & 0xffffffffull);
           unsigned long long sb = SHR_NONE;
           auto serial = [&](unsigned k) {
@@ -599,7 +629,8 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
       };
       if (tid >> 3 < T) {  // uniform over a wavefront: T is a multiple of 16
         resolve(0, std::true_type());
-        for (int t0 = SHR_PASS; t0 + (tid >> 3) < T; t0 += SHR_PASS) resolve(t0, std::false_type());
+        if constexpr (!FEW)
+          for (int t0 = SHR_PASS; t0 + (tid >> 3) < T; t0 += SHR_PASS) resolve(t0, std::false_type());
       } else {
         // no token of its own: let the other wavefronts' rows go first
         __builtin_amdgcn_s_sleep(8);
@@ -608,7 +639,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
     }
   }
 
-  if (a.counters) {  // one update per workgroup
+  if (!FEW && a.counters) {  // one update per workgroup
     if (lane == 0) {
       atomicAdd(&stat[0], n_slow);
       atomicAdd(&stat[1], n_exact);
@@ -689,17 +720,22 @@ hipError_t rvq_launch_encode_share(const rvq_ctx *ctx, const void *dX, int64_t N
   a.tie_serial = a.V > SHR_FEW;
   a.kappa = ctx->kappa;
   const int T = (a.vpw + 15) / 16 * 16;
+  const bool few = a.V <= SHR_FEW && T == 16;
   const int64_t grid64 = (a.V + a.vpw - 1) / a.vpw;
   if (grid64 > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)grid64), block(SHR_THREADS);
 #define RVQ_LAUNCH_SHARE(TPW)                                                                    \
   do {                                                                                           \
     const size_t lds = share_lds(T, 512 * (TPW)).bytes;                                          \
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&encode_share_kernel<TPW>), \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,               \
-                                       (int)share_lds(SHR_TOKENS, 512 * (TPW)).bytes);           \
+    if (few) {                                                                                   \
+      hipLaunchKernelGGL((encode_share_kernel<TPW, true>), grid, block, lds, s, a);              \
+      break;                                                                                     \
+    }                                                                                            \
+    hipError_t e = hipFuncSetAttribute(                                                          \
+        reinterpret_cast<const void *>(&encode_share_kernel<TPW, false>),                        \
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)share_lds(SHR_TOKENS, 512 * (TPW)).bytes); \
     if (e != hipSuccess) return e;                                                               \
-    hipLaunchKernelGGL(encode_share_kernel<TPW>, grid, block, lds, s, a);                        \
+    hipLaunchKernelGGL((encode_share_kernel<TPW, false>), grid, block, lds, s, a);               \
   } while (0)
   // as many codewords per wavefront as make one piece, up to 2048 per workgroup
   if (ctx->Kpad <= 512) RVQ_LAUNCH_SHARE(1);

@@ -304,6 +304,9 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
     (3000, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "repeats"),    # repeated and zero codewords
     (3000, 1, 700, 2, oracle.CONTIGUOUS, "fp32", 0, "huge"),        # residuals beyond fp16: exact search
     (3000, 1, 4096, 2, oracle.CONTIGUOUS, "fp32", 0, "nan"),
+    (600, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "all huge"),    # every token: no sweep at all
+    (4000, 1, 5000, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
+    (6000, 1, 300, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
 ])
 def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
     """The kernel whose wavefronts share a stage's codebook, at the edges of its tiles, pieces and vector
@@ -325,6 +328,10 @@ def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
     elif kind == "repeats":
         C[:, K // 2:] = C[:, :K - K // 2]
         C[:, 5:40] = 0.0
+    elif kind == "all huge":
+        X *= 1e6
+    elif kind == "inf codebook":  # no screen of that stage
+        C[0, 7, 3], C[1, K - 1, 0] = float("inf"), float("nan")
     elif kind == "huge":
         X[::7] *= 1e6
         X[3] = 3e38
