@@ -27,15 +27,15 @@
 //     compared once more, summed in encode_screen_kernel's order, so that the two agree there.)
 //  A token whose residual does not fit fp16 is searched exactly over the whole stage by the workgroup.
 //
-// What bounds it: up to 16 tokens per workgroup (FEW) a stage takes 3.8 us, a chain of latencies (the next
+// What bounds it: up to 16 tokens per workgroup (FEW) a stage takes 4.1 us, a chain of latencies (the next
 // stage's 128 KiB of operands through the CU's L1, the first rows of exact distances, four barriers
 // and their LDS round trips).  With more tokens the general form: at 188 per workgroup the vector units
 // issue in 59 % of the cycles (matrix cores 15 %, L1 address path 31 %); the rest is the sixteen
 // wavefronts in step at a barrier per pair of tiles, and what a stage costs once.  At TPW = 4 its 128
 // registers do not hold everything: 21 values per lane are spilled (9 at TPW = 2, 6 at TPW = 1).
 // Measured, rows of 32 groups, K = 2048, depth 8, before (small-batch or one-token-per-lane kernel) and
-// now: 32 rows 55 -> 31 us, 48 rows 83 -> 31, 128 rows 157 -> 34, 512 rows 203 -> 71, 1500 rows
-// 217 -> 123, 3000 rows 215 -> 212 us; K = 4096, 32 rows of 128 groups 156 -> 68 us, 300 rows 196 us.
+// now: 32 rows 55 -> 34 us, 48 rows 83 -> 34, 128 rows 157 -> 37, 512 rows 203 -> 71, 1500 rows
+// 217 -> 123, 3000 rows 215 -> 212 us; K = 4096, 32 rows of 128 groups 156 -> 71 us, 300 rows 196 us.
 #include <type_traits>
 
 #include "rvq_internal.h"
@@ -157,6 +157,7 @@ typedef __attribute__((address_space(1))) const char glb_char;
 typedef __attribute__((address_space(1))) const f32x4 glb_c4;
 typedef __attribute__((address_space(3))) const f32x4 lds_c4;
 typedef __attribute__((address_space(3))) const uint16_t lds_c16;
+typedef __attribute__((address_space(3))) unsigned lds_u32;
 typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 __device__ __forceinline__ void lds_min(lds_u64 *p, unsigned long long v) {
   (void)__hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -210,6 +211,70 @@ __device__ __forceinline__ void search_slow(lds_c4 *res, lds_u64 *best, lds_c16 
   }
 }
 
+// Exact distances of one token's marked groups, by a wavefront, eight groups at a time; the token's best
+// codeword so far takes the place of its marks.  For few tokens with many candidates (codewords
+// crowded into clusters): the kernel's own resolve step takes a token's groups one after the other, a
+// round trip to L2 each, with most wavefronts idle.  600 vectors, K = 2048 in clusters of 64, depth 4: 44 us
+// without it, 27 with it.  (Out of line: in line its registers are made room for on the common path, 48
+// rows of 32 groups 37 us instead of 34.)
+template <int TPW>
+__device__ __noinline__ void resolve_crowded(lds_c4 *res, lds_u64 *best_p, lds_u32 *mark, lds_c16 *perm,
+                                                glb_char *Cs, int K, int lane) {
+  const int q = lane & 7, sub = lane >> 3;
+  const unsigned word = mark[sub];
+  const f32x4 r = res[q];
+  // The marks of the eight words in order have ranks 0, 1, ...; in a round subgroup j of the wavefront takes
+  // the mark of rank base + j.  rank0: rank of this word's first one.
+  int rank0 = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const int n = __popc((unsigned)__builtin_amdgcn_readlane((int)word, 8 * w));
+    rank0 += w < sub ? n : 0;
+    total += n;
+  }
+  unsigned long long best = SHR_NONE;
+  unsigned left = word;
+  int next = rank0;  // rank of the first mark left in the word
+  for (int base = 0; base < total; base += 8) {
+    int g = -1;
+    for (int j = 0; j < 8; ++j) {
+      const bool mine = left != 0 && next == base + j;
+      const unsigned long long b = __ballot(mine);
+      if (b != 0) {
+        const int src = __ffsll((long long)b) - 1;
+        const int bit = __ffs((unsigned)__builtin_amdgcn_readlane((int)left, src)) - 1;
+        g = sub == j ? (src >> 3) * 32 + bit : g;
+        if (mine) {
+          left &= left - 1;
+          ++next;
+        }
+      }
+    }
+    const int gc = g < 0 ? 0 : g;  // (no group: position 0, whose true distances may take part)
+    const int pos = ((gc >> 4) * TPW + (gc & 3)) * 32 + (gc & 12);
+    f32x4 c[8];
+    unsigned k[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      k[e] = perm[pos + (e & 3) + 4 * (e & 4)];
+      c[e] = *(glb_c4 *)(Cs + (min(k[e], (unsigned)(K - 1)) * 128u + (uint32_t)q * 16u));
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float p = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float d = r[i] - c[e][i];
+        p = fmaf(d, d, p);
+      }
+      const unsigned long long key = ((unsigned long long)__float_as_uint(sum8(p)) << 32) | k[e];
+      best = key < best ? key : best;
+    }
+  }
+  if (q == 0) lds_min(best_p, best);
+  if (q == 0) mark[sub] = 0u;
+}
+
 // TPW: tiles of 32 codewords per wavefront; a piece of 512 TPW codewords is in registers at a time
 // (32 registers of operands and 32 of norms at TPW = 4, of the 128 that sixteen wavefronts leave
 // each other).  K <= 2048 is one piece; larger codebooks are swept and resolved piece after piece, with
@@ -217,7 +282,7 @@ __device__ __forceinline__ void search_slow(lds_c4 *res, lds_u64 *best, lds_c16 
 // FEW: at most SHR_FEW vectors in all and 16 in a workgroup, so one tile of tokens, a single step of the
 // resolve loop, no near-ties to decide another way and nothing to count.  Without those branches the
 // registers suffice, also with the rare paths in line (48 rows of 32 groups, K = 2048: 47 us in the
-// general form, 31 here).
+// general form, 34 here).
 template <int TPW, bool FEW>
 __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareArgs a) {
   constexpr int PIECE = 512 * TPW;
@@ -515,6 +580,21 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         lds_barrier();
         if (wave == 0) n_slow += (unsigned)ns;
       }
+      // ---- many candidates: a wavefront to a token (otherwise 1.03 groups per token are marked, and the
+      // resolve step has its wavefronts' tokens side by side).  Every wavefront counts all marks, two
+      // words per lane: kept by an atomic add in the sweep instead, the count cost 0.7 us a stage.
+      if constexpr (FEW) {
+        const uint2 w = reinterpret_cast<const uint2 *>(lds_h)[lane];
+        unsigned n = __popc(w.x) + __popc(w.y);
+        n += shr_dppu<0xB1>(n);
+        n += shr_dppu<0x4E>(n);
+        if (__any(n > 5)) {
+          if (wave < nvalid)
+            resolve_crowded<TPW>((lds_c4 *)lds_r + wave * 8, (lds_u64 *)lds_b + wave, (lds_u32 *)lds_h + wave * 8,
+                                 (lds_c16 *)perm, (glb_char *)(a.C32 + (int64_t)stage * a.K * 32), a.K, lane);
+          lds_barrier();
+        }
+      }
 
       // ---- resolve
       const StageConsts scn = stage_consts(min(stage + 1, a.depth - 1));
@@ -552,6 +632,10 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
           f32x4 c[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) c[e] = row((int)min(k[e], (unsigned)(a.K - 1)), q);
+          // (all eight in flight before the first is used: one round trip.  Left to itself the compiler
+          // here scores them four and four, 0.6 us a stage.)
+          if constexpr (FEW)
+            asm volatile("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7]));
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             float p = 0.f;

@@ -304,6 +304,9 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
     (3000, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "repeats"),    # repeated and zero codewords
     (3000, 1, 700, 2, oracle.CONTIGUOUS, "fp32", 0, "huge"),        # residuals beyond fp16: exact search
     (3000, 1, 4096, 2, oracle.CONTIGUOUS, "fp32", 0, "nan"),
+    (600, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "crowded"),     # ... a wavefront to a token
+    (1500, 3, 256, 2, oracle.STRIDED, "fp16", 1, "crowded"),
+    (2000, 1, 5000, 2, oracle.CONTIGUOUS, "fp32", 0, "crowded"),    # ... piece after piece
     (600, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "all huge"),    # every token: no sweep at all
     (4000, 1, 5000, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
     (6000, 1, 300, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
