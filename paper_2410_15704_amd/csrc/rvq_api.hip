@@ -70,7 +70,7 @@ int encode_enqueue(rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx, int sta
                                            dResidual, dStd, s));
       return RVQ_OK;
     }
-    if (rvq_share_fits(ctx, V)) {
+    if (rvq_share_fits(ctx, V, stage_end - stage_begin)) {
       if (rvq_share_needs_std(ctx, N))
         RVQ_HIP(ctx, rvq_launch_row_std(ctx, dX, N, ldx, dStd, std32, s));
       RVQ_HIP(ctx, rvq_launch_encode_share(ctx, dX, N, ldx, stage_begin, stage_end, dCodes, dResidual,

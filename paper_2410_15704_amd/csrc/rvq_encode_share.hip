@@ -163,13 +163,14 @@ __device__ __forceinline__ void lds_min(lds_u64 *p, unsigned long long v) {
   (void)__hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Exact search over the whole stage for the `ns` tokens listed in `slow`, by all wavefronts: each holds 128
-// codewords at a time and scores all of the tokens against them, so a codeword is fetched once for all
-// and the caller needs one barrier.  K = 2048, sixteen tokens: 27 us a stage (one token after the other with
+// Exact search over the whole stage for the `ns` tokens listed in `slow`, by all wavefronts: each holds
+// 16 SLOTS codewords at a time and scores all of the tokens against them, so a codeword is fetched once
+// for all and the caller needs one barrier.  (SLOTS = 8 costs the general form spills: one stage of K = 256
+// for 32768 vectors 18.7 -> 19.4 us.)  K = 2048, sixteen tokens: 27 us a stage (one token after the other with
 // two barriers each 48; the small-batch kernel, which this replaces there, 20).
+template <int SLOTS>
 __device__ __forceinline__ void search_slow(lds_c4 *res, lds_u64 *best, lds_c16 *slow, int ns, glb_char *Cs,
                                             int K, int wave, int lane) {
-  constexpr int SLOTS = 8;
   // four lanes per codeword, eight channels each; the partial sums meet in the exact path's tree
   const int pc = (lane & 3) * 2;
   for (int k0 = wave * 16 * SLOTS; k0 < K; k0 += SHR_WAVES * 16 * SLOTS) {
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
       // ---- exact search for the tokens that need it
       const int ns = piece == 0 ? nslow : 0;
       if (ns > 0) {
-        search_slow((lds_c4 *)lds_r, (lds_u64 *)lds_b, (lds_c16 *)lds_slow, ns,
+        search_slow<FEW ? 8 : 4>((lds_c4 *)lds_r, (lds_u64 *)lds_b, (lds_c16 *)lds_slow, ns,
                     (glb_char *)(a.C32 + (int64_t)stage * a.K * 32), a.K, wave, lane);
         lds_barrier();
         if (wave == 0) n_slow += (unsigned)ns;

@@ -191,8 +191,9 @@ hipError_t rvq_launch_encode_small(const rvq_ctx *ctx, const void *dX, int64_t N
                                    float *dResidual, void *dStd, hipStream_t s);
 // dhat == 32: the wavefronts of a workgroup share the stage's codewords and sweep the same tokens.
 // Computes the rows' std itself (and writes dStd), except where rvq_share_needs_std says that
-// row_std has to have filled std32 and dStd before.  rvq_share_fits: the vector counts it is for
-bool rvq_share_fits(const rvq_ctx *ctx, int64_t V);
+// row_std has to have filled std32 and dStd before.  rvq_share_fits: the vector counts it is for, in
+// a call of that many stages
+bool rvq_share_fits(const rvq_ctx *ctx, int64_t V, int stages);
 bool rvq_share_needs_std(const rvq_ctx *ctx, int64_t N);
 hipError_t rvq_launch_encode_share(const rvq_ctx *ctx, const void *dX, int64_t N, int64_t ldx,
                                    int stage_begin, int stage_end, int16_t *dCodes, float *dResidual,
