@@ -36,6 +36,7 @@
 // Measured, rows of 32 groups, K = 2048, depth 8, before (small-batch or one-token-per-lane kernel) and
 // now: 32 rows 55 -> 34 us, 48 rows 83 -> 34, 128 rows 157 -> 37, 512 rows 203 -> 71, 1500 rows
 // 217 -> 123, 3000 rows 215 -> 212 us; K = 4096, 32 rows of 128 groups 156 -> 71 us, 300 rows 196 us.
+#include <algorithm>
 #include <type_traits>
 
 #include "rvq_internal.h"
@@ -738,19 +739,33 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 
 }  // namespace
 
-// Where this kernel is the fastest (measured over K = 256 .. 8192, tokens per CU 2 .. 512, us for all
-// stages, the kernel before : this one):
-//   below: with at most two vectors per CU the small-batch kernel's latency is lower (K = 2048, depth 8:
-//   35 : 40; three vectors per CU 56 : 41);
-//   above: encode_screen_kernel's wavefronts re-use a token's operands for the whole stage and overtake
-//   once they are full, the later the larger the codebook: K = 512 at 192 tokens per CU 95 : 90, at
-//   256 97 : 109; K = 1024 at 256 132 : 119, at 320 131 : 137; K = 2048 at 375 222 : 212, at 512
-//   229 : 270; K = 4096 (two pieces, each with its resolve step) at 256 454 : 280, at 500, key rows,
-//   507 : 549; K = 8192 at 512 1374 : 786.
-bool rvq_share_fits(const rvq_ctx *ctx, int64_t V) {
+// Where this kernel is used.  Times in us for all stages, depth 8, bf16 rows of 32 groups, "screen" is
+// encode_screen_kernel, t / CU = tokens per CU.
+//  below: with at most two vectors per CU the small-batch kernel's latency is lower (K = 2048, two: 33 : 33,
+//    one: 28 : 33; three vectors per CU 55 : 33).
+//  up to 256 / CU: keys and values of a layer are encoded as a pair, and here encode_screen_kernel leaves
+//    half of the CUs free, so that a pair of calls on two streams runs side by side, while this kernel
+//    takes every CU and a pair takes twice a call.  The line is where the pair, each way at its best, takes
+//    the same: K = 256 at 96 / CU screen 114 : this 108, at 128 114 : 125; K = 512 at 128 130 : 126, at 144
+//    127 : 139; K = 1024 at 160 183 : 172, at 176 184 : 187, at 256 184 : 245; K = 2048 at 176 242 : 236, at
+//    192 236 : 245, at 256 255 : 309; K = 3072 at 224 492 : 455, at 240 470 : 488; K = 4096 at 256 566 : 541.
+//    (One call alone would be faster here up to the line below: K = 2048 at 192 205 : 123, at 256 217 : 156.
+//    Pairs that follow each other without a join favour encode_screen_kernel earlier: 188 / CU 221 : 244.)
+//  above 256 / CU: a pair no longer fits side by side, and encode_screen_kernel's wavefronts, which
+//    re-use a token's operands for the whole stage, overtake once they are full, the later the larger the
+//    codebook.  One call: K = 1536 at 288 168 : 163, at 304 166 : 171; K = 2048 at 352 214 : 194, at 384 213 : 216
+//    (pair 416 : 432); K = 4096 (two pieces, each with its resolve step) at 384 563 : 408, at 500, key rows,
+//    507 : 549; K = 8192, depth 4, at 512 717 : 470.
+//  one stage (a step of codebook learning: nothing runs beside it, and encode_screen_kernel's first
+//    copy of a stage's operands has nothing to hide under): up to 128 + K / 8.  fp32 vectors: K = 256 at
+//    156 / CU 23 : 21; K = 1024 at 256 36 : 29; K = 2048 at 256 62 : 35, at 384 62 : 45.
+bool rvq_share_fits(const rvq_ctx *ctx, int64_t V, int stages) {
   const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
-  const int64_t most = ctx->Kpad <= 2048 ? 128 + ctx->Kpad / 8 : 256 + ctx->Kpad / 32;
-  return V > 2 * cus && V <= cus * (most < SHR_TOKENS ? most : SHR_TOKENS);
+  const int64_t K = ctx->Kpad;
+  if (V <= 2 * cus) return false;
+  if (stages > 1 && V <= 256 * cus) return V <= cus * std::min(96 + K / 16, 128 + K / 32);
+  return V <= cus * (K > 2048 ? std::min<int64_t>(256 + K / 32, SHR_TOKENS)
+                              : 128 + (stages > 1 ? 7 * K / 64 : K / 8));
 }
 
 // tokens per workgroup: the vectors spread evenly over the CUs (whole tiles of 16 where there are
@@ -787,7 +802,7 @@ hipError_t rvq_launch_encode_share(const rvq_ctx *ctx, const void *dX, int64_t N
   a.ldx = ldx;
   a.V = N * ctx->G;
   if (a.V < 1) return hipSuccess;
-  if (c.dhat != 32 || !rvq_share_fits(ctx, a.V)) return hipErrorInvalidValue;
+  if (c.dhat != 32 || !rvq_share_fits(ctx, a.V, stage_end - stage_begin)) return hipErrorInvalidValue;
   a.counters = a.V > SHR_FEW ? ctx->counters : nullptr;
   a.in_dtype = c.in_dtype;
   a.std_dtype = c.std_dtype;
