@@ -438,10 +438,13 @@ def test_the_wait_bound_does_not_choose_the_kernel(gpu_device, V):
 
 # ------------------------------------------------------------------------- non-finite inputs
 @pytest.mark.parametrize("case", [
-    # d, dhat, K, depth, grouping: the matrix-core path (dhat 32) and the plain scan (dhat 16)
-    (256, 32, 300, 4, oracle.STRIDED),
-    (256, 32, 64, 3, oracle.CONTIGUOUS),
-    (64, 16, 50, 3, oracle.CONTIGUOUS),
+    # d, dhat, K, depth, grouping, path (0: the library's choice, the shared codebook at this size;
+    # 2: RVQ_PATH_SCREEN): the matrix-core kernels (dhat 32) and the plain scan (dhat 16)
+    (256, 32, 300, 4, oracle.STRIDED, 0),
+    (256, 32, 300, 4, oracle.STRIDED, 2),
+    (256, 32, 64, 3, oracle.CONTIGUOUS, 0),
+    (256, 32, 64, 3, oracle.CONTIGUOUS, 2),
+    (64, 16, 50, 3, oracle.CONTIGUOUS, 0),
 ])
 def test_rows_with_nan_or_infinity_leave_the_other_rows_alone(gpu_device, case):
     """The boundary asks for finite inputs and promises, for a row that has a NaN or an infinity,
@@ -449,8 +452,8 @@ def test_rows_with_nan_or_infinity_leave_the_other_rows_alone(gpu_device, case):
     200 and the last one are poisoned; every other row must get exactly the codes and the std
     of a run without the poison."""
     torch, b = _torch(), _b()
-    d, dhat, K, depth, grouping = case
-    N = 1300  # more than one chunk of 1024 group vectors per workgroup and a ragged tail
+    d, dhat, K, depth, grouping, path = case
+    N = 1300  # for dhat 32 10400 vectors: several chunks of the matrix-core kernels and a ragged tail
     rng = np.random.Generator(np.random.PCG64(d + K))
     X = rng.standard_normal((N, d)).astype(np.float32)
     C = (rng.standard_normal((depth, K, dhat)) * (0.7 ** np.arange(depth))[:, None, None]).astype(np.float32)
@@ -463,7 +466,8 @@ def test_rows_with_nan_or_infinity_leave_the_other_rows_alone(gpu_device, case):
     bad[N - 1, 18] = np.nan
     poisoned = np.array([3, 7, 100, 200, N - 1])
     clean_rows = np.setdiff1d(np.arange(N), poisoned)
-    q = b.Quantizer(d=d, dhat=dhat, depth=depth, K=K, grouping=grouping, in_dtype=b.F32, std_dtype=b.F32)
+    q = b.Quantizer(d=d, dhat=dhat, depth=depth, K=K, grouping=grouping, in_dtype=b.F32, std_dtype=b.F32,
+                    encode_path=path)
     q.set_codebooks(torch.from_numpy(C).cuda())
     c0, s0, _ = q.encode(torch.from_numpy(X).cuda())
     c1, s1, _ = q.encode(torch.from_numpy(bad).cuda())
@@ -478,6 +482,39 @@ def test_rows_with_nan_or_infinity_leave_the_other_rows_alone(gpu_device, case):
     assert np.array_equal(s1.cpu().numpy()[clean_rows], s0.cpu().numpy()[clean_rows])
     assert np.isfinite(out.float().cpu().numpy()[clean_rows]).all()
     q.close()
+
+
+# ------------------------------------------------------------------------- two streams
+def test_encodes_on_two_streams_do_not_disturb_each_other(gpu_device):
+    """Keys and values of a layer go to two contexts on two streams.  Calls of every size class (small
+    batch, shared codebook with one tile and with many, large kernel), issued many at a time on both
+    streams without a join, return what they return one after the other on one stream."""
+    torch, b = _torch(), _b()
+    d, depth, K = 512, 3, 1024
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(17)
+    qs, data = [], []
+    for grouping in (b.STRIDED, b.CONTIGUOUS):
+        q = b.Quantizer(d=d, dhat=32, depth=depth, K=K, grouping=grouping, in_dtype=b.BF16)
+        q.set_codebooks(torch.randn((depth, K, 32), device="cuda", generator=gen))
+        qs.append(q)
+        data.append([torch.randn((n, d), device="cuda", generator=gen).bfloat16() for n in (5, 40, 256, 1000, 2500, 9000)])
+    want = [[q.encode(x, want_residual=True) for x in xs] for q, xs in zip(qs, data)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = [[], []]
+    for _ in range(3):
+        for i in range(len(data[0])):
+            for which in (0, 1):
+                with torch.cuda.stream(streams[which]):
+                    got[which].append((i, qs[which].encode(data[which][i], want_residual=True)))
+    torch.cuda.synchronize()
+    for which in (0, 1):
+        for i, out in got[which]:
+            for x, y in zip(out, want[which][i]):
+                assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (which, data[which][i].shape)
+        assert b.rvq_check_kernels(qs[which].ctx) == 0
+        qs[which].close()
 
 
 # ------------------------------------------------------------------------- the ceiling probes

@@ -112,3 +112,50 @@ def test_captured_calls_replay_like_eager_ones(gpu_device):
     del g
     for t in (q, qc, kq, vq):
         t.close()
+
+
+@pytest.mark.parametrize("rows", [3, 40, 700, 1400])
+def test_captured_encodes_of_few_rows_replay_like_eager_ones(gpu_device, rows):
+    """rvq_encode and rvq_encode_static of the kernels for few rows (small batch, shared codebook with one
+    tile of tokens and with several), captured and replayed with new inputs and eager work between."""
+    import torch
+
+    from paper_2410_15704_amd import binding as b
+
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    C = torch.randn((3, 1000, 32), device="cuda", generator=gen) * 0.6
+    q = b.Quantizer(d=D, dhat=32, depth=3, K=1000, grouping=b.STRIDED, in_dtype=b.BF16)
+    q.set_codebooks(C)
+    xs = [torch.randn((rows, D), device="cuda", generator=gen).bfloat16() for _ in range(3)]
+    x = xs[0].clone()
+
+    def buffers():
+        return [torch.zeros((rows, G, 3), dtype=torch.int16, device="cuda"), torch.zeros(rows, dtype=torch.float16, device="cuda"),
+                torch.zeros((rows, G, 32), device="cuda"), torch.zeros((rows, G, 3), dtype=torch.int16, device="cuda"),
+                torch.zeros(rows, dtype=torch.float16, device="cuda")]
+
+    def calls(o):
+        b.rvq_encode(q.ctx, x, rows, D, 0, 3, o[0], o[1], o[2])
+        b.rvq_encode_static(q.ctx, x, rows, D, 0, 3, o[3], o[4])
+
+    eager, graph = buffers(), buffers()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        calls(graph)
+    for i in (0, 1, 2, 1):
+        x.copy_(xs[i])
+        calls(eager)
+        torch.cuda.synchronize()
+        junk = torch.randn((256, 256), device="cuda", generator=gen)
+        assert torch.isfinite((junk @ junk).sum()).item()
+        for t in graph:
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.uint8), c.view(torch.uint8)) for a, c in zip(graph, eager))
+        assert torch.equal(eager[0], eager[3]) and int(eager[0].max()) > 0
+    assert b.rvq_check_kernels(q.ctx) == 0
+    del g
+    q.close()

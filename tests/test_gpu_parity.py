@@ -56,7 +56,11 @@ def _half_ulp_distance(a_bits, b_bits):
     return np.abs(key(a_bits) - key(b_bits))
 
 
-SMALL_MAX_VECTORS = 4096  # up to here rvq_encode (path chosen by the library) takes the small-batch kernel
+# rvq_encode, path chosen by the library, dhat = 32, 256 CUs: up to 512 vectors the small-batch kernel; from
+# there to some tens of thousands (131072 at K = 8192) the kernel whose wavefronts share the codebook;
+# otherwise the matrix-core kernel of RVQ_PATH_SCREEN.  Up to 4096 vectors the codes are the exact path's.
+EXACT_MAX_VECTORS = 4096
+SHARED_MAX_VECTORS = 131072
 
 
 def check_encode(Xs, in_dtype, d, dhat, depth, K, grouping, C32, *, path=0, sample_rows=None,
@@ -67,9 +71,9 @@ def check_encode(Xs, in_dtype, d, dhat, depth, K, grouping, C32, *, path=0, samp
     the quantizer and the device outputs as well (the caller closes the quantizer)."""
     torch, b = _torch(), _b()
     N = Xs.shape[0]
-    if path == 0 and dhat == 32 and N * (d // dhat) <= SMALL_MAX_VECTORS and not keep:
-        # so few vectors go to the small-batch kernel: hold the matrix-core kernel to the same bar
-        # on this shape as well
+    if path == 0 and dhat == 32 and N * (d // dhat) <= SHARED_MAX_VECTORS:
+        # a call of this size may take one of the kernels for fewer vectors: hold the matrix-core kernel
+        # of RVQ_PATH_SCREEN to the same bar on this shape as well
         check_encode(Xs, in_dtype, d, dhat, depth, K, grouping, C32, path=2, sample_rows=sample_rows,
                      std_dtype=std_dtype, min_equal=min_equal, mismatch_cap=mismatch_cap, ddof=ddof,
                      ldx=ldx)
@@ -221,28 +225,31 @@ def test_encode_small_and_ragged(gpu_device, case):
 
 
 @pytest.mark.parametrize("case", [
-    # N, d, depth, K, grouping, dtype, scale   (N * d / 32 <= 4096 vectors: the small-batch kernel)
+    # N, d, depth, K, grouping, dtype, scale   (up to 4096 vectors; 256 CUs)
     (1, 1024, 8, 2048, oracle.STRIDED, "bf16", 1),      # one appended token: 32 workgroups
     (8, 1024, 8, 2048, oracle.CONTIGUOUS, "fp16", 1),   # 256 vectors, one per workgroup
-    (9, 1024, 8, 2048, oracle.STRIDED, "fp32", 1),      # 288: two per workgroup, four lanes a codeword
-    (30, 1024, 8, 2048, oracle.CONTIGUOUS, "fp16", 1),  # 960: four per workgroup
-    (33, 1024, 8, 2048, oracle.STRIDED, "bf16", 1),     # 1056: eight per workgroup, two lanes a codeword
-    (100, 1024, 8, 2048, oracle.STRIDED, "bf16", 1),    # 3200: sixteen per workgroup
-    (128, 1024, 8, 2048, oracle.CONTIGUOUS, "bf16", 1),  # the most the kernel takes
+    (9, 1024, 8, 2048, oracle.STRIDED, "fp32", 1),      # 288: two per workgroup
+    (16, 1024, 8, 2048, oracle.CONTIGUOUS, "fp32", 1),  # 512: the most of the small-batch kernel
+    (30, 1024, 8, 2048, oracle.CONTIGUOUS, "fp16", 1),  # 960: the shared codebook, four per workgroup
+    (33, 1024, 8, 2048, oracle.STRIDED, "bf16", 1),     # 1056: five per workgroup
+    (100, 1024, 8, 2048, oracle.STRIDED, "bf16", 1),    # 3200: thirteen per workgroup
+    (128, 1024, 8, 2048, oracle.CONTIGUOUS, "bf16", 1),  # 4096: sixteen per workgroup, one full tile
     (61, 128, 3, 100, oracle.STRIDED, "fp32", 1),       # a codebook that ends inside a load
     (50, 96, 5, 1, oracle.CONTIGUOUS, "fp16", 1),       # one codeword
     (20, 64, 2, 5000, oracle.STRIDED, "fp32", 1),       # three passes over the codebook, the last ragged
+    (400, 64, 2, 5000, oracle.STRIDED, "fp32", 1),      # three pieces of the shared codebook
+    (300, 96, 3, 1, oracle.CONTIGUOUS, "fp16", 1),      # one codeword, shared
     (3, 32, 16, 33, oracle.STRIDED, "fp32", 0),         # one group, 16 stages, rows not scaled
 ])
 def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
-    """The kernel for a few rows (what a serving loop appends per step) returns the codes, std and
+    """The kernels for a few rows (what a serving loop appends per step) return the codes, std and
     residuals of the exact path bit for bit: same fp32 direct-form distances added in the same
     order, same tie rule.  Also over a stage range that starts from given residuals.  (Both
     paths are held to the oracle by the other tests of this file.)"""
     torch, b = _torch(), _b()
     N, d, depth, K, grouping, dtype, scale = case
     G = d // 32
-    assert N * G <= SMALL_MAX_VECTORS
+    assert N * G <= EXACT_MAX_VECTORS
     X = synth.gaussian_rows(N, d, seed=4000 + N + K, dtype=dtype, outliers=max(1, d // 50))
     rng = np.random.Generator(np.random.PCG64(N + K))
     C = (rng.standard_normal((depth, K, 32)) * (0.7 ** np.arange(depth))[:, None, None]).astype(np.float32)
@@ -317,6 +324,9 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
     (600, 1, 2048, 2, oracle.CONTIGUOUS, "fp32", 0, "all huge"),    # every token: no sweep at all
     (4000, 1, 5000, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
     (6000, 1, 300, 2, oracle.CONTIGUOUS, "fp32", 0, "inf codebook"),
+    (1600, 4, 2048, 2, oracle.STRIDED, "fp32", 1, "nan"),           # the std of such rows too
+    (1200, 3, 700, 2, oracle.CONTIGUOUS, "bf16", 1, "nan"),
+    (9000, 3, 700, 2, oracle.STRIDED, "fp16", 1, "nan"),
 ])
 def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
     """The kernel whose wavefronts share a stage's codebook, at the edges of its tiles, pieces and vector
