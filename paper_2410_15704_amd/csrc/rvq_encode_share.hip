@@ -609,7 +609,6 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         g = min(g, shr_dppu<0x141>(g));
         if ((int)(g >> 5) == q) marks &= marks - 1;
         has = g != 0xffffffffu;
-        n_exact += __popcll(__ballot(has));  // eight lanes, eight codewords
         g = has ? g : 0u;
         return ((int)(g >> 4) * TPW + (int)(g & 3)) * 32 + (int)(g & 12);
       };
@@ -624,6 +623,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         while (__any(marks != 0)) {
           bool has;
           const int pos = next_group(marks, has);
+          n_exact += __popcll(__ballot(has));  // eight lanes, eight codewords
           const float second0 = second;
           const uint2 ka = *reinterpret_cast<const uint2 *>(perm + pos);
           const uint2 kb = *reinterpret_cast<const uint2 *>(perm + pos + 16);

@@ -383,6 +383,30 @@ def test_encode_shared_codebook_equals_the_other_paths(gpu_device, case):
             assert torch.equal(x[rows].view(torch.uint8), y[rows].view(torch.uint8)), name
 
 
+def test_statistics_of_the_shared_codebook_kernel(gpu_device):
+    """Four codewords are one candidate group, so every search scores its eight positions exactly, once:
+    also where two codewords are closer than the rounding of their distances and the winner is decided
+    by a second sum."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    C = torch.randn((2, 4, 32), device="cuda", generator=gen)
+    C[:, 1] = C[:, 0] * (1 + 3e-7)
+    V = 8193
+    X = C[0, torch.randint(0, 4, (V,), device="cuda", generator=gen)] + 0.1 * torch.randn((V, 32), device="cuda", generator=gen)
+    X[100] = 1e9  # one token that fp16 cannot hold, in both stages
+    q = b.Quantizer(d=32, dhat=32, depth=2, K=4, scale=0)
+    q.set_codebooks(C)
+    q.encode(X[:4096])
+    torch.cuda.synchronize()
+    assert set(b.rvq_get_counters(q.ctx).values()) == {0}  # so few vectors are not counted
+    q.encode(X)
+    torch.cuda.synchronize()
+    c = b.rvq_get_counters(q.ctx)
+    q.close()
+    assert c == dict(slow_searches=2, exact_rescored=8 * (2 * V - 2), groups_rescored=0, searches=2 * V, group_exact_passes=0)
+
+
 @pytest.mark.parametrize("K, per_cu, stages, shared", [
     # up to 256 vectors per CU the large kernel leaves half of the chip to a second call
     (256, 112, 2, True), (256, 113, 2, False), (1024, 160, 2, True), (1024, 161, 2, False),
