@@ -87,12 +87,12 @@ __global__ __launch_bounds__(256) void encode_exact_kernel(
 // codewords of a stage.  The tokens a serving loop appends per step are a few rows: too few
 // vectors to fill even one workgroup of the matrix-core kernel, whose stages take as long for
 // one token as for a thousand.  Here the 32 groups of one row already make 32 workgroups of 1024
-// threads.  LPC lanes share a codeword, 32 / LPC channels each: with four, the loads of a
+// threads.  SM_LPC = 4 lanes share a codeword, eight channels each: the loads of a
 // wavefront instruction cover sixteen codebook rows half a line at a time (with a row per lane
 // every instruction touched 64 lines and the address path, not memory, set the pace: 8 us per
 // stage instead of 3.5).  A lane's partial sums of (r - c)^2 over four channels each meet the
 // others in a balanced tree, inside the lane first and then by lane-exchange additions: the
-// tree encode_exact_kernel adds in, same tie rule, so for every LPC this
+// tree encode_exact_kernel adds in, same tie rule, so this
 // kernel returns that kernel's codes bit for bit.  The argmin is a minimum over (distance bits,
 // index): over the wavefront with lane moves, over the workgroup through LDS.  The residuals
 // live in LDS through all stages (Algorithm 1; Section 3 fuses the stages for the same reason);
@@ -100,6 +100,7 @@ __global__ __launch_bounds__(256) void encode_exact_kernel(
 // the registers of this one are free.
 constexpr int SM_THREADS = 1024;
 constexpr int SM_WAVES = SM_THREADS / 64;
+constexpr int SM_LPC = 4;                         // lanes that share a codeword
 constexpr int SM_LOADS = 16;                      // load instructions per thread and pass
 constexpr int SM_WAVE_ROWS = 8 * SM_LOADS;        // codewords a wavefront scores per pass
 constexpr int SM_PASS = SM_WAVES * SM_WAVE_ROWS;  // codewords per workgroup and pass (2048)
@@ -125,10 +126,8 @@ __device__ __forceinline__ uint32_t sm_wave_min(uint32_t v) {
   return min(min(r0, r1), min(r2, r3));
 }
 
-// VPW: vectors per workgroup.  LPC: lanes that share a codeword (8, 4 or 2), each with
-// 32 / LPC channels.  The partial sums meet in the same tree whatever LPC is (inside the lane
-// first, then by lane exchanges), so every instantiation returns the same bits.
-template <int VPW, int LPC>
+// VPW: vectors per workgroup (1 or 2)
+template <int VPW>
 __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
     const void *__restrict__ X, int in_dtype, int64_t N, int64_t ldx, int G, int grouping,
     int scale /* rows are divided by their std, computed here */, int ddof, bool vec_rows,
@@ -138,14 +137,14 @@ __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ __align__(16) float rs[VPW][DH];               // the residuals
   __shared__ unsigned long long wave_best[VPW][SM_WAVES];   // (distance bits, index) per wavefront
-  __shared__ float row_sd[SM_WAVES];                        // std of the rows this workgroup touches
+  __shared__ float row_sd[VPW];                             // std of the rows this workgroup touches
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int NQ = 8 / LPC;         // 16-byte pieces of a codeword in this lane
+  constexpr int NQ = 8 / SM_LPC;         // 16-byte pieces of a codeword in this lane
   constexpr int RPL = SM_LOADS / NQ;  // codewords per lane and pass
-  constexpr int RSTEP = 64 / LPC;     // codewords a load instruction of the wavefront covers
-  const int piece = (lane & (LPC - 1)) * NQ;  // this lane's first piece of four channels
+  constexpr int RSTEP = 64 / SM_LPC;     // codewords a load instruction of the wavefront covers
+  const int piece = (lane & (SM_LPC - 1)) * NQ;  // this lane's first piece of four channels
   const int64_t V = N * G;
   const int64_t v0 = (int64_t)blockIdx.x * VPW;
   // thread (u, j) of the first VPW * 32 looks after element j of vector u: it loads it, takes the
@@ -156,9 +155,9 @@ __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
   const int64_t ev = min(v0 + eu, V - 1);
   constexpr unsigned long long NONE = 0x7f800000ull << 32;  // (+inf, index 0): what no codeword beats
   // codeword slot j of a pass: rows wave_row0 + RSTEP j .. + RSTEP - 1, this lane has NQ pieces of
-  // row + lane / LPC
+  // row + lane / SM_LPC
   f32x4 c4[SM_LOADS];
-  const int lane_row = wave * SM_WAVE_ROWS + lane / LPC;
+  const int lane_row = wave * SM_WAVE_ROWS + lane / SM_LPC;
   auto fetch_slot = [&](int stage, int k0, int j) {
     // a scalar base and 32-bit byte offsets (a stage is at most 32768 rows of 128 bytes)
     const char *__restrict__ Ci = reinterpret_cast<const char *>(C + (int64_t)stage * K * DH);
@@ -174,7 +173,7 @@ __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
   };
   // requested first: the loads below come back behind these, which stage 0 needs anyway
   fetch(stage_begin, 0);
-  // The rows of this workgroup's vectors (at most VPW <= 16 of them): wavefront w takes row
+  // The rows of this workgroup's vectors (at most VPW of them): wavefront w takes row
   // n_first + w, with the arithmetic of row_std_kernel; the workgroup that holds a row's group 0
   // stores the value.
   const int64_t n_first = v0 / G;
@@ -217,9 +216,6 @@ __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
       // against it, so the requests run under the scoring and the reduction; the winner's row,
       // requested after them, comes back behind them (a wavefront's loads return in order), by
       // which time the next pass can start at once.
-      // (With a codeword per lane, LPC == 1, the two slots of 32 registers each make the
-      // compiler spill 91 values: that layout is not instantiated.)
-      static_assert(LPC >= 2, "requests are interleaved with the scoring slot by slot");
       const bool more = k0 + SM_PASS < K;
       const bool have_next = more || i + 1 < stage_end;
       const int nstage = more ? i : i + 1, nk0 = more ? k0 + SM_PASS : 0;
@@ -248,9 +244,8 @@ __global__ __launch_bounds__(SM_THREADS) void encode_small_kernel(
 #pragma unroll
             for (int t = 0; t < NQ; t += 2 * w) pq[t] += pq[t + w];
           float part = pq[0];
-          if constexpr (LPC >= 2) part += sm_dppf<0xB1>(part);   // lanes p ^ 1
-          if constexpr (LPC >= 4) part += sm_dppf<0x4E>(part);   // lanes p ^ 2: the quad's sum, in all four
-          if constexpr (LPC >= 8) part += sm_dppf<0x141>(part);  // mirrored half row: the other quad's sum
+          part += sm_dppf<0xB1>(part);  // lanes p ^ 1
+          part += sm_dppf<0x4E>(part);  // lanes p ^ 2: the quad's sum, in all four
           // distances are >= +0: their bits order like the values; a NaN has larger bits than
           // +inf and never wins, as with `dist < best`
           const int k = k0 + lane_row + RSTEP * l;
@@ -308,14 +303,12 @@ hipError_t rvq_launch_encode_small(const rvq_ctx *ctx, const void *dX, int64_t N
   // one workgroup fills a CU: a workgroup takes a second vector only when every CU has one
   const int vpw = V > ctx->num_cus ? 2 : 1;
   const dim3 grid((unsigned)((V + vpw - 1) / vpw)), block(SM_THREADS);
-#define RVQ_LAUNCH_SMALL(VPW, LPC)                                                               \
-  hipLaunchKernelGGL((encode_small_kernel<VPW, LPC>), grid, block, 0, s, dX, c.in_dtype, N, ldx, \
-                     ctx->G, c.grouping, c.scale, c.std_ddof, vec_rows, dStd, c.std_dtype,       \
+#define RVQ_LAUNCH_SMALL(VPW)                                                                \
+  hipLaunchKernelGGL(encode_small_kernel<VPW>, grid, block, 0, s, dX, c.in_dtype, N, ldx,    \
+                     ctx->G, c.grouping, c.scale, c.std_ddof, vec_rows, dStd, c.std_dtype,   \
                      ctx->C, c.K, c.depth, stage_begin, stage_end, dCodes, dResidual)
-  // four lanes per codeword, measured: a wavefront's load instruction then covers sixteen rows half a
-  // line at a time, and two of the three tree levels between lanes remain
-  if (vpw == 1) RVQ_LAUNCH_SMALL(1, 4);
-  else RVQ_LAUNCH_SMALL(2, 4);
+  if (vpw == 1) RVQ_LAUNCH_SMALL(1);
+  else RVQ_LAUNCH_SMALL(2);
 #undef RVQ_LAUNCH_SMALL
   return hipGetLastError();
 }
