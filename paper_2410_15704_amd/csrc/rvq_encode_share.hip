@@ -762,7 +762,10 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 bool rvq_share_fits(const rvq_ctx *ctx, int64_t V, int stages) {
   const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
   const int64_t K = ctx->Kpad;
-  if (V <= 2 * cus) return false;
+  if (V <= RVQ_SMALL_PER_CU * cus) return false;
+  // (promised for so few vectors: the exact path's codes, no use of the caller's std scratch; on a
+  // partition of the chip with fewer CUs the lines below lie lower than that)
+  if (V <= SHR_FEW) return V <= cus * SHR_TOKENS;
   if (stages > 1 && V <= 256 * cus) return V <= cus * std::min(96 + K / 16, 128 + K / 32);
   return V <= cus * (K > 2048 ? std::min<int64_t>(256 + K / 32, SHR_TOKENS)
                               : 128 + (stages > 1 ? 7 * K / 64 : K / 8));
