@@ -742,7 +742,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 // Where this kernel is used.  Times in us for all stages, depth 8, bf16 rows of 32 groups, "screen" is
 // encode_screen_kernel, t / CU = tokens per CU.
 //  below: with at most two vectors per CU the small-batch kernel's latency is lower (K = 2048, two: 33 : 33,
-//    one: 28 : 33; three vectors per CU 55 : 33).
+//    one: 28 : 33; three vectors per CU 55 : 33, K = 256 54 : 25, K = 4096 104 : 56).
 //  up to 256 / CU: keys and values of a layer are encoded as a pair, and here encode_screen_kernel leaves
 //    half of the CUs free, so that a pair of calls on two streams runs side by side, while this kernel
 //    takes every CU and a pair takes twice a call.  The line is where the pair, each way at its best, takes
