@@ -32,10 +32,10 @@
 // and their LDS round trips).  With more tokens the general form: at 188 per workgroup the vector units
 // issue in 59 % of the cycles (matrix cores 15 %, L1 address path 31 %); the rest is the sixteen
 // wavefronts in step at a barrier per pair of tiles, and what a stage costs once.  At TPW = 4 its 128
-// registers do not hold everything: 21 values per lane are spilled (9 at TPW = 2, 6 at TPW = 1).
+// registers do not hold everything: 22 values per lane are spilled (9 at TPW = 2, 4 at TPW = 1).
 // Measured, rows of 32 groups, K = 2048, depth 8, before (small-batch or one-token-per-lane kernel) and
-// now: 32 rows 55 -> 34 us, 48 rows 83 -> 34, 128 rows 157 -> 37, 512 rows 203 -> 71, 1500 rows
-// 217 -> 123, 3000 rows 215 -> 212 us; K = 4096, 32 rows of 128 groups 156 -> 71 us, 300 rows 196 us.
+// now: 32 rows 55 -> 34 us, 48 rows 83 -> 34, 128 rows 157 -> 37, 512 rows 203 -> 66, 1500 rows
+// 217 -> 120, 2500 rows 217 -> 178 us; K = 4096, 32 rows of 128 groups 156 -> 71 us, 300 rows 192 us.
 #include <algorithm>
 #include <type_traits>
 
@@ -634,9 +634,9 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
           f32x4 c[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) c[e] = row((int)min(k[e], (unsigned)(a.K - 1)), q);
-          // (all eight in flight before the first is used: one round trip.  Left to itself the compiler
-          // here scores them four and four, 0.6 us a stage.)
-          if constexpr (FEW)
+          // (All eight in flight before the first is used: one round trip.  Left to itself the compiler
+          // scores them four and four, 0.6 us a stage.  Later passes have no registers for it.)
+          if constexpr (FEW || first)
             asm volatile("" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]), "+v"(c[4]), "+v"(c[5]), "+v"(c[6]), "+v"(c[7]));
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
