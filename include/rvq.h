@@ -126,7 +126,7 @@ int rvq_get_codebooks(rvq_ctx *ctx, float *dC, void *stream);
  * is below 1e-30 is scaled by 1.
  * With dhat == 32 and encode_path RVQ_PATH_AUTO, calls of few group vectors (N * d / 32; at most 512
  * with 256 CUs: the rows a serving loop appends per step) run a kernel built for latency, calls up
- * to min(96 + K / 16, 128 + K / 32) vectors per CU, and those above 256 and up to 128 + 7 K / 64
+ * to min(96 + K / 8, 144 + 3 K / 64) vectors per CU, and those above 256 and up to 128 + 7 K / 64
  * (K > 2048: 256 + K / 32, at most 512), a matrix-core kernel whose wavefronts share the codebook
  * (calls of one stage: up to 128 + K / 8; K > 2048: as above), all others the matrix-core kernel of
  * RVQ_PATH_SCREEN.  Calls of at most 4096 vectors return the codes

@@ -743,18 +743,18 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 // encode_screen_kernel, t / CU = tokens per CU.
 //  below: with at most two vectors per CU the small-batch kernel's latency is lower (K = 2048, two: 33 : 33,
 //    one: 28 : 33; three vectors per CU 55 : 33, K = 256 54 : 25, K = 4096 104 : 56).
-//  up to 256 / CU: keys and values of a layer are encoded as a pair, and here encode_screen_kernel leaves
-//    half of the CUs free, so that a pair of calls on two streams runs side by side, while this kernel
-//    takes every CU and a pair takes twice a call.  The line is where the pair, each way at its best, takes
-//    the same: K = 256 at 96 / CU screen 114 : this 108, at 128 114 : 125; K = 512 at 128 130 : 126, at 144
-//    127 : 139; K = 1024 at 160 183 : 172, at 176 184 : 187, at 256 184 : 245; K = 2048 at 176 242 : 236, at
-//    192 236 : 245, at 256 255 : 309; K = 3072 at 224 492 : 455, at 240 470 : 488; K = 4096 at 256 566 : 541.
-//    (One call alone would be faster here up to the line below: K = 2048 at 192 205 : 123, at 256 217 : 156.
-//    Pairs that follow each other without a join favour encode_screen_kernel earlier: 188 / CU 221 : 244.)
+//  up to 256 / CU: here encode_screen_kernel leaves half of the CUs free, so that keys and values of a layer,
+//    a pair of calls on two streams, run side by side, while this kernel takes every CU and a pair takes
+//    twice a call.  One call gains, a pair loses; the line is where the product of the two ratios is 1,
+//    with pairs that follow each other without a join, which lose most.  One call; such a pair:
+//    K = 256 at 128 / CU 84 : 61; 88 : 112, at 144 84 : 67; 86 : 125.  K = 512 at 160 98 : 71; 102 : 133, at 176
+//    98 : 76; 101 : 144.  K = 1024 at 192 130 : 95; 138 : 186, at 208 132 : 102; 140 : 198.  K = 1536 at 208
+//    172 : 128; 186 : 246, at 224 162 : 134; 174 : 267.  K = 2048 at 192 202 : 121; 208 : 229, at 240 209 : 145;
+//    223 : 288, at 256 210 : 151; 219 : 301.  K = 3072 at 256 401 : 252; 444 : 504.
 //  above 256 / CU: a pair no longer fits side by side, and encode_screen_kernel's wavefronts, which
 //    re-use a token's operands for the whole stage, overtake once they are full, the later the larger the
 //    codebook.  One call: K = 1536 at 288 168 : 163, at 304 166 : 171; K = 2048 at 352 214 : 194, at 384 213 : 216
-//    (pair 416 : 432); K = 4096 (two pieces, each with its resolve step) at 384 563 : 408, at 500, key rows,
+//    (pair 416 : 429); K = 4096 (two pieces, each with its resolve step) at 384 563 : 408, at 500, key rows,
 //    507 : 549; K = 8192, depth 4, at 512 717 : 470.
 //  one stage (a step of codebook learning: nothing runs beside it, and encode_screen_kernel's first
 //    copy of a stage's operands has nothing to hide under): up to 128 + K / 8.  fp32 vectors: K = 256 at
@@ -766,7 +766,7 @@ bool rvq_share_fits(const rvq_ctx *ctx, int64_t V, int stages) {
   // (promised for so few vectors: the exact path's codes, no use of the caller's std scratch; on a
   // partition of the chip with fewer CUs the lines below lie lower than that)
   if (V <= SHR_FEW) return V <= cus * SHR_TOKENS;
-  if (stages > 1 && V <= 256 * cus) return V <= cus * std::min(96 + K / 16, 128 + K / 32);
+  if (stages > 1 && V <= 256 * cus) return V <= cus * std::min(96 + K / 8, 144 + 3 * K / 64);
   return V <= cus * (K > 2048 ? std::min<int64_t>(256 + K / 32, SHR_TOKENS)
                               : 128 + (stages > 1 ? 7 * K / 64 : K / 8));
 }

@@ -297,8 +297,8 @@ def test_encode_few_rows_equals_the_exact_path(gpu_device, case):
     (4100, 4, 2048, 3, oracle.STRIDED, "fp16", 1, "plain"),         # two tiles
     (12285, 3, 1000, 2, oracle.STRIDED, "fp32", 1, "plain"),        # three tiles, rows across workgroups
     (33025, 1, 2048, 2, oracle.CONTIGUOUS, "bf16", 1, "plain"),     # std computed beforehand
-    (49152, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # 192 tokens per CU, the most below 256
-    (49184, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "large"),       # one row more: the large kernel
+    (61440, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # 240 tokens per CU, the most below 256
+    (61472, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "large"),       # one row more: the large kernel
     (65536, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "large"),       # 256 per CU
     (65568, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # one row more: the shared codebook again
     (90112, 32, 2048, 2, oracle.STRIDED, "bf16", 1, "plain"),       # 352 tokens per CU, the most at K = 2048
@@ -409,8 +409,8 @@ def test_statistics_of_the_shared_codebook_kernel(gpu_device):
 
 @pytest.mark.parametrize("K, per_cu, stages, shared", [
     # up to 256 vectors per CU the large kernel leaves half of the chip to a second call
-    (256, 112, 2, True), (256, 113, 2, False), (1024, 160, 2, True), (1024, 161, 2, False),
-    (2048, 192, 2, True), (2048, 193, 2, False), (2048, 256, 2, False), (4096, 256, 2, True),
+    (256, 128, 2, True), (256, 129, 2, False), (1024, 192, 2, True), (1024, 193, 2, False),
+    (2048, 240, 2, True), (2048, 241, 2, False), (2048, 256, 2, False), (4096, 256, 2, True),
     # above that it does not
     (2048, 257, 2, True), (2048, 352, 2, True), (2048, 353, 2, False), (1024, 257, 2, False),
     (4096, 384, 2, True), (4096, 385, 2, False),
