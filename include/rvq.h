@@ -262,11 +262,11 @@ int rvq_ema_update(rvq_ctx *ctx, int32_t stage, const float *dR, const int16_t *
 /*
  * Statistics of the matrix-core encode path, accumulated since rvq_create (diagnostics; this
  * call synchronizes the device).  host_out is HOST memory, 5 values:
- *   [0] (token, stage) searches the fp16 screen could not settle and that were redone exactly in
- *       fp32 over the whole stage, [1] codewords re-scored exactly in fp32, [2] 16-codeword groups
+ *   [0] (token, stage) searches with more candidate groups than the kernel keeps track of, or whose residual
+ *       does not fit fp16 (those are redone exactly in fp32 over the whole stage), [1] codewords re-scored exactly in fp32, [2] 16-codeword groups
  *       re-scored from LDS, [3] all (token, stage) searches (padding lanes of the last
  *       workgroup included), [4] searches with more candidates than the kernel's list holds,
- *       settled by scoring every codeword of their candidate groups exactly.
+ *       settled, as the first kind of [0], by scoring every codeword near enough exactly.
  * These are the counts of the kernel of RVQ_PATH_SCREEN.  In calls that the kernel whose wavefronts
  * share the codebook takes, [1] counts the eight codewords of every candidate group, [3] leaves padding
  * out, and [2] and [4] stay as they are (it re-scores nothing from LDS and keeps no list).  Calls of at

@@ -9,14 +9,15 @@
 //     scores of ONE token per tile and reduces them without leaving its registers.  Per lane
 //     and tile only the smallest score is kept (v_min3 tree), tagged with the tile number in
 //     its low mantissa bits, and merged into the three smallest tile minima seen so far.
-//  2. Resolve.  With dr = r - fp16(r) and rho the largest relative rounding error of the fp16
-//     codewords, |screen(k) - exact(k)| <= e_k = g ||2 c_k|| + (kappa/4) ||2 c_k||^2 + g0 where
-//     g = ||dr|| + (rho + kappa (1 + rho)) ||fp16(r)|| and g0 = ||fp16(r)|| * (norm of codeword
-//     elements too small for a normal half) depend on the token only (Cauchy-Schwarz on both
-//     rounding terms; kappa covers fp32 accumulation and the tag bits).  Codewords are
+//  2. Resolve.  In scaled numbers (a = S (-2 c), x = T r, both rounded to fp16) with dx = x - fp16(x),
+//     |screen(k) - exact(k)| <= e_k = g1 ||a_k|| + (kappa/8) ||a_k||^2 + E_k + g0 where
+//     g1 = ||dx|| + kappa ||fp16(x)|| and g0 = tau/2 ||fp16(x)||^2 depend on the token only and
+//     E_k = ||fp16(a_k) - a_k||^2 / (2 tau) on the codeword only (Cauchy-Schwarz on both
+//     rounding terms, see RVQ_BOUND_TAU; kappa covers fp32 accumulation and the tag bits; the terms
+//     of the codeword alone are taken off the stored norms).  Codewords are
 //     stored in order of their norm, so the 16 codewords of a (tile, lane half) group share a
 //     tight bound e_g; the quantity that is tracked per group is the lower bound
-//     LB_g = (smallest screened score of the group) - e_g.  The exact winner lies in a group
+//     LB_g = (smallest screened score of the group) - e_g + g0.  The exact winner lies in a group
 //     with LB_g <= UB, UB = LB + 2 e of the group with the smallest LB.  Those few groups are
 //     re-scored from the same LDS copy with packed fp16 dot products (the best group of every
 //     token by its owner, the 3 % of further groups from a per-wavefront queue, four at a time
@@ -24,9 +25,9 @@
 //     every codeword whose lower bound is <= UB is scored exactly (fp32, direct form
 //     sum (r - c)^2, fp32 codebook), ties going to the smallest index.  A token with a single
 //     candidate (97 %) needs no score at all: the row is fetched once and subtracted.  A token
-//     with more candidates than its list holds has all rows of its window groups scored exactly
-//     by the wavefront; one with more groups in a lane than the three tracked ones, or whose
-//     residual does not fit fp16, is searched exactly over the whole codebook.
+//     with more candidates than its list holds, or more groups in a lane than the three tracked
+//     ones, is settled by a second sweep that marks the rows near enough (window_search); one
+//     whose residual does not fit fp16 is searched exactly over the whole codebook.
 //
 // The residual stays in registers (fp32) across all stages and is updated with the fp32
 // codeword, so stages never round-trip through memory (the fusion Section 3 of the paper
@@ -107,6 +108,8 @@ __device__ __forceinline__ void halves32f(float v, float &h0, float &h1) {
   h0 = __uint_as_float(u0);
   h1 = __uint_as_float(u1);
 }
+// the rounding part E of a group's bound, the lower half of its word
+__device__ __forceinline__ float bound_of_rounding(float w) { return __uint_as_float(__float_as_uint(w) << 16); }
 // v of this lane + v of its partner, the same bits in both
 __device__ __forceinline__ float sum32(float v) {
   unsigned h0, h1;
@@ -178,9 +181,8 @@ __device__ __forceinline__ int wave_nearest(float bd, int bk) {
 // at a time (with a row per lane it touched 64 lines, and the address path made a scan of 2048
 // rows take 35 us), and the rows of the next pass are requested slot by slot as soon as this
 // pass has used the registers.  The four partial sums of (r - c)^2 meet by two lane exchanges.
-// Kept out of line: it is needed for 0.02 % of the searches of the benchmark (1 % with codebooks
-// crowded into tight clusters), and inlined its registers would be made room for on the common
-// path.
+// Kept out of line: it is needed for residuals beyond fp16 only, and inlined its registers would be made
+// room for on the common path.
 __device__ __noinline__ int exact_scan(const float *__restrict__ Cs, int K, const float *vec, int lane) {
   constexpr int SLOTS = 8;                 // codewords per lane and pass
   constexpr int PASS = 16 * SLOTS;         // codewords per pass of the wavefront (128)
@@ -227,6 +229,143 @@ __device__ __noinline__ int exact_scan(const float *__restrict__ Cs, int K, cons
   }
   bk = wave_nearest(bd, bk);
   return bk == 0x7fffffff ? 0 : bk;
+}
+
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) const u32x2 lds_cuint2;
+typedef __attribute__((address_space(3))) const float lds_cfloat;
+typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
+typedef __attribute__((address_space(3))) const uint16_t lds_cu16;
+typedef __attribute__((address_space(3))) unsigned long long lds_u64;
+
+// Exact nearest codeword, among the operands that are in LDS, of up to eight tokens of a wavefront whose
+// candidates the common path cannot hold: more rows than the candidate list, more groups than the
+// three tracked per lane half, or a full queue.  `vec` holds their fp32 residuals, `meta` their window
+// (threshold, token part of the error bound); the winner of each is left in `best` as (distance bits,
+// codeword), the largest value if there is none.
+// The tokens' window is known, so a second sweep, of one tile of 16 tokens, marks every four rows whose
+// smallest score lies within it (v_mfma_f32_16x16x32_f16: a lane holds four rows of one token), and only
+// marked rows are scored exactly: sixteen times four rows per pass, of whichever tokens.  29 instructions a tile
+// of 32 codewords and 4 us a call; the scan of the whole stage by the wavefront that used to settle tokens
+// with too many groups fetches 256 KiB per token, 10 us while everyone in the workgroup waits.  How often: 0.02 %
+// of the searches of 1024-channel keys, 1 to 3 % in the first stage of heads of 128 channels with outliers (that
+// stage of 2^20 vectors, K = 2048: 807 -> 400 us, or 442 -> 337, or 323 -> 285, by the draw).
+// Kept out of line, as exact_scan is.
+__device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds_cfloat *bounds, lds_cu16 *perm,
+                                           lds_cf32x4 *vec, lds_cuint2 *meta, lds_u64 *best, int ntiles_, int n_,
+                                           const float *__restrict__ Cs_, int K_, float Tscale, int lane) {
+  // (arguments come in vector registers; these are the same in every lane)
+  const int ntiles = __builtin_amdgcn_readfirstlane(ntiles_), n = __builtin_amdgcn_readfirstlane(n_);
+  const int K = __builtin_amdgcn_readfirstlane(K_);
+  const uint64_t cs_ = reinterpret_cast<uint64_t>(Cs_);
+  const char *Cs = reinterpret_cast<const char *>(
+      ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(cs_ >> 32)) << 32) |
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)cs_));
+  const int col = lane & 15, c = lane >> 4;  // matrix-core arrangement: token, and eight channels / four rows
+  const bool mine = col < n;
+  const int tok = mine ? col : 0;
+  half8 B;
+  {
+    const float tiny = 6.103515625e-5f / Tscale;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 x = vec[tok * 8 + 2 * c + t];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) B[4 * t + e] = fabsf(x[e]) < tiny ? (_Float16)0.f : (_Float16)(x[e] * Tscale);
+    }
+  }
+  const u32x2 mt = meta[tok];
+  const float thr = mine ? __uint_as_float(mt.x) : -INFINITY, g1 = __uint_as_float(mt.y);
+  // operand rows m = lane & 15 of row half r: channels 8 c .. 8 c + 7 = piece pair (c & 1), lane half c >> 1
+  const int piece0 = (c & 1) * 128 + (c >> 1) * 32;
+  unsigned marks[4];
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    marks[w] = 0;
+    const int tend = min(16 * w + 16, ntiles);
+#pragma unroll 1
+    for (int t0 = 16 * w; t0 < tend; t0 += 4) {
+      const int slot0 = col ^ (t0 & 28);  // row m of tile t lies in slot m ^ (t & 31)
+      u32x2 q[4][4];
+      f32x4 nv[4][2];
+      float bd[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        // (tiles come in pairs; past the end the last pair is read again)
+        const int t = u < 2 ? t0 + u : min(t0 + u, ntiles - 4 + u);
+        lds_cuint2 *ap = A + t * 256 + piece0 + (u < 2 ? slot0 ^ u : col ^ (t & 31));
+        q[u][0] = ap[0]; q[u][1] = ap[64];
+        lds_cuint2 *aq = A + t * 256 + piece0 + (u < 2 ? slot0 ^ (16 + u) : (16 + col) ^ (t & 31));
+        q[u][2] = aq[0]; q[u][3] = aq[64];
+        lds_cf32x4 *np = (lds_cf32x4 *)(norms + (t * 2 + (c & 1)) * 16 + 4 * (c >> 1));
+        nv[u][0] = np[0]; nv[u][1] = np[2];
+        bd[u] = bounds[t * 2 + (c & 1)];
+      }
+      unsigned m8 = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float lim = fmaf(g1, bd[u], thr);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const half8 a = __builtin_bit_cast(half8, make_uint4(q[u][2 * r].x, q[u][2 * r].y, q[u][2 * r + 1].x, q[u][2 * r + 1].y));
+          const f32x4 sc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, B, nv[u][r], 0, 0, 0);
+          const float mn = fminf(min3f(sc[0], sc[1], sc[2]), sc[3]);
+          m8 |= mn <= lim ? 1u << (2 * u + r) : 0u;
+        }
+      }
+      if (t0 + 4 > ntiles) m8 &= 0xfu;  // (the last pair has marked its rows before)
+      marks[w] |= m8 << (2 * (t0 & 15));
+    }
+  }
+  // exact scores of the marked rows: a pass takes one mark of the first sixteen lanes that have any
+  for (;;) {
+    const bool has = (marks[0] | marks[1] | marks[2] | marks[3]) != 0;
+    const unsigned long long bal = __ballot(has);
+    if (!bal) break;
+    const int idx = __popcll(bal & ((1ull << lane) - 1ull));
+    unsigned desc = 0;
+    if (has && idx < 16) {
+      const int w = marks[0] ? 0 : (marks[1] ? 1 : (marks[2] ? 2 : 3));
+      const unsigned mw = w == 0 ? marks[0] : (w == 1 ? marks[1] : (w == 2 ? marks[2] : marks[3]));
+      const int bit = __ffs(mw) - 1;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) marks[i] &= i == w ? mw - 1 : 0xffffffffu;
+      desc = 0x80000000u | ((unsigned)tok << 16) | ((unsigned)c << 8) | (unsigned)(32 * w + bit);
+    }
+    // mark number idx goes to the lanes 4 idx .. 4 idx + 3, a row each
+    desc = (unsigned)__builtin_amdgcn_ds_permute((has && idx < 16 ? idx * 4 : 63) * 4, (int)desc);
+    desc = (unsigned)__builtin_amdgcn_update_dpp(0, (int)desc, 0x00, 0xf, 0xf, false);  // quad_perm [0,0,0,0]
+    const int tk = (int)(desc >> 16) & 15, qc = (int)(desc >> 8) & 3, tr = (int)(desc & 0xffu);
+    const unsigned k = perm[(tr >> 1) * 32 + 16 * (tr & 1) + 4 * qc + (lane & 3)];
+    const bool valid = (desc >> 31) && k < (unsigned)K;
+    const f32x4 *crow = reinterpret_cast<const f32x4 *>(Cs + (valid ? k : 0u) * 128u);
+    f32x4 cw[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cw[i] = crow[i];
+    float q4[4];  // the sums of exact_scan, in its order
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float p[2] = {0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const f32x4 x = vec[tk * 8 + 2 * i + t];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float dlt = x[e] - cw[2 * i + t][e];
+          p[t] = fmaf(dlt, dlt, p[t]);
+        }
+      }
+      q4[i] = p[0] + p[1];
+    }
+    const uint32_t d = valid ? __float_as_uint((q4[0] + q4[1]) + (q4[2] + q4[3])) : 0x7f800000u;
+    uint32_t m = min(d, scr_dpp<0xB1>(d));
+    m = min(m, scr_dpp<0x4E>(m));
+    uint32_t kk = valid && d == m ? k : 0xffffffffu;
+    kk = min(kk, scr_dpp<0xB1>(kk));
+    kk = min(kk, scr_dpp<0x4E>(kk));
+    if ((lane & 3) == 0 && kk != 0xffffffffu)
+      __hip_atomic_fetch_min(&best[tk], ((unsigned long long)m << 32) | kk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
 }
 
 // pieces of the sweep's reduction of one accumulator set: R1 folds the 16 scores of a lane into two
@@ -533,8 +672,8 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   // have changed places, which makes [0..7] the matrix-core B operands of token tile 2k (tokens
   // owned by lanes 0..31) and [8..15] those of token tile 2k + 1.
   unsigned Bw[SCR_DT][16];
-  float g1[SCR_DT];     // token part of the error bound: e_k = g1 ||2c|| + k4 ||2c||^2 + g0
-  float g0[SCR_DT];     // ||fp16(r)|| * (largest norm of codeword elements dropped to zero)
+  float g1[SCR_DT];     // token parts of the error bound: e_k = g1 ||2c|| + k4 ||2c||^2 + E_k + g0
+  float g0[SCR_DT];
   int slow[SCR_DT];     // token goes to the exact wavefront search
   float bestd[SCR_DT];  // exact distance and index of the best candidate scored so far
   int bestk[SCR_DT];
@@ -543,9 +682,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 
   // fp16 operands and error bounds of `stage` from the current residuals
   auto convert = [&](int stage) {
-    const float rho = a.stats[stage * 8 + 0];
     const bool usable = a.stats[stage * 8 + 1] != 0.0f;
-    const float Fdrop = a.stats[stage * 8 + 2];
     const float Tscale = a.stats[stage * 8 + 4];  // power of two applied to the residuals
     const float tiny = 6.103515625e-5f / Tscale;  // below this the scaled value is no normal half
 #pragma unroll
@@ -572,8 +709,8 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       }
       const float nq = sqrtf(s_q) * 1.000001f;
       const float nd = sqrtf(s_d) * 1.000001f;
-      g1[k] = (nd + (rho + a.kappa * (1.0f + rho)) * nq) * 1.000001f;
-      g0[k] = nq * Fdrop * 1.000001f;
+      g1[k] = (nd + 1.0005f * a.kappa * nq) * 1.000001f;  // (||fp16(a)|| <= (1 + 2^-11) ||a||)
+      g0[k] = 0.5f * RVQ_BOUND_TAU * 1.000001f * nq * nq;
       // an element beyond the half range turns s_q into infinity (or the sum into a NaN)
 #ifdef RVQ_FORCE_SLOW
       slow[k] = 1;
@@ -808,7 +945,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         return tl < 0 ? 0 : (tl >= ntiles ? ntiles - 1 : tl);
       };
       // the window of the lane's token in double tile k: thr = upper bound on the exact minimum,
-      // from the best group of either lane half (LB + 2 e_g, 25 % spare); e0..e3 = the token's four
+      // from the best group of either lane half (LB + 2 e_g, 2.5 % spare for the rounding of this sum); e0..e3 = the token's four
       // tracked groups, the best one first (the two best of half 0 and of half 1); pend = which of
       // them lie within the window
       struct Window { float thr, e0, e1, e2, e3; unsigned pend; bool afirst; };
@@ -817,16 +954,17 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         const float a1 = ta[k][0], a2 = ta[k][1], a3 = ta[k][2];
         const float b1 = tb[k][0], b2 = tb[k][1], b3 = tb[k][2];
         const float Aa = lds_g[tile_of(a1) * 2 + 0], Ab = lds_g[tile_of(b1) * 2 + 1];
-        const float ua = a1 + 2.5f * (g1[k] * Aa + k4 * Aa * Aa + g0[k]);
-        const float ub = b1 + 2.5f * (g1[k] * Ab + k4 * Ab * Ab + g0[k]);
+        const float ua = a1 + 2.05f * (g1[k] * Aa + k4 * Aa * Aa + bound_of_rounding(Aa) + g0[k]);
+        const float ub = b1 + 2.05f * (g1[k] * Ab + k4 * Ab * Ab + bound_of_rounding(Ab) + g0[k]);
         w.thr = fminf(ua, ub);
         // a third group of one lane half inside the window: more groups than are tracked
-        if (a3 <= w.thr || b3 <= w.thr) slow[k] = 1;
+        const bool wide = a3 <= w.thr || b3 <= w.thr;
+        if (wide && !slow[k]) nc[k] = 0x200;
         w.afirst = a1 <= b1;
         w.e0 = w.afirst ? a1 : b1; w.e1 = w.afirst ? b1 : a1;
         w.e2 = w.afirst ? a2 : b2; w.e3 = w.afirst ? b2 : a2;
         w.pend = 0;
-        if (!slow[k])
+        if (!slow[k] && !wide)
           w.pend = (w.e0 <= w.thr && w.e0 < 1e37f ? 1u : 0u) | (w.e1 <= w.thr && w.e1 < 1e37f ? 2u : 0u) |
                    (w.e2 <= w.thr && w.e2 < 1e37f ? 4u : 0u) | (w.e3 <= w.thr && w.e3 < 1e37f ? 8u : 0u);
         return w;
@@ -837,10 +975,12 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       // of the tokens have one) are queued, so that they are re-scored together afterwards
       // instead of one extra pass per double tile.
       int qn = 0;  // queue entries of this wavefront (wave-uniform)
+      float thr[SCR_DT];
 #pragma unroll
       for (int k = 0; k < NDT; ++k) {
         const int tok = k * 64 + lane;
         const Window w = window(k);
+        thr[k] = w.thr;
         {
           const int tl = tile_of(w.e0);
           const int hh = (w.afirst ? 0 : 1);
@@ -942,73 +1082,56 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       }
 
       PHASE_MARK(6);  // resolve: queued groups
-      // ---- a token with more candidates than the list holds (or whose groups did not fit the
-      // queue): the wavefront scores ALL rows of its (at most four) groups in the window
-      // exactly, one lane per row, and the token keeps the single winner.  Exact, because the
-      // true winner of the chunk lies in one of these groups.
+      // ---- a token with more candidates than the list holds, more groups in its window than are
+      // tracked, or groups that did not fit the queue: window_search, eight tokens of the wavefront at a time (the
+      // queue's memory, free by now, takes their residuals), and the token keeps the single winner
       {
-        bool any_over = false;
+        bool hard[SCR_DT], any_hard = false;
 #pragma unroll
-        for (int k = 0; k < NDT; ++k) any_over = any_over || (nc[k] > SCR_CAND && !slow[k]);
-        if (__any(any_over)) {
-#pragma unroll 1
+        for (int k = 0; k < NDT; ++k) {
+          hard[k] = nc[k] > SCR_CAND && !slow[k];
+          any_hard = any_hard || hard[k];
+        }
+        if (__any(any_hard)) {
+          int order[SCR_DT], total = 0;  // place of the lane's token among the wavefront's
+#pragma unroll
           for (int k = 0; k < NDT; ++k) {
-            int nck = nc[0], slowk = slow[0];
+            const unsigned long long bal = __ballot(hard[k]);
+            const int wide = __popcll(__ballot(hard[k] && (nc[k] & 0x200)));
+            order[k] = total + __popcll(bal & ((1ull << lane) - 1ull));
+            total += __popcll(bal);
+            n_slow += wide;
+            n_over += __popcll(bal) - wide;
+          }
+          uint2 *meta = qM;
+          unsigned long long *best = reinterpret_cast<unsigned long long *>(qM + 8);
+#pragma unroll 1
+          for (int base = 0; base < total; base += 8) {
+            if (lane < 8) best[lane] = ~0ull;
 #pragma unroll
-            for (int k2 = 1; k2 < NDT; ++k2) { nck = k == k2 ? nc[k2] : nck; slowk = k == k2 ? slow[k2] : slowk; }
-            unsigned long long ovm = __ballot(nck > SCR_CAND && !slowk);
-            if (ovm) {
-              Window w = window(0);
+            for (int k = 0; k < NDT; ++k) {
+              const int at = order[k] - base;
+              if (hard[k] && at >= 0 && at < 8) {
+                f32x4 *dst = reinterpret_cast<f32x4 *>(qB) + at * 8;
 #pragma unroll
-              for (int k2 = 1; k2 < NDT; ++k2)
-                if (k == k2) w = window(k2);
-              while (ovm) {
-                const int src = __ffsll((long long)ovm) - 1;
-                ovm &= ovm - 1;
-                n_over += 1;
-                const int gi = lane >> 4, rw = lane & 15;  // lane -> (group of the window, row)
-                // (src is the same in every lane: the values come through scalar registers)
-                auto bcast = [&](float x) {
-                  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
-                };
-                const float ge0 = bcast(w.e0), ge1 = bcast(w.e1), ge2 = bcast(w.e2), ge3 = bcast(w.e3);
-                const unsigned gpend = (unsigned)__builtin_amdgcn_readlane((int)w.pend, src);
-                const int gaf = __builtin_amdgcn_readlane((int)w.afirst, src);
-                const float gval = gi == 0 ? ge0 : (gi == 1 ? ge1 : (gi == 2 ? ge2 : ge3));
-                const int ghh = (gaf ? gi : gi + 1) & 1;
-                const int gtl = tile_of(gval);
-                const int gm = 8 * (rw >> 2) + 4 * ghh + (rw & 3);
-                const unsigned gk = ((gpend >> gi) & 1u) ? (unsigned)lds_p[gtl * 32 + gm] : 0xffffu;
-                const bool gvalid = gk < (unsigned)a.K;
-                // exact distance of the token to this lane's row.  The token's residual comes out
-                // of its owner's registers as scalars (src is uniform), so it costs no vector
-                // registers and no trip through memory.
-                const f32x4 *crow = reinterpret_cast<const f32x4 *>(
-                    a.C32 + ((int64_t)stage * a.K + (gvalid ? gk : 0u)) * 32);
-                float dist = 0.f;
+                for (int c4 = 0; c4 < 8; ++c4)
+                  dst[c4] = f32x4{r[k][4 * c4], r[k][4 * c4 + 1], r[k][4 * c4 + 2], r[k][4 * c4 + 3]};
+                meta[at] = make_uint2(__float_as_uint(thr[k]), __float_as_uint(g1[k]));
+              }
+            }
+            __builtin_amdgcn_wave_barrier();
+            window_search((lds_cuint2 *)lds_A, (lds_cfloat *)lds_n, (lds_cfloat *)lds_g, (lds_cu16 *)lds_p,
+                          (lds_cf32x4 *)qB, (lds_cuint2 *)meta, (lds_u64 *)best, ntiles, min(8, total - base),
+                          a.C32 + (int64_t)stage * a.K * 32, a.K, a.stats[stage * 8 + 4], lane);
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int c4 = 0; c4 < 8; ++c4) {
-                  const f32x4 cw = crow[c4];
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) {
-                    const int j = c4 * 4 + e;
-                    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, r[0][j]), src));
-                    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, r[1][j]), src));
-                    const float dlt = (k == 0 ? r0 : r1) - cw[e];
-                    dist = fmaf(dlt, dlt, dist);
-                  }
-                }
-                static_assert(SCR_DT == 2, "the double tile is picked with one select");
-                // nearest over the wavefront, ties to the smallest index
-                const int bk = wave_nearest(gvalid ? dist : INFINITY, gvalid ? (int)gk : 0x7fffffff);
-                // bk == 0x7fffffff cannot happen for a token with candidates; it would leave the
-                // token without one and send it to the wavefront search below
-                if (lane == src) {
-                  lds_c[(wtok + k * 64 + src) * SCR_CAND] = (uint16_t)(bk == 0x7fffffff ? 0 : bk);
-#pragma unroll
-                  for (int k2 = 0; k2 < NDT; ++k2)
-                    if (k == k2) nc[k2] = bk == 0x7fffffff ? 0 : 1;
-                }
+            for (int k = 0; k < NDT; ++k) {
+              const int at = order[k] - base;
+              if (hard[k] && at >= 0 && at < 8) {
+                const unsigned bk = (unsigned)best[at];
+                // (no winner cannot happen; it would send the token to the wavefront search below)
+                lds_c[(wtok + k * 64 + lane) * SCR_CAND] = (uint16_t)bk;
+                nc[k] = bk == 0xffffffffu ? 0 : 1;
               }
             }
           }

@@ -11,9 +11,9 @@
 // Search, exact as in the other kernels (Algorithm 1: nearest codeword, smallest index on ties):
 //  1. Sweep.  v_mfma_f32_16x16x32_f16 on fp16(S (-2c)) and fp16(T r) gives a lane four scores of one
 //     token per instruction; per (32 codewords, lane) only the smallest of its eight is kept, in a
-//     register.  With the error bound of the fp16 screen (|score - exact| <= e = g1 A + k4 A^2 + g0,
-//     A the largest ||S 2c|| of the wavefront's norm-sorted codewords; the stored norms have the
-//     group's own k4 A^2 taken off) the smallest score gives an upper bound on the exact minimum;
+//     register.  With the error bound of the fp16 screen (|score - exact| <= e = g1 A + k4 A^2 + E + g0,
+//     A the largest ||S 2c|| and E the largest rounding part of the wavefront's norm-sorted codewords; the stored
+//     norms have the group's own k4 A^2 and the codeword's own E taken off) the smallest score gives an upper bound on the exact minimum;
 //     the least over the wavefronts, found with lane exchanges and one LDS minimum per (wavefront,
 //     token), is the token's threshold.
 //  2. Pick.  A lane whose kept minimum reaches below its token's threshold marks those eight
@@ -322,6 +322,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   half8 A[2 * TPW];
   f32x4 nrm[2 * TPW];
   float Ag = 0.f;  // largest ||S 2c|| of them (they are sorted by norm: all alike)
+  float Eg = 0.f;  // what the codewords' part of their bounds adds to a threshold
   float2 normw = {0.f, 0.f};  // two norms and two entries of the position -> codeword map of the piece,
   uint32_t permw = 0;         // on their way to LDS
   // (buffer loads: the bases stay in scalar registers and a lane's part of an address is one register;
@@ -359,13 +360,13 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
 
   // ---- fp16 operand, error bound and bookkeeping of token `tok` for `stage`, from its residual
   // (eight lanes per token, four channels in each)
-  struct StageConsts { float rho, Fdrop, Tscale, tiny; bool usable; };
+  struct StageConsts { float Tscale, tiny; bool usable; };
   auto stage_consts = [&](int stage) -> StageConsts {
     const float *st = a.stats + stage * 8;
-    return {st[0], st[2], st[4], 6.103515625e-5f / st[4], st[1] != 0.0f};
+    return {st[4], 6.103515625e-5f / st[4], st[1] != 0.0f};
   };
   auto convert = [&](int stage, const StageConsts &sc, int tok, const f32x4 r) {
-    const float rho = sc.rho, Fdrop = sc.Fdrop, Tscale = sc.Tscale, tiny = sc.tiny;
+    const float Tscale = sc.Tscale, tiny = sc.tiny;
     const bool usable = sc.usable;
     float s_q = 0.f, s_d = 0.f;
     half4 hx;
@@ -397,11 +398,11 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         w.y = __float_as_int(-1e35f);  // below every score: no candidates are looked for
         if (valid) lds_slow[atomicAdd(&slow_n[stage & 1], 1)] = (uint16_t)tok;
       } else {
-        // 2.5 g0, and what the fp32 distances of two codewords can be off by rounding: 2 x 34 x 2^-24 of
+        // 2.05 g0, and what the fp32 distances of two codewords can be off by rounding: 2 x 34 x 2^-24 of
         // (|r| + |c|)^2 <= 2 (|r|^2 + |c|^2), where S T |r|^2 = 2 nq^2 here (the |c|^2 part is
         // inside the spare third of the k4 term)
-        w.y = __float_as_int(2.5f * (nq * Fdrop * 1.000001f) + 2e-5f * nq * nq);
-        w.z = __float_as_int((nd + (rho + a.kappa * (1.0f + rho)) * nq) * 1.000001f);
+        w.y = __float_as_int((2.05f * 0.5f * RVQ_BOUND_TAU + 2e-5f) * nq * nq);
+        w.z = __float_as_int((nd + 1.0005f * a.kappa * nq) * 1.000001f);
       }
       lds_i[tok] = w;
     }
@@ -463,7 +464,10 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   for (int stage = a.stage_begin; stage < a.stage_end; ++stage) {
     const uint16_t *perm = nullptr;
     for (int piece = 0; piece < pieces; ++piece) {
+      // (both halves of the groups' words; the word itself, read as a float, is the first of them)
+      Eg = max8(__uint_as_float(__float_as_uint(Ag) << 16));
       Ag = max8(Ag);
+      Eg = fmaf(k4u * Ag, Ag, 2.05f * Eg);
       // (double buffers: the other half may still be read by a slower wavefront)
       float *nbuf = lds_nrm + buf * PIECE;
       uint16_t *pbuf = lds_perm + buf * PIECE;
@@ -510,10 +514,10 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
             ub1 = __builtin_fminf(ub1, mm[1][j]);
             __builtin_amdgcn_sched_barrier(0);  // (results of one step at a time: registers)
           }
-          // the exact minimum is at most score + e + k4 A^2 (the token's part is added in `pick`), with
-          // 25 % spare on the 2 e above the scores' lower bound, score - g1 A
-          ub1 = min_rows16(fmaf(Ag, fmaf(k4u, Ag, 1.5f * g1), ub1));
-          ub0 = min_rows16(fmaf(Ag, fmaf(k4u, Ag, 1.5f * g0), ub0));
+          // the exact minimum is at most score + e + k4 A^2 + E (the token's part is added in `pick`), with
+          // 2.5 % spare, for the rounding of this sum, on the 2 e above the scores' lower bound, score - g1 A
+          ub1 = min_rows16(fmaf(Ag, 1.05f * g1, ub1 + Eg));
+          ub0 = min_rows16(fmaf(Ag, 1.05f * g0, ub0 + Eg));
           if (lane < 32) atomicMin(&lds_i[tile0 * 16 + lane].x, order_bits(__float_as_int(lane < 16 ? ub0 : ub1)));
         } else {
 #pragma unroll
@@ -524,7 +528,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
             mm[1][j] = SHR_BIG;
             ub0 = __builtin_fminf(ub0, mm[0][j]);
           }
-          ub0 = min_rows16(fmaf(Ag, fmaf(k4u, Ag, 1.5f * g0), ub0));
+          ub0 = min_rows16(fmaf(Ag, 1.05f * g0, ub0 + Eg));
           if (lane < 16) atomicMin(&lds_i[tile0 * 16 + lane].x, order_bits(__float_as_int(ub0)));
         }
       };

@@ -10,6 +10,15 @@
 // polls of a wait between wavefronts before it gives up (a poll takes some 300 clocks)
 constexpr uint32_t RVQ_WAIT_POLLS_DEFAULT = 1u << 22;
 
+// The fp16 codeword a16 = a + da (a = S (-2 c)) meets the fp16 residual x16: its rounding moves a score by
+// da . x16, at most |da| |x16| <= (|da|^2 / tau + tau |x16|^2) / 2 for any tau > 0.  The first half is a
+// number of the codeword, taken off its stored norm, the second one of the token, so the bound of a token
+// and a codeword holds that codeword's own rounding error and not the stage's largest (1.9e-4 of |a| typically,
+// 4.7e-4 where one channel outweighs the others: the bound is 0.63 to 0.73 of what it was with that).  The two
+// halves are equal, and equal to the product, at tau = |da| / |x16| = 4 rho |c| / |r| (S = 2 T); 2^-11 is
+// that for rho = 1.95e-4, the mean of fp16 rounding, and |c| = 0.63 |r|.
+constexpr float RVQ_BOUND_TAU = 4.8828125e-4f;
+
 // largest channel-pair table (bytes) the LDS decode path keeps resident: depth * K * 8
 constexpr size_t RVQ_SPLIT_MAX_LDS = 144 * 1024;
 

@@ -8,14 +8,14 @@
 //   C16    : fp16(-2 c) of the codeword at each position, laid out exactly as the A operand of
 //            v_mfma_f32_32x32x16_f16 is read, so the kernel copies it into LDS linearly and a
 //            lane's operand is one 16-byte LDS read
-//   groupA : for every (tile, lane half) group of 16 rows, the largest ||S 2c||
-//   normp  : S T ||c||^2 - kappa/8 * groupA^2 in the order a lane's 16 accumulator registers
-//            want (the subtracted term bounds the accumulation error of the group's scores)
-//   stats  : per stage 8 floats: [0] rho, the largest relative rounding error
-//            ||fp16(S a) - S a|| / ||S a|| (a = -2c) over the elements kept; [1] usable flag
-//            (finite codebook); [2] the largest norm of the elements of S a dropped because they
-//            are below the smallest normal half; [3] S and [4] T, the powers of two the codebook
-//            and the residuals are scaled by before rounding to fp16 (chosen so that the largest
+//   groupA : for every (tile, lane half) group of 16 rows, the largest ||S 2c|| (upper half of the word) and the
+//            largest share of the codewords' rounding in the error bound (lower half), both as bf16
+//            rounded up; the whole word read as a float is the first of them, a little larger
+//   normp  : S T ||c||^2 - kappa/8 * groupA^2 - ||fp16(S a) - S a||^2 / (2 tau), a = -2c, in the order a lane's 16
+//            accumulator registers want (the first term taken off bounds the accumulation error of the
+//            group's scores, the second is the codeword's half of the bound on its rounding, RVQ_BOUND_TAU)
+//   stats  : per stage 8 floats: [1] usable flag (finite codebook); [3] S and [4] T, the powers of two the
+//            codebook and the residuals are scaled by before rounding to fp16 (chosen so that the largest
 //            |S a| lies in [2^13, 2^14) and T = S / 2); [5] the largest |a|
 // A codeword that repeats an earlier one exactly can never win (ties go to the smallest index): it
 // gets no position.
@@ -36,9 +36,8 @@ __global__ void norms_kernel(const float *__restrict__ C, float *__restrict__ no
   norms[first + i] = (float)acc;
 }
 
-__device__ __forceinline__ void atomic_max_pos(float *addr, float v) {
-  atomicMax(reinterpret_cast<unsigned int *>(addr), __float_as_uint(v));  // v >= 0
-}
+// v >= 0 as bf16, rounded up
+__device__ __forceinline__ uint32_t bf16_up(float v) { return (__float_as_uint(v) + 0xffffu) >> 16; }
 
 // sum / maximum over the 32 lanes that share a row (lanes 0..31 and 32..63 hold different rows)
 __device__ __forceinline__ double row_sum(double v) {
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     float *__restrict__ groupA, float *__restrict__ stats) {
   __shared__ float red[16];
   __shared__ int wave_held[16], here[32];  // codewords of the tile's rows, -1: none
-  __shared__ float nrm[32], len[32], rho_s[32], drop_s[32];
+  __shared__ float nrm[32], len[32], rnd[32];
   const int tiles = Kpad / 32;
   const int stage = stage_begin + blockIdx.x / tiles;
   const int t = blockIdx.x % tiles;
@@ -188,8 +187,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
   const __half hv = flushed ? __float2half_rn(0.f) : __float2half_rn(a);
   const double back = (double)__half2float(hv);
   const double a2 = row_sum((double)a * a);
-  const double f2 = row_sum(flushed ? (double)a * a : 0.0);               // absolute part of the error
-  const double e2 = row_sum(flushed ? 0.0 : (back - a) * (back - a));     // relative part
+  const double e2 = row_sum((back - a) * (back - a));  // rounding error, elements dropped among it
   // the 16-byte operand of a lane is stored as two 8-byte pieces 512 bytes apart, so that the
   // kernel fetches it with two conflict-free 8-byte LDS reads
   const int h = j >> 4, q = (j >> 3) & 1, e = j & 7;
@@ -206,13 +204,11 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     if (k >= 0) {
       nrm[m] = (float)(a2 * 0.25 * ((double)T / (double)S));  // S T ||c||^2
       len[m] = (float)(sqrt(a2) * (1.0 + 1e-6));              // ||S 2c||, rounded up
-      rho_s[m] = a2 > 0.0 ? (float)(sqrt(e2 / a2) * (1.0 + 1e-6)) : 0.f;
-      drop_s[m] = (float)(sqrt(f2) * (1.0 + 1e-6));
+      rnd[m] = (float)(e2 * (0.5 / RVQ_BOUND_TAU) * (1.0 + 1e-6));
     } else {
       nrm[m] = 1e30f;  // padding can never come near the minimum
       len[m] = 0.f;
-      rho_s[m] = 0.f;
-      drop_s[m] = 0.f;
+      rnd[m] = 0.f;
     }
   }
   __syncthreads();
@@ -220,18 +216,18 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     // group hh of the tile: rows 8 b + 4 hh + i, b, i = 0..3, which are the 16 accumulator
     // registers rr = 4 b + i of the lanes of half hh
     const int hh = threadIdx.x >> 4, rr = threadIdx.x & 15;
-    float A = 0.f;
-    for (int r2 = 0; r2 < 16; ++r2) A = fmaxf(A, len[8 * (r2 >> 2) + 4 * hh + (r2 & 3)]);
+    float A = 0.f, E = 0.f;
+    for (int r2 = 0; r2 < 16; ++r2) {
+      const int row = 8 * (r2 >> 2) + 4 * hh + (r2 & 3);
+      A = fmaxf(A, len[row]);
+      E = fmaxf(E, rnd[row]);
+    }
     // kappa * (S T ||c||^2) = kappa / 4 * (T / S) * ||S 2c||^2 = kappa / 8 * A^2
     const float shift = 0.125f * kappa * A * A * 1.000001f;
     const int mm = 8 * (rr >> 2) + 4 * hh + (rr & 3);
-    normp[(int64_t)stage * Kpad + (int64_t)t * 32 + hh * 16 + rr] = nrm[mm] - shift;
-    if (rr == 0) groupA[(int64_t)stage * (Kpad / 16) + t * 2 + hh] = A;
-    const float rho = row_max(rho_s[threadIdx.x]), drop = row_max(drop_s[threadIdx.x]);
-    if (threadIdx.x == 0) {
-      atomic_max_pos(&stats[stage * 8 + 0], rho);
-      atomic_max_pos(&stats[stage * 8 + 2], drop);
-    }
+    normp[(int64_t)stage * Kpad + (int64_t)t * 32 + hh * 16 + rr] = nrm[mm] - (shift + rnd[mm]);
+    if (rr == 0)
+      groupA[(int64_t)stage * (Kpad / 16) + t * 2 + hh] = __uint_as_float((bf16_up(A) << 16) | bf16_up(E));
   }
 }
 

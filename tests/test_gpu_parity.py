@@ -627,6 +627,35 @@ def test_encode_screen_crowded_codebook_takes_every_fallback(gpu_device):
     assert cnt["groups_rescored"] > cnt["searches"]            # extra groups went through the queue
 
 
+@pytest.mark.parametrize("K, V", [(64, 700), (192, 1500), (1000, 131), (2048, 140000), (2112, 900)])
+def test_encode_screen_windows_of_many_groups(gpu_device, K, V):
+    """Codewords in clusters whose members the fp16 scores cannot tell apart, of which a token's window holds
+    more rows than its list and more groups than are tracked: one pair of tiles, an odd number of pairs,
+    a ragged wavefront, both chunk forms, a second piece of one pair.  The chosen codeword's distance exceeds the
+    smallest by no more than the rounding of two fp32 sums, 2 x 34 x 2^-24 (|r| + |c|)^2."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + V)
+    centres = torch.randn((max(2, K // 64), 32), device="cuda", generator=gen)
+    C = centres[torch.arange(K, device="cuda") % len(centres)]
+    C = C * (1.0 + 2e-3 * torch.randn((K, 32), device="cuda", generator=gen))
+    X = torch.randn((V, 32), device="cuda", generator=gen) + 0.5 * centres[torch.arange(V, device="cuda") % len(centres)]
+    q = b.Quantizer(d=32, dhat=32, depth=1, K=K, scale=0, encode_path=b.PATH_SCREEN)
+    q.set_codebooks(C[None].contiguous())
+    codes, _, _ = q.encode(X)
+    torch.cuda.synchronize()
+    cnt = b.rvq_get_counters(q.ctx)
+    q.close()
+    assert cnt["group_exact_passes"] > V // 8 and (K < 1000 or cnt["slow_searches"] > 0), cnt
+    codes = codes.view(-1).long()
+    for i in range(0, V, 4096):
+        x, c = X[i:i + 4096].double(), C.double()
+        d = ((x[:, None, :] - c[None]) ** 2).sum(2) if K <= 192 else torch.cdist(x, c, compute_mode="donot_use_mm_for_euclid_dist") ** 2
+        got = ((x - c[codes[i:i + 4096]]) ** 2).sum(1)
+        lim = 2 * 34 * 2.0 ** -24 * (x.norm(dim=1) + c.norm(dim=1).max()) ** 2
+        assert bool((got - d.min(1).values <= lim).all())
+
+
 def test_encode_screen_duplicate_zero_and_dead_codewords(gpu_device):
     """Exact duplicates (the smallest index must win), an all-zero stage and codewords far from
     every input (dead codes) on the matrix-core path."""
