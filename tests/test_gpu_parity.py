@@ -458,6 +458,33 @@ def test_repeated_codewords_cost_nothing(gpu_device, K, repeats):
     assert got[0][2] == got[1][2]
 
 
+@pytest.mark.parametrize("K, repeats", [(6, 1), (67, 2), (130, 61), (2050, 3)])
+def test_repeats_among_codewords_of_equal_norm(gpu_device, K, repeats):
+    """Codewords that hold the same integers in another order have exactly equal norms without being
+    repeats; the repeats among them are of a later one, so that the first codeword of the norm is not the one
+    to compare with.  Left out of the search they change neither codes nor statistics (both sizes pad alike)."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    C = torch.randn((K, 32), device="cuda", generator=gen)
+    row = torch.arange(32, device="cuda", dtype=torch.float32) * 0.0625
+    n = min(K - repeats, 40)
+    for i in range(n):
+        C[i] = row.roll(i) if i < 32 else row.roll(i).flip(0)
+    C[K - repeats:] = C[n - 1]
+    X = torch.randn((3000, 32), device="cuda", generator=gen) * 0.3 + C[torch.arange(3000, device="cuda") % K]
+    got = []
+    for m in (K, K - repeats):
+        q = b.Quantizer(d=32, dhat=32, depth=1, K=m, scale=0, encode_path=b.PATH_SCREEN)
+        q.set_codebooks(C[None, :m].contiguous())
+        codes, _, res = q.encode(X, want_residual=True)
+        torch.cuda.synchronize()
+        got.append((codes, res, b.rvq_get_counters(q.ctx)))
+        q.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2] == got[1][2]
+
+
 def test_encode_chunks_of_512_and_of_1024_agree(gpu_device):
     """A call with at most 512 vectors per CU runs the matrix-core kernel with one token per lane
     (chunks of 512), a larger one with two (chunks of 1024).  A token's codes do not depend on
