@@ -268,7 +268,7 @@ int rvq_set_codebooks(rvq_ctx *ctx, const float *dC, void *stream) {
   hipStream_t s = (hipStream_t)stream;
   const size_t cb = (size_t)ctx->cfg.depth * ctx->cfg.K * ctx->cfg.dhat * sizeof(float);
   RVQ_HIP(ctx, hipMemcpyAsync(ctx->C, dC, cb, hipMemcpyDeviceToDevice, s));
-  RVQ_HIP(ctx, rvq_launch_prepare_codebook(ctx, 0, ctx->cfg.depth, s));
+  RVQ_HIP(ctx, rvq_launch_prepare_codebook(ctx, 0, ctx->cfg.depth, false, s));
   ctx->have_codebooks = true;
   return RVQ_OK;
 }
@@ -422,9 +422,10 @@ int rvq_ema_update(rvq_ctx *ctx, int32_t stage, const float *dR, const int16_t *
   if (!ctx->have_codebooks) return RVQ_ENOCODEBOOK;
   if (M == 0) return RVQ_OK;
   hipStream_t s = (hipStream_t)stream;
+  bool rows_done = false;
   RVQ_HIP(ctx, rvq_launch_ema(ctx, stage, dR, dCodes, code_stride, M, decay, eps, dClusterSize,
-                              dEmbedSum, s));
-  RVQ_HIP(ctx, rvq_launch_prepare_codebook(ctx, stage, stage + 1, s));
+                              dEmbedSum, &rows_done, s));
+  RVQ_HIP(ctx, rvq_launch_prepare_codebook(ctx, stage, stage + 1, rows_done, s));
   return RVQ_OK;
 }
 

@@ -181,8 +181,45 @@ inline bool rvq_rows_vectorizable(const void *dX, int64_t ldx, int d, int in_dty
   return (reinterpret_cast<uintptr_t>(dX) % 16) == 0 && (ldx * esz) % 16 == 0 && (d * esz) % 16 == 0;
 }
 
+// ---- derived data of one codeword (dhat == 32), by 32 lanes, channel j = lane & 31 in each: the squared norm
+// (summed in double, rounded once), the largest |2 c| (infinity if an element is not finite), the channel-split
+// copy Csplit[a][i][k] = (C_i[k][2a], C_i[k][2a+1]), and the initial values of what later kernels
+// fill: perm = -1 (no codeword at this position), stats = {0, 1, 0, ...}.
+struct RvqRows32 {
+  int K, Kpad, depth;
+  float *norms, *rowmax;
+  int32_t *perm;
+  float *stats, *Csplit;
+};
+__device__ __forceinline__ double rvq_row_sum32(double v) {
+  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+__device__ __forceinline__ void rvq_prep_row32(const RvqRows32 &p, int stage, int k, int j, float c) {
+  const int64_t ik = (int64_t)stage * p.K + k;
+  const double n2 = rvq_row_sum32((double)c * (double)c);
+  const float a = fabsf(2.0f * c);
+  float mx = a <= 3.0e38f ? a : __int_as_float(0x7f800000);  // NaN -> infinity
+  for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  if (j == 0) {
+    p.norms[ik] = (float)n2;
+    p.rowmax[ik] = mx;
+  }
+  for (int pos = k * 32 + j; pos < p.Kpad; pos += p.K * 32) p.perm[(int64_t)stage * p.Kpad + pos] = -1;
+  if (k == 0 && j < 8) p.stats[stage * 8 + j] = j == 1 ? 1.0f : 0.0f;
+  if (p.Csplit) {
+    const float c1 = __shfl_xor(c, 1, 64);
+    if (!(j & 1))
+      *reinterpret_cast<float2 *>(p.Csplit + (((int64_t)(j >> 1) * p.depth * p.K) + ik) * 2) = make_float2(c, c1);
+  }
+}
+inline RvqRows32 rvq_rows32(const rvq_ctx *ctx) {
+  return {ctx->cfg.K, ctx->Kpad, ctx->cfg.depth, ctx->norms, ctx->rowmax, ctx->perm, ctx->stats, ctx->Csplit};
+}
+
 // ---- kernel launchers (each returns a hipError_t from the launch) -----------------------------
-hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int stage_end,
+// rows_done: rvq_prep_row32 has run on all codewords of the stages
+hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int stage_end, bool rows_done,
                                        hipStream_t s);
 // std32: device, float [N]: the unrounded per-row std (written by row_std, read by the encode
 // kernels); nullptr in the encode launchers means "rows are already scaled"
@@ -221,7 +258,7 @@ hipError_t rvq_launch_unpack(const rvq_ctx *ctx, const uint8_t *dPacked, int64_t
                              hipStream_t s);
 hipError_t rvq_launch_ema(rvq_ctx *ctx, int stage, const float *dR, const int16_t *dCodes,
                           int64_t code_stride, int64_t M, float decay, float eps,
-                          float *dClusterSize, float *dEmbedSum, hipStream_t s);
+                          float *dClusterSize, float *dEmbedSum, bool *rows_done, hipStream_t s);
 size_t rvq_ema_workspace_bytes(const rvq_ctx *ctx);
 // attention of one query position over a cache of codes (128-channel heads); dWork holds
 // rvq_attn_workspace_floats(N, Hq, Hkv) floats; packed_bytes: 0 (int16 codes), 11 or 12 (records)

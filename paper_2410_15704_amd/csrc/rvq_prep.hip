@@ -39,46 +39,14 @@ __global__ void norms_kernel(const float *__restrict__ C, float *__restrict__ no
 // v >= 0 as bf16, rounded up
 __device__ __forceinline__ uint32_t bf16_up(float v) { return (__float_as_uint(v) + 0xffffu) >> 16; }
 
-// sum / maximum over the 32 lanes that share a row (lanes 0..31 and 32..63 hold different rows)
-__device__ __forceinline__ double row_sum(double v) {
-  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float row_max(float v) {
-  for (int o = 16; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
-// dhat == 32, one lane per (codeword, channel): the squared norm (summed in double, rounded once),
-// the largest |2 c| of the row (infinity if an element is not finite), the channel-split copy
-// Csplit[a][i][k] = (C_i[k][2a], C_i[k][2a+1]), and the initial values of what the later kernels
-// fill: perm = -1 (no codeword at this position), stats = {0, 1, 0, ...}.
-__global__ __launch_bounds__(256) void prep_rows32_kernel(
-    const float *__restrict__ C, int K, int Kpad, int depth, int stage_begin, int stage_end,
-    float *__restrict__ norms, float *__restrict__ rowmax, int32_t *__restrict__ perm,
-    float *__restrict__ stats, float *__restrict__ Csplit) {
+// dhat == 32, one lane per (codeword, channel); ema_finish32_kernel does the same for the codewords it makes
+__global__ __launch_bounds__(256) void prep_rows32_kernel(const float *__restrict__ C, int stage_begin, int stage_end,
+                                                          const RvqRows32 p) {
   const int64_t r = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);  // row among the stages' rows
   const int j = threadIdx.x & 31;
-  if (r >= (int64_t)(stage_end - stage_begin) * K) return;
-  const int stage = stage_begin + (int)(r / K);
-  const int k = (int)(r % K);
-  const int64_t ik = (int64_t)stage * K + k;
-  const float c = C[ik * 32 + j];
-  const double n2 = row_sum((double)c * (double)c);
-  const float a = fabsf(2.0f * c);
-  const float mx = row_max(a <= 3.0e38f ? a : __int_as_float(0x7f800000));  // NaN -> infinity
-  if (j == 0) {
-    norms[ik] = (float)n2;
-    rowmax[ik] = mx;
-  }
-  for (int pos = k * 32 + j; pos < Kpad; pos += K * 32) perm[(int64_t)stage * Kpad + pos] = -1;
-  if (k == 0 && j < 8) stats[stage * 8 + j] = j == 1 ? 1.0f : 0.0f;
-  if (Csplit) {
-    const float c1 = __shfl_xor(c, 1, 64);
-    if (!(j & 1))
-      *reinterpret_cast<float2 *>(Csplit + (((int64_t)(j >> 1) * depth * K) + ik) * 2) =
-          make_float2(c, c1);
-  }
+  if (r >= (int64_t)(stage_end - stage_begin) * p.K) return;
+  const int stage = stage_begin + (int)(r / p.K), k = (int)(r % p.K);
+  rvq_prep_row32(p, stage, k, j, C[((int64_t)stage * p.K + k) * 32 + j]);
 }
 
 // Position of every codeword in the order (norm, index) of its stage, and whether it is an exact repeat of an
@@ -234,8 +202,8 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
   const bool flushed = fabsf(a) < 6.103515625e-5f;
   const __half hv = flushed ? __float2half_rn(0.f) : __float2half_rn(a);
   const double back = (double)__half2float(hv);
-  const double a2 = row_sum((double)a * a);
-  const double e2 = row_sum((back - a) * (back - a));  // rounding error, elements dropped among it
+  const double a2 = rvq_row_sum32((double)a * a);
+  const double e2 = rvq_row_sum32((back - a) * (back - a));  // rounding error, elements dropped among it
   // the 16-byte operand of a lane is stored as two 8-byte pieces 512 bytes apart, so that the
   // kernel fetches it with two conflict-free 8-byte LDS reads
   const int h = j >> 4, q = (j >> 3) & 1, e = j & 7;
@@ -281,7 +249,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
 
 }  // namespace
 
-hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int stage_end,
+hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int stage_end, bool rows_done,
                                        hipStream_t s) {
   const int64_t K = ctx->cfg.K;
   const int ns = stage_end - stage_begin;
@@ -292,9 +260,9 @@ hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int 
                        ctx->cfg.dhat, (int64_t)stage_begin * K, (int64_t)ns * K);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(prep_rows32_kernel, dim3((unsigned)((ns * K + 7) / 8)), dim3(256), 0, s, ctx->C,
-                     (int)K, ctx->Kpad, ctx->cfg.depth, stage_begin, stage_end, ctx->norms,
-                     ctx->rowmax, ctx->perm, ctx->stats, ctx->Csplit);
+  if (!rows_done)
+    hipLaunchKernelGGL(prep_rows32_kernel, dim3((unsigned)((ns * K + 7) / 8)), dim3(256), 0, s, ctx->C,
+                       stage_begin, stage_end, rvq_rows32(ctx));
   hipLaunchKernelGGL(rank_kernel, dim3((unsigned)(ns * ((K + RANK_CW - 1) / RANK_CW))), dim3(64 * RANK_CW), 0, s,
                      ctx->C, ctx->norms, (int)K, ctx->Kpad, stage_begin, ctx->perm);
   hipLaunchKernelGGL(screen_tile_kernel, dim3((unsigned)(ns * (ctx->Kpad / 32))), dim3(1024), 0, s,

@@ -458,7 +458,7 @@ def test_repeated_codewords_cost_nothing(gpu_device, K, repeats):
     assert got[0][2] == got[1][2]
 
 
-@pytest.mark.parametrize("K, repeats", [(6, 1), (67, 2), (130, 61), (2050, 3)])
+@pytest.mark.parametrize("K, repeats", [(6, 1), (67, 2), (190, 61), (2055, 3)])
 def test_repeats_among_codewords_of_equal_norm(gpu_device, K, repeats):
     """Codewords that hold the same integers in another order have exactly equal norms without being
     repeats; the repeats among them are of a later one, so that the first codeword of the norm is not the one
