@@ -510,10 +510,14 @@ constexpr int SCR_DT = 2;          // double tiles (64 tokens, one per lane) per
 constexpr int SCR_WTOK = 64 * SCR_DT;  // tokens per wavefront
 
 // SC: the (padded) codebook fits the LDS copy whole; otherwise it is swept in pieces of SCR_KC
+// PRE (with HALF, fp32 rows in 16-byte pieces, calls of one stage): a chunk's rows are requested a chunk ahead.  A
+// call of one stage reads 128 bytes, sweeps once and writes 128 bytes per vector; nobody waits for operands, so
+// the loads are what a wavefront stands still for, and there are registers for them with one token per
+// lane (242 of 256) and not with two.
 // HALF: every lane owns one token instead of two (chunks of 512 vectors).  A stage then takes
 // about 0.6 of the time and a call with fewer chunks than CUs spreads over twice as many of them:
 // the instantiation for calls between the few rows of encode_small_kernel and a full chip.
-template <int DT, bool SC, bool HALF = false>
+template <int DT, bool SC, bool HALF = false, bool PRE = false>
 __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const ScreenArgs a) {
   constexpr int NDT = HALF ? 1 : SCR_DT;            // double tiles (tokens per lane) in use
   constexpr int CHUNK = SCR_WAVES * 64 * NDT;       // group vectors per workgroup and chunk
@@ -553,6 +557,15 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 
   // ---- the 32 channels of this lane's two tokens, scaled by the row std (Section 2.2)
   float r[SCR_DT][32];
+  // PRE: the rows of the wavefront's next chunk, requested as soon as this chunk's have been taken over
+  uint4 ahead[8];
+  auto request_chunk = [&](int64_t chunk) {
+    const int64_t v = min(chunk * CHUNK + wave * 64 + lane, a.V - 1);
+    const int64_t n = v / a.G;
+    const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const float *>(a.X) + n * a.ldx + (v - n * a.G) * 32);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) ahead[c] = src[c];
+  };
   auto load_chunk = [&](int64_t chunk) {
     vbase = chunk * CHUNK + wave * (64 * NDT);
 #pragma unroll
@@ -566,7 +579,13 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       const int g = (int)(vc - n * a.G);
       const float sd = a.std32 ? a.std32[n] : 1.0f;
       float x[32];
-      if (a.vec_rows) {
+      if constexpr (PRE) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          x[4 * c] = __uint_as_float(ahead[c].x); x[4 * c + 1] = __uint_as_float(ahead[c].y);
+          x[4 * c + 2] = __uint_as_float(ahead[c].z); x[4 * c + 3] = __uint_as_float(ahead[c].w);
+        }
+      } else if (a.vec_rows) {
         // contiguous groups whose 32 channels start on a 16-byte boundary: whole 16-byte pieces
         // (element by element the 64 lanes of a load would touch 64 lines for 4 bytes each)
         constexpr int EPP = DT == RVQ_F32 ? 4 : 8;  // elements per piece
@@ -1275,9 +1294,11 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   // top of the following step), so input load and first operand copy are not paid per chunk at a
   // barrier.  Both teams run the same sequence L(0) T(0) L(1) T(1) ...; they differ in who copies.
   const int SG = nmy * nst;
+  if constexpr (PRE) request_chunk(blockIdx.x);
   for (int sg = 0; sg < SG; ++sg) {
     if (load_next >= 0) {  // the first chunk, or the one after a chunk's last stage
       load_chunk(load_next);
+      if constexpr (PRE) request_chunk(load_next + gridDim.x);  // (past the end: the last vector)
       load_next = -1;
       PHASE_MARK(0);  // input load
       convert(a.stage_begin);
@@ -1374,7 +1395,12 @@ hipError_t rvq_launch_encode_screen(const rvq_ctx *ctx, const void *dX, int64_t 
   const int64_t rounds_half = ((a.V + SCR_TOKENS / 2 - 1) / (SCR_TOKENS / 2) + cus - 1) / cus;
   // (a codebook swept in pieces pays its copies and barriers per chunk: there the one-token form
   // is taken only where it is a single round)
-  const bool half = a.Kpad <= SCR_KC ? rounds_half * 19 < rounds_full * 35 : rounds_half == 1;
+  // One stage of fp32 rows in 16-byte pieces, a step of codebook learning: the form that requests rows ahead,
+  // whatever the size (stage of unclustered residuals, two tokens per lane : ahead, us: K = 2048, 2^20 vectors
+  // 249 : 212, 300000 94 : 85, 150000 67 : 57; K = 1024 192 : 153, 71 : 60, 54 : 40; K = 256 164 : 104,
+  // 62 : 46, 48 : 32).
+  const bool pre = a.Kpad <= SCR_KC && stage_end - stage_begin == 1 && a.vec_rows && c.in_dtype == RVQ_F32;
+  const bool half = pre ? true : a.Kpad <= SCR_KC ? rounds_half * 19 < rounds_full * 35 : rounds_half == 1;
   const int64_t chunk = half ? SCR_TOKENS / 2 : SCR_TOKENS;
   const int64_t nchunks = (a.V + chunk - 1) / chunk;
   const int64_t grid64 = nchunks < ctx->num_cus ? nchunks : ctx->num_cus;
@@ -1386,7 +1412,9 @@ hipError_t rvq_launch_encode_screen(const rvq_ctx *ctx, const void *dX, int64_t 
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)SCR_LDS_BYTES);      \
   if (e != hipSuccess) return e;                                                                \
   hipLaunchKernelGGL((encode_screen_kernel<DT, SC, ##__VA_ARGS__>), grid, block, SCR_LDS_BYTES, s, a)
-  if (half && a.Kpad <= SCR_KC) {
+  if (pre) {
+    RVQ_LAUNCH_SCREEN(RVQ_F32, true, true, true);
+  } else if (half && a.Kpad <= SCR_KC) {
     switch (c.in_dtype) {
       case RVQ_F32: RVQ_LAUNCH_SCREEN(RVQ_F32, true, true); break;
       case RVQ_BF16: RVQ_LAUNCH_SCREEN(RVQ_BF16, true, true); break;

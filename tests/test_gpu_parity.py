@@ -485,6 +485,34 @@ def test_repeats_among_codewords_of_equal_norm(gpu_device, K, repeats):
     assert got[0][2] == got[1][2]
 
 
+@pytest.mark.parametrize("V, K, d, residual", [(1, 64, 32, True), (512, 256, 32, True), (513, 2048, 32, False),
+                                               (131073, 320, 32, True), (262145, 2048, 32, True), (70001, 1024, 96, True)])
+def test_one_stage_rows_requested_ahead(gpu_device, V, K, d, residual):
+    """Calls of one stage on fp32 rows that can be read in 16-byte pieces request their rows a chunk ahead.  The
+    same rows at a stride that rules such pieces out take the other forms: equal bits.  One vector, whole
+    chunks, one more, workgroups with one chunk more than others, several rounds; rows of three groups.  (Not
+    scaled: the std of rows read in pieces is summed in another order, so residuals would differ by its last bit.)"""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    N = V * 32 // d
+    C = torch.randn((2, K, 32), device="cuda", generator=gen)
+    X = torch.randn((N, d), device="cuda", generator=gen)
+    odd = torch.zeros((N, d + 1), device="cuda")
+    odd[:, :d] = X
+    q = b.Quantizer(d=d, dhat=32, depth=2, K=K, scale=0, grouping=b.CONTIGUOUS, in_dtype=b.F32, encode_path=b.PATH_SCREEN)
+    q.set_codebooks(C)
+    got = []
+    for rows in (X, odd[:, :d]):
+        codes = torch.full((N, d // 32, 2), -1, dtype=torch.int16, device="cuda")
+        _, std, res = q.encode(rows, want_residual=residual, stages=(1, 2), codes=codes)
+        got.append((codes, res, std))
+    torch.cuda.synchronize()
+    q.close()
+    assert torch.equal(got[0][0], got[1][0]) and bool((got[0][0][..., 0] == -1).all())
+    assert not residual or torch.equal(got[0][1], got[1][1])
+
+
 def test_encode_chunks_of_512_and_of_1024_agree(gpu_device):
     """A call with at most 512 vectors per CU runs the matrix-core kernel with one token per lane
     (chunks of 512), a larger one with two (chunks of 1024).  A token's codes do not depend on
