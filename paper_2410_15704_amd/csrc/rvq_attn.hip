@@ -10,11 +10,10 @@
 // Lane layout: 8 lanes own one (token, group), each a 16-byte quarter of every 128-byte codeword
 // row (a row is one cache line, gathered from L2 like decode_rows32_kernel does); 32 lanes = one
 // token, a wavefront works on two tokens at a time, a workgroup of four wavefronts on eight.
-// Each half-wavefront keeps its own running maximum, sum and weighted value sum (online softmax,
-// base 2); the eight of a workgroup are merged through LDS into one partial result per
-// (kv head, split of the cache), and a second small kernel merges the splits.
-#include <type_traits>
-
+// The common case first scores a block of tokens and then adds up its values (attn_phases_kernel); the general
+// one takes each token's key and value together (attn_partial_kernel).  Either leaves one partial result per
+// (kv head, split of the cache), maximum, sum and weighted values in base 2, and a second small kernel
+// merges the splits.
 #include "rvq_internal.h"
 
 namespace {
@@ -145,21 +144,15 @@ __device__ __forceinline__ float att_sum16(float s) {
   return s;
 }
 
-// FAST: the common case with everything that shapes the loop known at compile time: depth 8 with
-// all stages used, rotation tables given, both std buffers present in half precision.  Otherwise
-// those are run-time conditions (the loop then has branches around its loads and is slower).
+// The general case: any depth up to 8, no rotation or no std, fp32 std; those are run-time conditions, and the
+// loop has branches around its loads.  attn_phases_kernel is for the others.
 // KS / VS: strided grouping of the key / value quantizer.
 // PK: 0 = int16 codes; 11 / 12 = packed records of that many bytes (depth 8 only).
-template <int REP, bool FAST, bool KS, bool VS, int PK>
+template <int REP, bool KS, bool VS, int PK>
 __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const AttnArgs a) {
-  constexpr bool D8 = FAST;
   __shared__ float sm_m[2 * ATT_WAVES][REP];
   __shared__ float sm_l[2 * ATT_WAVES][REP];
   __shared__ float sm_acc[2 * ATT_WAVES][REP][ATT_HD];
-  // FAST: what comes from HBM passes through these, one area per wavefront
-  __shared__ __align__(16) i32x4 sm_codes[FAST ? ATT_WAVES : 1][2][64];       // [K, V][half][trip of 8][group]
-  __shared__ float sm_std[FAST ? ATT_WAVES : 1][2][16];                       // [K, V][half][trip of 8]
-  __shared__ __align__(16) float sm_tab[FAST ? ATT_WAVES : 1][2][ATT_HD];     // [half][64 cos, 64 sin]
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -209,7 +202,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   const uint32_t last = (uint32_t)(nend - nbeg) - 1u;         // last token of the split, relative
   const uint32_t row_recs = (uint32_t)(a.Hkv * ATT_G);        // (row, group) records between tokens
 
-  // what a token needs from HBM; the general path fetches it one trip ahead (the gathers depend on the
+  // what a token needs from HBM; it is fetched one trip ahead (the gathers depend on the
   // codes)
   struct Pre {
     AttCodes kc, vc;
@@ -218,8 +211,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   auto fetch = [&](uint32_t t, Pre &p) {
     const uint32_t tc = t < last ? t : last;  // clamped: loads carry no branch
     const uint32_t rec = tc * row_recs + (uint32_t)g;
-    p.kc = att_load_codes<D8, PK>(kcb, rec, a.depth);
-    p.vc = att_load_codes<D8, PK>(vcb, rec, a.depth);
+    p.kc = att_load_codes<false, PK>(kcb, rec, a.depth);
+    p.vc = att_load_codes<false, PK>(vcb, rec, a.depth);
     const uint32_t ro = tc * (uint32_t)a.Hkv;
     p.ks = !ksb ? 1.0f : (a.kstd_dtype == RVQ_F32 ? ((const float *)ksb)[ro]
                                                   : rvq_f16_bits_to_f32(((const uint16_t *)ksb)[ro]));
@@ -236,13 +229,13 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   // the gathered rows: waiting for the gathers does not wait for HBM.
   struct Rows { f32x4 k[8], v[8]; };
   auto issue = [&](const Pre &p, Rows &R) {
-    att_issue<FAST, PK>(Ckb, lane_off, a.Kk, p.kc, a.k_depth_used, R.k);
-    att_issue<FAST, PK>(Cvb, lane_off, a.Kv, p.vc, a.v_depth_used, R.v);
+    att_issue<false, PK>(Ckb, lane_off, a.Kk, p.kc, a.k_depth_used, R.k);
+    att_issue<false, PK>(Cvb, lane_off, a.Kv, p.vc, a.v_depth_used, R.v);
   };
   auto work = [&](uint32_t t, const Pre &p, const Rows &R) {
     const bool valid = t <= last;
-    f32x4 k4 = att_sum<FAST>(R.k, a.k_depth_used);
-    f32x4 v4 = att_sum<FAST>(R.v, a.v_depth_used);
+    f32x4 k4 = att_sum<false>(R.k, a.k_depth_used);
+    f32x4 v4 = att_sum<false>(R.v, a.v_depth_used);
     k4 *= p.ks;
     v4 *= p.vs;
     // rotation: channel c and its partner c ^ 1 are one pair; the partner is element e ^ 1 of
@@ -280,103 +273,18 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   constexpr uint32_t STEP = 2 * ATT_WAVES;
   Rows R;
   uint32_t t = (uint32_t)hw;  // token of this half-wavefront, relative to nbeg
-  if constexpr (FAST) {
-    // The L1's address path is what bounds the loop (93 % busy): a load instruction takes it 16 cycles
-    // for 16 bytes a lane, whether or not lanes ask for the same bytes.  The eight lanes of a group
-    // share their codes and the four groups of a token their tables, so with a load per lane for each
-    // of them 176 of a trip's 432 accesses were repeats.  Here the 64 lanes fetch 64 different records,
-    // the codes of eight trips of both half-wavefronts, and the 32 lanes of a token its 512 bytes
-    // of tables, a piece each; both go through LDS, which is idle otherwise (a wavefront's own
-    // area: its LDS operations run in order, so nothing has to be waited for).  131072 tokens x 8 kv
-    // heads: 542 -> 481 us.
-    i32x4 *codes_k = sm_codes[wave][0], *codes_v = sm_codes[wave][1];
-    float *tab = sm_tab[wave][half];
-    AttCodes kn, vn;             // the next eight trips' record of this lane (trip q8, group g) ...
-    float ksn = 0.f, vsn = 0.f;  // ... and that token's std
-    auto fetch8 = [&](int it) {
-      const uint32_t tt = (uint32_t)hw + STEP * (uint32_t)(it + q8), tc = tt < last ? tt : last;
-      kn = att_load_codes<true, PK>(kcb, tc * row_recs + (uint32_t)g, 8);
-      vn = att_load_codes<true, PK>(vcb, tc * row_recs + (uint32_t)g, 8);
-      ksn = rvq_f16_bits_to_f32(((const uint16_t *)ksb)[tc * (uint32_t)a.Hkv]);
-      vsn = rvq_f16_bits_to_f32(((const uint16_t *)vsb)[tc * (uint32_t)a.Hkv]);
-    };
-    auto store8 = [&]() {
-      codes_k[half * 32 + q8 * 4 + g] = kn.w;
-      codes_v[half * 32 + q8 * 4 + g] = vn.w;
-      sm_std[wave][0][half * 8 + q8] = ksn;
-      sm_std[wave][1][half * 8 + q8] = vsn;
-    };
-    // this lane's piece of a token's tables: lanes 0..15 of the half cos, 16..31 sin
-    const int l32 = lane & 31;
-    const float *tab_src = (l32 < 16 ? cosb : sinb) + (l32 & 15) * 4;
-    auto fetch_tab = [&](uint32_t tt) -> f32x4 {
-      const uint32_t tc = tt < last ? tt : last;
-      typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
-      return *reinterpret_cast<const f32x4a4 *>(tab_src + tc * (ATT_HD / 2));
-    };
-    f32x4 tabn = {0.f, 0.f, 0.f, 0.f};
-    if (trips > 0) {
-      fetch8(0);
-      tabn = fetch_tab(t);
-      store8();
-    }
-    // trip j of a block of eight; the first one of a block requests the next block's codes, in code of
-    // its own so that the other trips do not wait for them
-    auto trip = [&](int it0, int j, auto first) {
-      Pre p;
-      __builtin_amdgcn_wave_barrier();
-      p.kc.w = codes_k[half * 32 + j * 4 + g];
-      p.vc.w = codes_v[half * 32 + j * 4 + g];
-      p.ks = sm_std[wave][0][half * 8 + j];
-      p.vs = sm_std[wave][1][half * 8 + j];
-      issue(p, R);
-      if constexpr (first) fetch8(it0 + 8);
-      __builtin_amdgcn_wave_barrier();
-      *reinterpret_cast<f32x4 *>(tab + l32 * 4) = tabn;
-      __builtin_amdgcn_wave_barrier();
-      tabn = fetch_tab(t + STEP);
-      // the lane's four channels lie in the pairs 8 q8 + 2 e + (g >> 1) (strided) or in the two pairs
-      // 16 g + 2 q8, + 1 (contiguous)
-      if constexpr (KS) {
-        const f32x4 *cp = reinterpret_cast<const f32x4 *>(tab + 8 * q8);
-        const f32x4 *sp_ = reinterpret_cast<const f32x4 *>(tab + ATT_HD / 2 + 8 * q8);
-        const f32x4 c0 = cp[0], c1 = cp[1], s0 = sp_[0], s1 = sp_[1];
-        const bool hi = (g >> 1) != 0;
-        p.cs[0] = hi ? c0[1] : c0[0]; p.cs[1] = hi ? c0[3] : c0[2];
-        p.cs[2] = hi ? c1[1] : c1[0]; p.cs[3] = hi ? c1[3] : c1[2];
-        p.sn[0] = hi ? s0[1] : s0[0]; p.sn[1] = hi ? s0[3] : s0[2];
-        p.sn[2] = hi ? s1[1] : s1[0]; p.sn[3] = hi ? s1[3] : s1[2];
-      } else {
-        typedef float f32x2 __attribute__((ext_vector_type(2)));
-        const f32x2 c2 = *reinterpret_cast<const f32x2 *>(tab + 16 * g + 2 * q8);
-        const f32x2 s2 = *reinterpret_cast<const f32x2 *>(tab + ATT_HD / 2 + 16 * g + 2 * q8);
-        p.cs[0] = p.cs[1] = c2[0]; p.cs[2] = p.cs[3] = c2[1];
-        p.sn[0] = p.sn[1] = s2[0]; p.sn[2] = p.sn[3] = s2[1];
-      }
-      work(t, p, R);
-      t += STEP;
-    };
-    for (int it = 0; it < trips; it += 8) {
-      trip(it, 0, std::true_type());
-      const int n = min(8, trips - it);
-      for (int j = 1; j < n; ++j) trip(it, j, std::false_type());
-      __builtin_amdgcn_wave_barrier();
-      store8();
-    }
-  } else {
-    Pre pa, pb;
-    if (trips > 0) fetch(t, pa);
-    for (int it = 0; it < trips; it += 2) {
-      issue(pa, R);
-      fetch(t + STEP, pb);
-      work(t, pa, R);
-      t += STEP;
-      if (it + 1 >= trips) break;
-      issue(pb, R);
-      fetch(t + STEP, pa);
-      work(t, pb, R);
-      t += STEP;
-    }
+  Pre pa, pb;
+  if (trips > 0) fetch(t, pa);
+  for (int it = 0; it < trips; it += 2) {
+    issue(pa, R);
+    fetch(t + STEP, pb);
+    work(t, pa, R);
+    t += STEP;
+    if (it + 1 >= trips) break;
+    issue(pb, R);
+    fetch(t + STEP, pa);
+    work(t, pb, R);
+    t += STEP;
   }
 
   // merge the eight half-wavefronts of the workgroup
@@ -411,50 +319,369 @@ __global__ __launch_bounds__(64 * ATT_WAVES) void attn_partial_kernel(const Attn
   }
 }
 
-// one workgroup per query head: merge the partial results of the splits and normalise
+// sums of REP values over the 32 lanes of a token: every step that can hands half of the values to the partner
+// lane and keeps the other half, so lane l ends up with the sum of value l % REP
+template <int REP>
+__device__ __forceinline__ float att_sum_token(float (&s)[REP], int lane) {
+  float v;
+  if constexpr (REP == 1) {
+    v = s[0] + att_mov_dpp<0xB1>(s[0]);
+  } else {
+    float k[REP / 2];
+#pragma unroll
+    for (int i = 0; i < REP / 2; ++i) {
+      const bool odd = (lane & 1) != 0;
+      k[i] = (odd ? s[2 * i + 1] : s[2 * i]) + att_mov_dpp<0xB1>(odd ? s[2 * i] : s[2 * i + 1]);
+    }
+    if constexpr (REP == 2) {
+      v = k[0];
+    } else {
+      float k2[REP / 4];
+#pragma unroll
+      for (int i = 0; i < REP / 4; ++i) {
+        const bool up = (lane & 2) != 0;
+        k2[i] = (up ? k[2 * i + 1] : k[2 * i]) + att_mov_dpp<0x4E>(up ? k[2 * i] : k[2 * i + 1]);
+      }
+      if constexpr (REP == 4) {
+        v = k2[0];
+      } else {
+        const bool up = (lane & 4) != 0;  // (four lanes on, whatever the lane's bit 3: both are added below)
+        v = (up ? k2[1] : k2[0]) + att_mov_dpp<0x124>(up ? k2[0] : k2[1]);
+      }
+    }
+  }
+  if constexpr (REP <= 2) v += att_mov_dpp<0x4E>(v);
+  if constexpr (REP <= 4) v += att_mov_dpp<0x124>(v);
+  v += att_mov_dpp<0x128>(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The common case: depth 8 with all stages used, rotation tables given, both std buffers in half precision.  A
+// workgroup takes ATT_BLOCK tokens at a time through two phases:
+//   keys:   every token is decoded, rotated and scored; the scores stay in LDS;
+//   (then the block's maxima, and the weights 2^(score - maximum) times the values' std, in place of the scores)
+//   values: every token is decoded and added up under its weights.
+// What bounds it is the gathers of 8 KiB of codeword rows per (token, kv head): L1 address path and L2.  Two
+// phases because
+//  - an XCD's L2 (4 MiB) holds one codebook (2 MiB at K = 2048) with room, not two: the workgroups of a launch
+//    that is resident at once stay roughly in the same phase;
+//  - a phase's rows take half the registers, so the next token's rows travel while this token's are worked on;
+//  - a token's weight is computed once, not by its 32 lanes, and nothing is rescaled per token.
+// The workgroups of the kv heads of one split sit on one XCD (ids eight apart): rotary tables and the cache
+// lines that several heads' codes share are fetched by one L2.
+// Everything from HBM passes through LDS: the 64 lanes fetch the codes of eight trips of both half-wavefronts, a
+// record each, and the 32 lanes of a token its tables, a piece each (per lane of use, 176 of a trip's 432
+// L1 accesses would repeat another lane's).  A wavefront's own areas: its LDS operations run in order.
+constexpr int ATT_BLOCK = 1024;
+template <int REP, bool KS, bool VS, int PK>
+__global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const AttnArgs a) {
+  constexpr int NT = 64 * ATT_WAVES;
+  constexpr uint32_t STEP = 2 * ATT_WAVES;               // tokens per trip of the workgroup
+  constexpr int PER = ATT_BLOCK * REP / NT;              // scores per thread
+  __shared__ __align__(16) float sm_w[ATT_BLOCK * REP];  // scores, then weights: [token of the block][query head]
+  __shared__ __align__(16) i32x4 sm_codes[ATT_WAVES][2][64];  // [eight trips, even / odd][half][trip][group]
+  __shared__ float sm_std[ATT_WAVES][2][16];                  // [even / odd][half][trip]
+  __shared__ __align__(16) float sm_tab[ATT_WAVES][2][ATT_HD];  // [half][64 cos, 64 sin]
+  __shared__ float sm_red[ATT_WAVES][REP], sm_corr[REP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, g = (lane >> 3) & 3, q8 = lane & 7;
+  // id = (split % xcds) + xcds * (head + Hkv * (split / xcds)), xcds = 8, or 1 with fewer than eight splits
+  const int id = blockIdx.x, rest = a.S >= 8 ? id >> 3 : id, h = rest % a.Hkv;
+  const int sp = a.S >= 8 ? (id & 7) + 8 * (rest / a.Hkv) : rest / a.Hkv;
+  if (sp >= a.S) return;
+  const int64_t nbeg = (int64_t)sp * a.tps;
+  const int64_t nend = nbeg + a.tps < a.N ? nbeg + a.tps : a.N;
+  const uint32_t span = (uint32_t)(nend - nbeg), last = span - 1u;  // tokens of the split (>= 1)
+  const uint32_t hw = (uint32_t)(wave * 2 + half);
+
+  int ck[4], cv[4];  // channels of this lane's four values: element j = 4 q8 + e of group g
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int j = 4 * q8 + e;
+    ck[e] = KS ? j * ATT_G + g : g * 32 + j;
+    cv[e] = VS ? j * ATT_G + g : g * 32 + j;
+  }
+  float qv[REP][4], acc[REP][4];
+#pragma unroll
+  for (int r = 0; r < REP; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      qv[r][e] = a.q[(int64_t)(h * REP + r) * ATT_HD + ck[e]] * a.scale_log2e;
+      acc[r][e] = 0.f;
+    }
+  float m_run = ATT_NEG, l_run = 0.f;  // of query head tid % REP; the sum of this thread's weights only
+
+  // 32-bit offsets from bases that are the same for the whole workgroup (the launcher checks that they fit)
+  const int64_t row0 = nbeg * a.Hkv + h;
+  constexpr int64_t REC = PK ? PK : 16;  // bytes of one (row, group)
+  const char *kcb = reinterpret_cast<const char *>(a.kcodes) + row0 * ATT_G * REC;
+  const char *vcb = reinterpret_cast<const char *>(a.vcodes) + row0 * ATT_G * REC;
+  const uint16_t *ksb = reinterpret_cast<const uint16_t *>(a.kstd) + row0;
+  const uint16_t *vsb = reinterpret_cast<const uint16_t *>(a.vstd) + row0;
+  const uint32_t hkv = (uint32_t)a.Hkv, row_recs = hkv * ATT_G;
+  const uint32_t lane_off = 16u * (uint32_t)q8;
+  // this lane's piece of a token's tables: lanes 0..15 of the half cos, 16..31 sin
+  const int l32 = lane & 31;
+  const float *tab_src = (l32 < 16 ? a.cos : a.sin) + nbeg * (ATT_HD / 2) + (l32 & 15) * 4;
+  float *tab = sm_tab[wave][half];
+
+  AttCodes cn;  // the next eight trips' record of this lane (trip q8, group g)
+  auto fetch8 = [&](const char *base, uint32_t t0, int it) {
+    const uint32_t tt = t0 + hw + STEP * (uint32_t)(it + q8), tc = tt < last ? tt : last;
+    cn = att_load_codes<true, PK>(base, tc * row_recs + (uint32_t)g, 8);
+  };
+  auto store8 = [&](int it) { sm_codes[wave][(it >> 3) & 1][half * 32 + q8 * 4 + g] = cn.w; };
+  auto codes_of = [&](int i) {
+    AttCodes c;
+    c.w = sm_codes[wave][(i >> 3) & 1][half * 32 + (i & 7) * 4 + g];
+    return c;
+  };
+
+  for (uint32_t t0 = 0; t0 < span; t0 += ATT_BLOCK) {
+    const uint32_t cnt = min(span - t0, (uint32_t)ATT_BLOCK);
+    const int trips = (int)((cnt + STEP - 1) / STEP);  // >= 1
+    // ---- keys
+    {
+      float ksn;
+      auto fetch_std = [&](int it) {
+        const uint32_t tt = t0 + hw + STEP * (uint32_t)(it + q8), tc = tt < last ? tt : last;
+        ksn = rvq_f16_bits_to_f32(ksb[tc * hkv]);
+      };
+      auto store_std = [&](int it) { sm_std[wave][(it >> 3) & 1][half * 8 + q8] = ksn; };
+      auto fetch_tab = [&](int i) -> f32x4 {
+        const uint32_t tt = t0 + hw + STEP * (uint32_t)i, tc = tt < last ? tt : last;
+        typedef float f32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+        return *reinterpret_cast<const f32x4a4 *>(tab_src + tc * (ATT_HD / 2));
+      };
+      fetch8(kcb, t0, 0);
+      fetch_std(0);
+      f32x4 tabn = fetch_tab(0), tabm = fetch_tab(1);
+      store8(0);
+      store_std(0);
+      __builtin_amdgcn_wave_barrier();
+      auto trip = [&](int i, f32x4 &tb) {
+        f32x4 R[8];
+        __builtin_amdgcn_wave_barrier();
+        att_issue<true, PK>(reinterpret_cast<const char *>(a.Ck), lane_off, a.Kk, codes_of(i), 8, R);
+        if ((i & 7) == 0) {
+          fetch8(kcb, t0, i + 8);
+          fetch_std(i + 8);
+        }
+        const float ks = sm_std[wave][(i >> 3) & 1][half * 8 + (i & 7)];
+        *reinterpret_cast<f32x4 *>(tab + l32 * 4) = tb;
+        __builtin_amdgcn_wave_barrier();
+        tb = fetch_tab(i + 2);
+        float cs[4], sn[4];
+        if constexpr (KS) {
+          // pairs 8 q8 + 2 e + (g >> 1)
+          const f32x4 *cp = reinterpret_cast<const f32x4 *>(tab + 8 * q8);
+          const f32x4 *sp_ = reinterpret_cast<const f32x4 *>(tab + ATT_HD / 2 + 8 * q8);
+          const f32x4 c0 = cp[0], c1 = cp[1], s0 = sp_[0], s1 = sp_[1];
+          const bool hi = (g >> 1) != 0;
+          cs[0] = hi ? c0[1] : c0[0]; cs[1] = hi ? c0[3] : c0[2];
+          cs[2] = hi ? c1[1] : c1[0]; cs[3] = hi ? c1[3] : c1[2];
+          sn[0] = hi ? s0[1] : s0[0]; sn[1] = hi ? s0[3] : s0[2];
+          sn[2] = hi ? s1[1] : s1[0]; sn[3] = hi ? s1[3] : s1[2];
+        } else {
+          // the two pairs 16 g + 2 q8, + 1
+          typedef float f32x2 __attribute__((ext_vector_type(2)));
+          const f32x2 c2 = *reinterpret_cast<const f32x2 *>(tab + 16 * g + 2 * q8);
+          const f32x2 s2 = *reinterpret_cast<const f32x2 *>(tab + ATT_HD / 2 + 16 * g + 2 * q8);
+          cs[0] = cs[1] = c2[0]; cs[2] = cs[3] = c2[1];
+          sn[0] = sn[1] = s2[0]; sn[2] = sn[3] = s2[1];
+        }
+        f32x4 k4 = att_sum<true>(R, 8);
+        k4 *= ks;
+        // rotation: the partner of channel c is c ^ 1, element e ^ 1 of this lane (contiguous groups) or the same
+        // element of the lane of group g ^ 1, eight lanes away in the same row of 16 (strided)
+        float kr[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float other = KS ? att_mov_dpp<0x128>(k4[e]) : k4[e ^ 1];
+          kr[e] = k4[e] * cs[e] + ((ck[e] & 1) ? other : -other) * sn[e];
+        }
+        float s[REP];
+#pragma unroll
+        for (int r = 0; r < REP; ++r) {
+          s[r] = kr[0] * qv[r][0];
+#pragma unroll
+          for (int e = 1; e < 4; ++e) s[r] = fmaf(kr[e], qv[r][e], s[r]);
+        }
+        const float v = att_sum_token<REP>(s, lane);
+        const uint32_t tt = hw + STEP * (uint32_t)i;  // token of the block
+        if (l32 < REP) sm_w[tt * REP + l32] = v;      // (beyond the end: overwritten with weight 0)
+        if ((i & 7) == 5) {
+          store8(i + 3);
+          store_std(i + 3);
+        }
+      };
+      for (int i = 0; i < trips; i += 2) {
+        trip(i, tabn);
+        if (i + 1 < trips) trip(i + 1, tabm);
+      }
+    }
+    // ---- weights
+    fetch8(vcb, t0, 0);
+    const int have = (int)cnt * REP, pad = trips * (int)STEP * REP;
+    uint16_t vs[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      vs[i] = 0;
+      if (i * NT >= pad) continue;  // (the same for the whole workgroup)
+      const uint32_t t = t0 + (uint32_t)(tid + i * NT) / REP;
+      vs[i] = vsb[(t < last ? t : last) * hkv];
+    }
+    __syncthreads();
+    {
+      float sc[PER], mx = m_run;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int idx = tid + i * NT;
+        sc[i] = -3.0e38f;
+        if (i * NT >= pad) continue;
+        if (idx < have) sc[i] = sm_w[idx];
+        mx = fmaxf(mx, sc[i]);
+      }
+#pragma unroll
+      for (int o = 32; o >= REP; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      if (lane < REP) sm_red[wave][lane] = mx;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < ATT_WAVES; ++w) mx = fmaxf(mx, sm_red[w][tid % REP]);
+      const float corr = __builtin_amdgcn_exp2f(m_run - mx);
+      l_run *= corr;
+      m_run = mx;
+      if (tid < REP) sm_corr[tid] = corr;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        if (i * NT >= pad) continue;
+        const int idx = tid + i * NT;
+        const float pw = idx < have ? __builtin_amdgcn_exp2f(sc[i] - mx) : 0.f;
+        l_run += pw;
+        if (idx < pad) sm_w[idx] = pw * rvq_f16_bits_to_f32(vs[i]);
+      }
+    }
+    store8(0);
+    __syncthreads();
+    // ---- values
+    {
+#pragma unroll
+      for (int r = 0; r < REP; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[r][e] *= sm_corr[r];
+      auto trip = [&](int i) {
+        f32x4 R[8];
+        __builtin_amdgcn_wave_barrier();
+        att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(i), 8, R);
+        if ((i & 7) == 0) fetch8(vcb, t0, i + 8);
+        const uint32_t tt = hw + STEP * (uint32_t)i;
+        float w[REP];
+#pragma unroll
+        for (int r = 0; r < REP; ++r) w[r] = sm_w[tt * REP + r];
+        const f32x4 v4 = att_sum<true>(R, 8);
+#pragma unroll
+        for (int r = 0; r < REP; ++r)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(w[r], v4[e], acc[r][e]);
+        if ((i & 7) == 5) store8(i + 3);
+      };
+      for (int i = 0; i < trips; ++i) trip(i);
+    }
+    __syncthreads();  // (the next block's scores overwrite the weights)
+  }
+
+  // ---- the workgroup's sums: the halves of a wavefront by a lane swap, the wavefronts through LDS (the
+  // weights' memory), one query head at a time where it does not hold all
+  constexpr int AT_ONCE = ATT_BLOCK * REP / (ATT_WAVES * ATT_HD) < REP ? ATT_BLOCK * REP / (ATT_WAVES * ATT_HD) : REP;
+  static_assert(AT_ONCE >= 1 && REP % AT_ONCE == 0, "the block's scores hold one head's sums at least");
+  float *dst = a.part + ((int64_t)h * a.S + sp) * REP * ATT_PART;
+#pragma unroll
+  for (int r0 = 0; r0 < REP; r0 += AT_ONCE) {
+    if (r0) __syncthreads();
+#pragma unroll
+    for (int r = r0; r < r0 + AT_ONCE; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned u = __float_as_uint(acc[r][e]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        if (half == 0) sm_w[((r - r0) * ATT_WAVES + wave) * ATT_HD + cv[e]] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+      }
+    __syncthreads();
+    for (int idx = tid; idx < AT_ONCE * ATT_HD; idx += NT) {
+      const int r = idx / ATT_HD, c = idx % ATT_HD;
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < ATT_WAVES; ++w) tot += sm_w[(r * ATT_WAVES + w) * ATT_HD + c];
+      dst[(r0 + r) * ATT_PART + 2 + c] = tot;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o >= REP; o >>= 1) l_run += __shfl_xor(l_run, o, 64);
+  if (lane < REP) sm_red[wave][lane] = l_run;
+  __syncthreads();
+  if (tid < REP) {
+    float L = 0.f;
+#pragma unroll
+    for (int w = 0; w < ATT_WAVES; ++w) L += sm_red[w][tid];
+    dst[tid * ATT_PART] = m_run;
+    dst[tid * ATT_PART + 1] = L;
+  }
+}
+
+// One workgroup per query head: merge the partial results of the splits and normalise.  Eight threads share a
+// channel, an eighth of the splits each (one thread per channel took 16 us for 256 splits, 6 for 53: round trips).
 constexpr int ATT_MAX_SPLITS = 2048;
-__global__ __launch_bounds__(ATT_HD) void attn_merge_kernel(const float *__restrict__ part, int S, int REP,
-                                                            float *__restrict__ out) {
+constexpr int ATT_MERGE = 8 * ATT_HD;
+__global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__restrict__ part, int S, int REP,
+                                                               float *__restrict__ out) {
   __shared__ float f[ATT_MAX_SPLITS];  // maxima of the splits, then their weights 2^(m_s - M)
-  __shared__ float red[ATT_HD];
-  const int hq = blockIdx.x, c = threadIdx.x;
+  __shared__ float red[ATT_MERGE / 64][2];
+  __shared__ float sums[8][ATT_HD];
+  const int hq = blockIdx.x, c = threadIdx.x % ATT_HD, oct = threadIdx.x / ATT_HD;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int h = hq / REP, r = hq % REP;
   const float *base = part + ((int64_t)h * S * REP + r) * ATT_PART;
   const int64_t stride = (int64_t)REP * ATT_PART;
-  // the largest maximum
-  float M = ATT_NEG;
-  for (int s = c; s < S; s += ATT_HD) {
-    const float ms = base[s * stride];
-    f[s] = ms;
-    M = fmaxf(M, ms);
+  float ms[ATT_MAX_SPLITS / ATT_MERGE], ls[ATT_MAX_SPLITS / ATT_MERGE], M = ATT_NEG, L = 0.f;
+#pragma unroll
+  for (int i = 0; i < ATT_MAX_SPLITS / ATT_MERGE; ++i) {
+    const int s = threadIdx.x + i * ATT_MERGE;
+    ms[i] = s < S ? base[s * stride] : ATT_NEG;
+    ls[i] = s < S ? base[s * stride + 1] : 0.f;
+    M = fmaxf(M, ms[i]);
   }
-  red[c] = M;
+  for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+  if (lane == 0) red[wave][0] = M;
   __syncthreads();
-  for (int o = ATT_HD / 2; o > 0; o >>= 1) {
-    if (c < o) red[c] = fmaxf(red[c], red[c + o]);
-    __syncthreads();
+#pragma unroll
+  for (int w = 0; w < ATT_MERGE / 64; ++w) M = fmaxf(M, red[w][0]);
+#pragma unroll
+  for (int i = 0; i < ATT_MAX_SPLITS / ATT_MERGE; ++i) {
+    const int s = threadIdx.x + i * ATT_MERGE;
+    const float w = __builtin_amdgcn_exp2f(ms[i] - M);
+    if (s < S) {
+      f[s] = w;
+      L = fmaf(ls[i], w, L);
+    }
   }
-  M = red[0];
+  for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o, 64);
+  if (lane == 0) red[wave][1] = L;
   __syncthreads();
-  // weights of the splits and the total sum
-  float L = 0.f;
-  for (int s = c; s < S; s += ATT_HD) {
-    const float w = __builtin_amdgcn_exp2f(f[s] - M);
-    f[s] = w;
-    L = fmaf(base[s * stride + 1], w, L);
-  }
-  red[c] = L;
-  __syncthreads();
-  for (int o = ATT_HD / 2; o > 0; o >>= 1) {
-    if (c < o) red[c] += red[c + o];
-    __syncthreads();
-  }
-  L = red[0];
-  // channel c: the loads of different splits do not depend on each other
   float tot = 0.f;
 #pragma unroll 8
-  for (int s = 0; s < S; ++s) tot = fmaf(base[s * stride + 2 + c], f[s], tot);
-  out[(int64_t)hq * ATT_HD + c] = tot / L;
+  for (int s = oct; s < S; s += 8) tot = fmaf(base[s * stride + 2 + c], f[s], tot);
+  sums[oct][c] = tot;
+  __syncthreads();
+  if (oct == 0) {
+    L = 0.f;
+    tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < ATT_MERGE / 64; ++w) L += red[w][1];
+#pragma unroll
+    for (int w = 0; w < 8; ++w) tot += sums[w][c];
+    out[(int64_t)hq * ATT_HD + c] = tot / L;
+  }
 }
 
 }  // namespace
@@ -516,30 +743,44 @@ hipError_t rvq_launch_attn_decode(const rvq_ctx *kctx, const rvq_ctx *vctx, cons
   a.v_strided = vctx->cfg.grouping == RVQ_STRIDED;
   a.scale_log2e = scale * 1.4426950408889634f;
   const int rep = Hq / Hkv;
-  const dim3 grid((unsigned)(a.S * Hkv)), block(64 * ATT_WAVES);
   const bool fast = a.depth == 8 && k_depth_used == 8 && v_depth_used == 8 && dCos && dKStd && dVStd &&
                     a.kstd_dtype == RVQ_F16 && a.vstd_dtype == RVQ_F16;
-#define RVQ_ATT_LAUNCH5(R, F, P)                                                                       \
-  if (a.k_strided) {                                                                                   \
-    if (a.v_strided) hipLaunchKernelGGL((attn_partial_kernel<R, F, true, true, P>), grid, block, 0, s, a);  \
-    else hipLaunchKernelGGL((attn_partial_kernel<R, F, true, false, P>), grid, block, 0, s, a);        \
-  } else {                                                                                             \
-    if (a.v_strided) hipLaunchKernelGGL((attn_partial_kernel<R, F, false, true, P>), grid, block, 0, s, a); \
-    else hipLaunchKernelGGL((attn_partial_kernel<R, F, false, false, P>), grid, block, 0, s, a);       \
+  if (fast) {
+    // Two workgroups per CU, resident at once, so that their phases stay together; whole multiples of the XCDs,
+    // so that no CU has a third.  131072 tokens x 8 kv heads, 4 queries each: one workgroup per CU 463 us, two
+    // 338, one and a half 464, two and a half 450, three 377 (blocks of 512), four 368.
+    int64_t cap = 2 * (int64_t)(kctx->num_cus > 0 ? kctx->num_cus : 1) / Hkv;
+    if (cap >= 8) cap = cap / 8 * 8;
+    if (cap >= 1 && a.S > cap) {
+      const int64_t longer = ((N + cap - 1) / cap + 7) / 8 * 8;
+      if (longer * Hkv * ATT_G * 16 < (int64_t)1 << 32) {  // (codes of a split are addressed with 32 bits)
+        a.tps = longer;
+        a.S = (int)((N + longer - 1) / longer);
+      }
+    }
   }
-#define RVQ_ATT_LAUNCH4(R, F)                        \
+  const dim3 grid((unsigned)((fast && a.S >= 8 ? (a.S + 7) / 8 * 8 : a.S) * Hkv)), block(64 * ATT_WAVES);
+#define RVQ_ATT_LAUNCH3(KERNEL, R, P)                                                                 \
+  if (a.k_strided) {                                                                                 \
+    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, true, true, P>), grid, block, 0, s, a);           \
+    else hipLaunchKernelGGL((KERNEL<R, true, false, P>), grid, block, 0, s, a);                      \
+  } else {                                                                                           \
+    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, false, true, P>), grid, block, 0, s, a);          \
+    else hipLaunchKernelGGL((KERNEL<R, false, false, P>), grid, block, 0, s, a);                     \
+  }
+#define RVQ_ATT_LAUNCH2(KERNEL, R)                   \
   if (packed_bytes == 11) {                          \
-    RVQ_ATT_LAUNCH5(R, F, 11)                        \
+    RVQ_ATT_LAUNCH3(KERNEL, R, 11)                   \
   } else if (packed_bytes == 12) {                   \
-    RVQ_ATT_LAUNCH5(R, F, 12)                        \
+    RVQ_ATT_LAUNCH3(KERNEL, R, 12)                   \
   } else {                                           \
-    RVQ_ATT_LAUNCH5(R, F, 0)                         \
+    RVQ_ATT_LAUNCH3(KERNEL, R, 0)                    \
   }
-#define RVQ_ATT_LAUNCH(R)          \
-  if (fast) {                      \
-    RVQ_ATT_LAUNCH4(R, true)       \
-  } else {                         \
-    RVQ_ATT_LAUNCH4(R, false)      \
+#define RVQ_ATT_LAUNCH(R)                            \
+  if (fast) {                                        \
+    RVQ_ATT_LAUNCH2(attn_phases_kernel, R)           \
+  } else {                                           \
+    RVQ_ATT_LAUNCH2(attn_partial_kernel, R)          \
   }
   switch (rep) {
     case 1: RVQ_ATT_LAUNCH(1) break;
@@ -548,10 +789,10 @@ hipError_t rvq_launch_attn_decode(const rvq_ctx *kctx, const rvq_ctx *vctx, cons
     default: RVQ_ATT_LAUNCH(8) break;
   }
 #undef RVQ_ATT_LAUNCH
-#undef RVQ_ATT_LAUNCH4
-#undef RVQ_ATT_LAUNCH5
+#undef RVQ_ATT_LAUNCH2
+#undef RVQ_ATT_LAUNCH3
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)Hq), dim3(ATT_HD), 0, s, dWork, a.S, rep, dOut);
+  hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)Hq), dim3(ATT_MERGE), 0, s, dWork, a.S, rep, dOut);
   return hipGetLastError();
 }

@@ -116,6 +116,17 @@ def test_attn_decode_sharp_and_flat_softmax(gpu_device):
         np.testing.assert_allclose(got[a], vx[a // 4], rtol=1e-4, atol=1e-5 * np.abs(vx).max())
 
 
+@pytest.mark.parametrize("N, Hkv, rep, kg, vg", [
+    (2100, 256, 1, oracle.STRIDED, oracle.CONTIGUOUS),   # fewer splits than XCDs, two blocks each, a ragged second
+    (8201, 64, 2, oracle.CONTIGUOUS, oracle.STRIDED),    # the second block of a split is one trip, of the last one token
+    (1025, 1, 8, oracle.STRIDED, oracle.STRIDED),        # as many splits as the workspace holds
+])
+def test_attn_decode_blocks_and_splits(gpu_device, N, Hkv, rep, kg, vg):
+    """Splits of more tokens than a block holds, with queries sharp enough that the running maximum moves between
+    blocks, and both orders of workgroups; the bar is the other tests'."""
+    _check(_case(2000 + N, N, Hkv, rep, 8, 512, 256, kg, vg, sharp=4.0))
+
+
 def test_attn_decode_equals_decode_then_attention_on_the_gpu(gpu_device):
     """The fused call against the unfused route through the library's own decode entry points
     (rvq_decode_rope for keys, rvq_decode for values, fp32 outputs) followed by a plain softmax
