@@ -378,11 +378,12 @@ template <int REP, bool KS, bool VS, int PK>
 __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const AttnArgs a) {
   constexpr int NT = 64 * ATT_WAVES;
   constexpr uint32_t STEP = 2 * ATT_WAVES;               // tokens per trip of the workgroup
-  constexpr int PER = ATT_BLOCK * REP / NT;              // scores per thread
+  constexpr int VPT = ATT_BLOCK / NT;                    // value stds per thread
   __shared__ __align__(16) float sm_w[ATT_BLOCK * REP];  // scores, then weights: [token of the block][query head]
-  __shared__ __align__(16) i32x4 sm_codes[ATT_WAVES][2][64];  // [eight trips, even / odd][half][trip][group]
+  __shared__ __align__(16) i32x4 sm_codes[2][ATT_WAVES][2][64];  // [K, V][eight trips, even / odd][half][trip][group]
   __shared__ float sm_std[ATT_WAVES][2][16];                  // [even / odd][half][trip]
   __shared__ __align__(16) float sm_tab[ATT_WAVES][2][ATT_HD];  // [half][64 cos, 64 sin]
+  __shared__ float sm_vs[ATT_BLOCK];                          // the values' std
   __shared__ float sm_red[ATT_WAVES][REP], sm_corr[REP];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, g = (lane >> 3) & 3, q8 = lane & 7;
@@ -431,16 +432,22 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
     const uint32_t tt = t0 + hw + STEP * (uint32_t)(it + q8), tc = tt < last ? tt : last;
     cn = att_load_codes<true, PK>(base, tc * row_recs + (uint32_t)g, 8);
   };
-  auto store8 = [&](int it) { sm_codes[wave][(it >> 3) & 1][half * 32 + q8 * 4 + g] = cn.w; };
-  auto codes_of = [&](int i) {
+  auto store8 = [&](int kv, int it) { sm_codes[kv][wave][(it >> 3) & 1][half * 32 + q8 * 4 + g] = cn.w; };
+  auto codes_of = [&](int kv, int i) {
     AttCodes c;
-    c.w = sm_codes[wave][(i >> 3) & 1][half * 32 + (i & 7) * 4 + g];
+    c.w = sm_codes[kv][wave][(i >> 3) & 1][half * 32 + (i & 7) * 4 + g];
     return c;
   };
 
   for (uint32_t t0 = 0; t0 < span; t0 += ATT_BLOCK) {
     const uint32_t cnt = min(span - t0, (uint32_t)ATT_BLOCK);
     const int trips = (int)((cnt + STEP - 1) / STEP);  // >= 1
+    uint16_t vstd[VPT];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      const uint32_t t = t0 + (uint32_t)(tid + i * NT);
+      vstd[i] = vsb[(t < last ? t : last) * hkv];
+    }
     // ---- keys
     {
       float ksn;
@@ -456,15 +463,21 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       };
       fetch8(kcb, t0, 0);
       fetch_std(0);
+      const AttCodes kn = cn;
+      fetch8(vcb, t0, 0);
+      const AttCodes vn = cn;
+      cn = kn;
       f32x4 tabn = fetch_tab(0), tabm = fetch_tab(1);
-      store8(0);
+      store8(0, 0);
       store_std(0);
+      cn = vn;
+      store8(1, 0);
       __builtin_amdgcn_wave_barrier();
       auto trip = [&](int i, f32x4 &tb) {
         f32x4 R[8];
         __builtin_amdgcn_wave_barrier();
-        att_issue<true, PK>(reinterpret_cast<const char *>(a.Ck), lane_off, a.Kk, codes_of(i), 8, R);
-        if ((i & 7) == 0) {
+        att_issue<true, PK>(reinterpret_cast<const char *>(a.Ck), lane_off, a.Kk, codes_of(0, i), 8, R);
+        if ((i & 7) == 0 && i + 8 < trips) {
           fetch8(kcb, t0, i + 8);
           fetch_std(i + 8);
         }
@@ -511,8 +524,8 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
         const float v = att_sum_token<REP>(s, lane);
         const uint32_t tt = hw + STEP * (uint32_t)i;  // token of the block
         if (l32 < REP) sm_w[tt * REP + l32] = v;      // (beyond the end: overwritten with weight 0)
-        if ((i & 7) == 5) {
-          store8(i + 3);
+        if ((i & 7) == 5 && i + 3 < trips) {
+          store8(0, i + 3);
           store_std(i + 3);
         }
       };
@@ -522,27 +535,17 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       }
     }
     // ---- weights
-    fetch8(vcb, t0, 0);
-    const int have = (int)cnt * REP, pad = trips * (int)STEP * REP;
-    uint16_t vs[PER];
+    // the first trip's rows travel under the weights
+    f32x4 R[8];
+    __builtin_amdgcn_wave_barrier();
+    att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, 0), 8, R);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      vs[i] = 0;
-      if (i * NT >= pad) continue;  // (the same for the whole workgroup)
-      const uint32_t t = t0 + (uint32_t)(tid + i * NT) / REP;
-      vs[i] = vsb[(t < last ? t : last) * hkv];
-    }
+    for (int i = 0; i < VPT; ++i) sm_vs[tid + i * NT] = rvq_f16_bits_to_f32(vstd[i]);
     __syncthreads();
     {
-      float sc[PER], mx = m_run;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int idx = tid + i * NT;
-        sc[i] = -3.0e38f;
-        if (i * NT >= pad) continue;
-        if (idx < have) sc[i] = sm_w[idx];
-        mx = fmaxf(mx, sc[i]);
-      }
+      const int have = (int)cnt * REP, pad = trips * (int)STEP * REP;
+      float mx = m_run;
+      for (int idx = tid; idx < have; idx += NT) mx = fmaxf(mx, sm_w[idx]);
 #pragma unroll
       for (int o = 32; o >= REP; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
       if (lane < REP) sm_red[wave][lane] = mx;
@@ -553,16 +556,12 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       l_run *= corr;
       m_run = mx;
       if (tid < REP) sm_corr[tid] = corr;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        if (i * NT >= pad) continue;
-        const int idx = tid + i * NT;
-        const float pw = idx < have ? __builtin_amdgcn_exp2f(sc[i] - mx) : 0.f;
+      for (int idx = tid; idx < pad; idx += NT) {
+        const float pw = idx < have ? __builtin_amdgcn_exp2f(sm_w[idx] - mx) : 0.f;
         l_run += pw;
-        if (idx < pad) sm_w[idx] = pw * rvq_f16_bits_to_f32(vs[i]);
+        sm_w[idx] = pw * sm_vs[idx / REP];
       }
     }
-    store8(0);
     __syncthreads();
     // ---- values
     {
@@ -570,11 +569,10 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       for (int r = 0; r < REP; ++r)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[r][e] *= sm_corr[r];
-      auto trip = [&](int i) {
-        f32x4 R[8];
+      auto trip = [&](int i, bool first) {
         __builtin_amdgcn_wave_barrier();
-        att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(i), 8, R);
-        if ((i & 7) == 0) fetch8(vcb, t0, i + 8);
+        if (!first) att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, i), 8, R);
+        if ((i & 7) == 0 && i + 8 < trips) fetch8(vcb, t0, i + 8);
         const uint32_t tt = hw + STEP * (uint32_t)i;
         float w[REP];
 #pragma unroll
@@ -584,9 +582,10 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
         for (int r = 0; r < REP; ++r)
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(w[r], v4[e], acc[r][e]);
-        if ((i & 7) == 5) store8(i + 3);
+        if ((i & 7) == 5 && i + 3 < trips) store8(1, i + 3);
       };
-      for (int i = 0; i < trips; ++i) trip(i);
+      trip(0, true);
+      for (int i = 1; i < trips; ++i) trip(i, false);
     }
     __syncthreads();  // (the next block's scores overwrite the weights)
   }
@@ -643,6 +642,11 @@ __global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__re
   const int h = hq / REP, r = hq % REP;
   const float *base = part + ((int64_t)h * S * REP + r) * ATT_PART;
   const int64_t stride = (int64_t)REP * ATT_PART;
+  // the first rounds of partial sums are requested along with the maxima
+  constexpr int AHEAD = 8;
+  float ps[AHEAD];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) ps[i] = oct + 8 * i < S ? base[(oct + 8 * i) * stride + 2 + c] : 0.f;
   float ms[ATT_MAX_SPLITS / ATT_MERGE], ls[ATT_MAX_SPLITS / ATT_MERGE], M = ATT_NEG, L = 0.f;
 #pragma unroll
   for (int i = 0; i < ATT_MAX_SPLITS / ATT_MERGE; ++i) {
@@ -669,8 +673,11 @@ __global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__re
   if (lane == 0) red[wave][1] = L;
   __syncthreads();
   float tot = 0.f;
-#pragma unroll 8
-  for (int s = oct; s < S; s += 8) tot = fmaf(base[s * stride + 2 + c], f[s], tot);
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i)
+    if (oct + 8 * i < S) tot = fmaf(ps[i], f[oct + 8 * i], tot);
+#pragma unroll 4
+  for (int s = oct + 8 * AHEAD; s < S; s += 8) tot = fmaf(base[s * stride + 2 + c], f[s], tot);
   sums[oct][c] = tot;
   __syncthreads();
   if (oct == 0) {
