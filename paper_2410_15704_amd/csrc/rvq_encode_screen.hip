@@ -681,9 +681,12 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   // stage).  Every wavefront runs L(0) T(0) L(1) T(1) ... at its own pace; the workgroup meets
   // only to swap the operands in LDS between stages, and not at a barrier (see the counters
   // below).  For that swap the eight wavefronts form two teams: team 0 (wavefronts 0..3) copies,
-  // team 1 only waits for the copy.  A codebook larger than LDS is swept in chunks with workgroup
-  // barriers inside phase L: there every wavefront is in team 0.
-  const int team = (single_chunk && wave >= SCR_WAVES / 2) ? 1 : 0;
+  // team 1 only waits for the copy.  A codebook larger than LDS is taken a piece of SCR_KC codewords at a
+  // time: phase L and the exact scores of the piece's candidates per piece, the rest of phase T once; the
+  // pieces are swapped by the same counters as the stages.  (At two workgroup barriers per piece, as it
+  // was, the wavefronts went in step and the copy of a piece stood alone: 6000 rows of 128 groups, K = 4096, depth
+  // 8 2180 us, 2117 now; 1000 rows, one token per lane, 500 us, 406 now.)
+  const int team = wave >= SCR_WAVES / 2 ? 1 : 0;
 
   // ---- per-stage state of this lane's two tokens
   // fp16 residual as packed pairs: [0..7] channels 0..15, [8..15] channels 16..31 of the lane's own
@@ -797,22 +800,11 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   };
 
   // ---- phase L of a stage: everything that reads the stage's operands in LDS
-  auto lds_phase = [&](int stage) {
-    // (a codebook that fits has one piece: the bound is a constant, and the loop goes away)
-    for (int cbase = 0; cbase < a.Kpad; cbase += SCR_KC) {
+  auto lds_phase = [&](int stage, int first_code, int end_code) {
+    // (one piece per call; as a loop, the phases stay blocks of their own and the registers with them)
+    for (int cbase = first_code; cbase < end_code; cbase += SCR_KC) {
       const int kc = min(SCR_KC, a.Kpad - cbase);
       const int ntiles = kc >> 5;
-      // ---- stage the chunk's operands in LDS (a codebook that fits LDS whole was staged by the
-      // caller of this phase): linear copies, the global layouts are already what the kernel
-      // reads, moved by direct global->LDS loads so no registers are tied up
-      if (!single_chunk) {
-        __syncthreads();
-        stage_to_lds(stage, cbase, kc, wave, SCR_WAVES);
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wavefront's direct loads have landed
-        __syncthreads();
-      }
-      PHASE_MARK(2);  // staging + barriers
-
       // ---- sweep: three smallest tagged group lower bounds per lane and token tile.
       // Software pipeline over two accumulator sets (see SWEEP_TILE); the fences pin its order.
       float m1[SCR_TT], m2[SCR_TT], m3[SCR_TT];
@@ -1157,12 +1149,6 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         }
       }
       PHASE_MARK(7);  // resolve: group-wide exact passes
-
-      if (!single_chunk) {
-        exact_candidates(stage);
-#pragma unroll
-        for (int k = 0; k < NDT; ++k) nc[k] = 0;  // new lists per chunk of the codebook
-      }
     }
   };
 
@@ -1280,20 +1266,32 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       __hip_atomic_fetch_add((lds_u32 *)(lds_f + idx), 1u, __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_WORKGROUP);
   };
-  if (single_chunk) {
-    if (tid < 4) lds_f[tid] = 0u;
-    // the first stage's operands: copied by all wavefronts
-    stage_to_lds(a.stage_begin, 0, a.Kpad, wave, SCR_WAVES);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wavefront's direct loads have landed
-    __syncthreads();
-    PHASE_MARK(2);  // staging
-  }
+  if (tid < 4) lds_f[tid] = 0u;
+  // the first operands: copied by all wavefronts
+  stage_to_lds(a.stage_begin, 0, min(a.Kpad, SCR_KC), wave, SCR_WAVES);
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wavefront's direct loads have landed
+  __syncthreads();
+  PHASE_MARK(2);  // staging
   // sg counts the (chunk, stage) steps of this workgroup: stage sg % nst of its chunk sg / nst.
   // A wavefront carries straight on from the last stage of one chunk to the first of the next
   // (the tail phase of a chunk's last stage stores its residuals; the next chunk is loaded at the
   // top of the following step), so input load and first operand copy are not paid per chunk at a
   // barrier.  Both teams run the same sequence L(0) T(0) L(1) T(1) ...; they differ in who copies.
   const int SG = nmy * nst;
+  // the operands that a phase L works on: swapped in before it, given up after it
+  auto operands = [&](unsigned swaps, int stage, int cb) {
+    if (team == 0) {
+      spin_ge(0, (unsigned)(SCR_WAVES / 2) * swaps);
+      spin_ge(1, (unsigned)(SCR_WAVES / 2) * swaps);
+      PHASE_MARK(8);  // waiting for the end of the previous phase L
+      stage_to_lds(stage, cb, min(a.Kpad - cb, SCR_KC), wave, SCR_WAVES / 2);
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+      signal(2);
+    }
+    spin_ge(2, (unsigned)(SCR_WAVES / 2) * swaps);
+    PHASE_MARK(2);  // staging
+  };
+  unsigned swaps = 0;  // phases L behind this wavefront (codebooks in pieces)
   if constexpr (PRE) request_chunk(blockIdx.x);
   for (int sg = 0; sg < SG; ++sg) {
     if (load_next >= 0) {  // the first chunk, or the one after a chunk's last stage
@@ -1304,20 +1302,21 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       convert(a.stage_begin);
     }
     const int i = sg % nst;
-    if (single_chunk && sg > 0 && nst > 1) {  // (one stage per call: the operands stay)
-      if (team == 0) {
-        spin_ge(0, (unsigned)(SCR_WAVES / 2) * sg);
-        spin_ge(1, (unsigned)(SCR_WAVES / 2) * sg);
-        PHASE_MARK(8);  // waiting for the end of the previous stage's phase L
-        stage_to_lds(a.stage_begin + i, 0, a.Kpad, wave, SCR_WAVES / 2);
-        __builtin_amdgcn_s_waitcnt(0x0f70);
-        signal(2);
+    if constexpr (single_chunk) {
+      if (sg > 0 && nst > 1) operands((unsigned)sg, a.stage_begin + i, 0);  // (one stage per call: the operands stay)
+      lds_phase(a.stage_begin + i, 0, a.Kpad);
+      signal(team);
+    } else {
+      for (int cb = 0; cb < a.Kpad; cb += SCR_KC) {
+        if (swaps > 0) operands(swaps, a.stage_begin + i, cb);
+        lds_phase(a.stage_begin + i, cb, min(cb + SCR_KC, a.Kpad));
+        signal(team);
+        ++swaps;
+        exact_candidates(a.stage_begin + i);
+#pragma unroll
+        for (int k = 0; k < NDT; ++k) nc[k] = 0;  // new lists per piece of the codebook
       }
-      spin_ge(2, (unsigned)(SCR_WAVES / 2) * sg);
-      PHASE_MARK(2);  // staging
     }
-    lds_phase(a.stage_begin + i);
-    if (single_chunk) signal(team);
     const int64_t nextc = (sg + 1 < SG && i == nst - 1)
                               ? (int64_t)blockIdx.x + (int64_t)(sg / nst + 1) * gridDim.x : -1;
     tail_phase(a.stage_begin + i, nextc);
