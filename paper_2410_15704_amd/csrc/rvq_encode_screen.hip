@@ -1385,21 +1385,21 @@ hipError_t rvq_launch_encode_screen(const rvq_ctx *ctx, const void *dX, int64_t 
   // one workgroup fills a CU (LDS): as many workgroups as CUs, each walking its share of the chunks
   // Two tokens per lane (chunks of 1024) or one (chunks of 512)?  A
   // workgroup takes its chunks one after the other, and the call lasts as long as the workgroup
-  // with the most of them: measured, 350 us per chunk of 1024 and 190 us per chunk of 512.  The
-  // form with the shorter estimate runs: one token per lane for calls that leave CUs idle
-  // otherwise, and where it evens out a ragged last round (9000 rows of 32 groups: three rounds
-  // of 512 instead of two of 1024).
+  // with the most of them.  A chunk of 512 takes 0.48 of the time of one of 1024 with up to 512 codewords, 0.51
+  // with 1024 and 0.54 beyond (the sweep's reads from LDS per token are what the larger chunk saves; short
+  // stages are rather a matter of registers), and the form with the shorter estimate runs.  Two : one token per
+  // lane, us, depth 8, value rows of 32 groups, 1000, 1500 and 4090 vectors per CU: K = 256 184 : 173, 333 : 248,
+  // 656 : 638; K = 512 210 : 196, 370 : 279, 719 : 711; K = 1024 252 : 250, 455 : 363, 906 : 944; K = 2048 375 : 386, 666 : 553,
+  // 1361 : 1451; K = 4096 (two pieces) 681 : 710, 1210 : 1043, 2515 : 2749.
   const int64_t cus = ctx->num_cus > 0 ? ctx->num_cus : 1;
   const int64_t rounds_full = ((a.V + SCR_TOKENS - 1) / SCR_TOKENS + cus - 1) / cus;
   const int64_t rounds_half = ((a.V + SCR_TOKENS / 2 - 1) / (SCR_TOKENS / 2) + cus - 1) / cus;
-  // (a codebook swept in pieces pays its copies and barriers per chunk: there the one-token form
-  // is taken only where it is a single round)
   // One stage of fp32 rows in 16-byte pieces, a step of codebook learning: the form that requests rows ahead,
   // whatever the size (stage of unclustered residuals, two tokens per lane : ahead, us: K = 2048, 2^20 vectors
   // 249 : 212, 300000 94 : 85, 150000 67 : 57; K = 1024 192 : 153, 71 : 60, 54 : 40; K = 256 164 : 104,
   // 62 : 46, 48 : 32).
   const bool pre = a.Kpad <= SCR_KC && stage_end - stage_begin == 1 && a.vec_rows && c.in_dtype == RVQ_F32;
-  const bool half = pre ? true : a.Kpad <= SCR_KC ? rounds_half * 19 < rounds_full * 35 : rounds_half == 1;
+  const bool half = pre || rounds_half * (a.Kpad <= 512 ? 48 : (a.Kpad <= 1024 ? 51 : 54)) < rounds_full * 100;
   const int64_t chunk = half ? SCR_TOKENS / 2 : SCR_TOKENS;
   const int64_t nchunks = (a.V + chunk - 1) / chunk;
   const int64_t grid64 = nchunks < ctx->num_cus ? nchunks : ctx->num_cus;
