@@ -1048,6 +1048,29 @@ def test_packed_codes_and_decode_packed(gpu_device, case):
         q.close()
 
 
+@pytest.mark.parametrize("K", [1, 2, 100, 1024, 2048, 4096, 20000, 32768])
+@pytest.mark.parametrize("V", [1, 255, 256, 257, 3001])
+def test_pack_records_of_eight_codes(gpu_device, K, V):
+    """Records of eight codes, every kind of code width, whole and ragged workgroups, codes outside [0, K): the bits
+    of the clamped codes, low end first, and nothing behind the last record."""
+    torch, b = _torch(), _b()
+    rng = np.random.Generator(np.random.PCG64(K + V))
+    codes = rng.integers(0, K, (V, 1, 8)).astype(np.int16)
+    codes[:: 5, 0, 3] = -7
+    if K < 32768:
+        codes[:: 7, 0, 6] = 32767
+    bits = max(1, (K - 1).bit_length())
+    q = b.Quantizer(d=32, dhat=32, depth=8, K=K, scale=0)
+    out = torch.full((V * bits + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+    b.rvq_pack_codes(q.ctx, torch.from_numpy(codes).cuda(), V, out)
+    torch.cuda.synchronize()
+    q.close()
+    c = np.clip(codes.astype(np.int64), 0, K - 1).reshape(V, 8)
+    want = np.packbits(((c[:, :, None] >> np.arange(bits)) & 1).reshape(V, -1).astype(np.uint8), axis=1, bitorder="little")
+    got = out.cpu().numpy()
+    assert np.array_equal(got[:V * bits], want.reshape(-1)) and (got[V * bits:] == 0xA5).all()
+
+
 def test_decode_packed_slice_matches_decode(gpu_device):
     """A full workload-3 slice (524288 tokens, strided: the LDS kernel; contiguous: the row-gather
     kernel) decoded from 11-bit records equals the decode from int16 codes bit for bit; the
