@@ -54,6 +54,7 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int SCR_WAVES = 8;
 constexpr int SCR_TT = 4;                              // token tiles per wavefront
@@ -722,18 +723,22 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       float s_q = 0.f, s_d = 0.f;
 #pragma unroll
       for (int j = 0; j < 32; j += 2) {
-        _Float16 hx[2];
+        // (12 instructions a pair instead of 15: both elements are rounded by one instruction, whose result the
+        // compiler is kept from computing again element by element, and their squares are one dot product:
+        // 32768 rows 1315 -> 1306 us, 6000 rows of 4096 channels 1966 -> 1959 and 2016 -> 2000)
+        f32x2 x;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) x[e] = (fabsf(r[k][j + e]) < tiny ? 0.f : r[k][j + e]) * Tscale;
+        unsigned pw = __builtin_bit_cast(unsigned, __builtin_convertvector(x, half2v));
+        asm volatile("" : "+v"(pw));
+        const half2v pr = __builtin_bit_cast(half2v, pw);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          const float x = r[k][j + e] * Tscale;  // exact
-          hx[e] = fabsf(r[k][j + e]) < tiny ? (_Float16)0.f : (_Float16)x;
-          const float xr = (float)hx[e];
-          const float dx = x - xr;  // exact
-          s_q = fmaf(xr, xr, s_q);
+          const float dx = fmaf(r[k][j + e], Tscale, -(float)pr[e]);  // exact
           s_d = fmaf(dx, dx, s_d);
         }
-        const half2v pr = {hx[0], hx[1]};
-        Bw[k][j >> 1] = __builtin_bit_cast(unsigned, pr);
+        s_q = __builtin_amdgcn_fdot2(pr, pr, s_q, false);
+        Bw[k][j >> 1] = pw;
       }
       const float nq = sqrtf(s_q) * 1.000001f;
       const float nd = sqrtf(s_d) * 1.000001f;
