@@ -357,10 +357,32 @@ __device__ __forceinline__ float att_sum_token(float (&s)[REP], int lane) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// op over the lanes of a wavefront that agree modulo REP (1, 2, 4 or 8), in every lane: by lane moves, none of
+// which goes through LDS (six shuffles there are a quarter of a microsecond, twice per workgroup and merge)
+template <int REP, class Op>
+__device__ __forceinline__ float att_wave_reduce(float v, Op op) {
+  {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  v = op(v, att_mov_dpp<0x128>(v));
+  if constexpr (REP <= 4) v = op(v, att_mov_dpp<0x124>(v));
+  if constexpr (REP <= 2) v = op(v, att_mov_dpp<0x4E>(v));
+  if constexpr (REP <= 1) v = op(v, att_mov_dpp<0xB1>(v));
+  return v;
+}
+__device__ __forceinline__ float att_max(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ float att_add(float a, float b) { return a + b; }
+
 // The common case: depth 8 with all stages used, rotation tables given, both std buffers in half precision.  A
 // workgroup takes ATT_BLOCK tokens at a time through two phases:
 //   keys:   every token is decoded, rotated and scored; the scores stay in LDS;
-//   (then the block's maxima, and the weights 2^(score - maximum) times the values' std, in place of the scores)
+//   (then the maxima of the wavefront's tokens, and the weights 2^(score - maximum) times the values' std, in place
+//   of the scores: every wavefront by itself, there is no barrier before the end)
 //   values: every token is decoded and added up under its weights.
 // What bounds it is the gathers of 8 KiB of codeword rows per (token, kv head): L1 address path and L2.  Two
 // phases because
@@ -378,13 +400,14 @@ template <int REP, bool KS, bool VS, int PK>
 __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const AttnArgs a) {
   constexpr int NT = 64 * ATT_WAVES;
   constexpr uint32_t STEP = 2 * ATT_WAVES;               // tokens per trip of the workgroup
-  constexpr int VPT = ATT_BLOCK / NT;                    // value stds per thread
-  __shared__ __align__(16) float sm_w[ATT_BLOCK * REP];  // scores, then weights: [token of the block][query head]
+  constexpr int BW = ATT_BLOCK / ATT_WAVES;              // tokens of a wavefront in a block
+  constexpr int VPT = BW / 64;                           // value stds per lane
+  __shared__ __align__(16) float sm_w[ATT_BLOCK * REP];  // scores, then weights: [wavefront][token][query head]
   __shared__ __align__(16) i32x4 sm_codes[2][ATT_WAVES][2][64];  // [K, V][eight trips, even / odd][half][trip][group]
   __shared__ float sm_std[ATT_WAVES][2][16];                  // [even / odd][half][trip]
   __shared__ __align__(16) float sm_tab[ATT_WAVES][2][ATT_HD];  // [half][64 cos, 64 sin]
-  __shared__ float sm_vs[ATT_BLOCK];                          // the values' std
-  __shared__ float sm_red[ATT_WAVES][REP], sm_corr[REP];
+  __shared__ float sm_vs[ATT_WAVES][BW];                      // the values' std
+  __shared__ float sm_m[ATT_WAVES][REP], sm_l[ATT_WAVES][REP], sm_corr[ATT_WAVES][REP];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, g = (lane >> 3) & 3, q8 = lane & 7;
   // id = (split % xcds) + xcds * (head + Hkv * (split / xcds)), xcds = 8, or 1 with fewer than eight splits
@@ -411,7 +434,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       qv[r][e] = a.q[(int64_t)(h * REP + r) * ATT_HD + ck[e]] * a.scale_log2e;
       acc[r][e] = 0.f;
     }
-  float m_run = ATT_NEG, l_run = 0.f;  // of query head tid % REP; the sum of this thread's weights only
+  float m_run = ATT_NEG, l_run = 0.f;  // the wavefront's, of query head lane % REP; the sum of this lane's weights only
 
   // 32-bit offsets from bases that are the same for the whole workgroup (the launcher checks that they fit)
   const int64_t row0 = nbeg * a.Hkv + h;
@@ -442,10 +465,13 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
   for (uint32_t t0 = 0; t0 < span; t0 += ATT_BLOCK) {
     const uint32_t cnt = min(span - t0, (uint32_t)ATT_BLOCK);
     const int trips = (int)((cnt + STEP - 1) / STEP);  // >= 1
+    // token of the block that is number j of this wavefront: half j & 1, trip j >> 1
+    auto token = [&](uint32_t j) { return (uint32_t)wave * 2u + (j & 1u) + STEP * (j >> 1); };
+    float *wts = sm_w + wave * BW * REP;
     uint16_t vstd[VPT];
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-      const uint32_t t = t0 + (uint32_t)(tid + i * NT);
+      const uint32_t t = t0 + token((uint32_t)(lane + i * 64));
       vstd[i] = vsb[(t < last ? t : last) * hkv];
     }
     // ---- keys
@@ -522,8 +548,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
           for (int e = 1; e < 4; ++e) s[r] = fmaf(kr[e], qv[r][e], s[r]);
         }
         const float v = att_sum_token<REP>(s, lane);
-        const uint32_t tt = hw + STEP * (uint32_t)i;  // token of the block
-        if (l32 < REP) sm_w[tt * REP + l32] = v;      // (beyond the end: overwritten with weight 0)
+        if (l32 < REP) wts[(2 * i + half) * REP + l32] = v;  // (beyond the end: overwritten with weight 0)
         if ((i & 7) == 5 && i + 3 < trips) {
           store8(0, i + 3);
           store_std(i + 3);
@@ -540,43 +565,38 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
     __builtin_amdgcn_wave_barrier();
     att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, 0), 8, R);
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) sm_vs[tid + i * NT] = rvq_f16_bits_to_f32(vstd[i]);
-    __syncthreads();
+    for (int i = 0; i < VPT; ++i) sm_vs[wave][lane + i * 64] = rvq_f16_bits_to_f32(vstd[i]);
+    __builtin_amdgcn_wave_barrier();
     {
-      const int have = (int)cnt * REP, pad = trips * (int)STEP * REP;
+      const int num = 2 * trips * REP;
       float mx = m_run;
-      for (int idx = tid; idx < have; idx += NT) mx = fmaxf(mx, sm_w[idx]);
-#pragma unroll
-      for (int o = 32; o >= REP; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-      if (lane < REP) sm_red[wave][lane] = mx;
-      __syncthreads();
-#pragma unroll
-      for (int w = 0; w < ATT_WAVES; ++w) mx = fmaxf(mx, sm_red[w][tid % REP]);
+      for (int idx = lane; idx < num; idx += 64)
+        if (token((uint32_t)(idx / REP)) < cnt) mx = fmaxf(mx, wts[idx]);
+      mx = att_wave_reduce<REP>(mx, att_max);
       const float corr = __builtin_amdgcn_exp2f(m_run - mx);
       l_run *= corr;
       m_run = mx;
-      if (tid < REP) sm_corr[tid] = corr;
-      for (int idx = tid; idx < pad; idx += NT) {
-        const float pw = idx < have ? __builtin_amdgcn_exp2f(sm_w[idx] - mx) : 0.f;
+      if (lane < REP) sm_corr[wave][lane] = corr;
+      for (int idx = lane; idx < num; idx += 64) {
+        const float pw = token((uint32_t)(idx / REP)) < cnt ? __builtin_amdgcn_exp2f(wts[idx] - mx) : 0.f;
         l_run += pw;
-        sm_w[idx] = pw * sm_vs[idx / REP];
+        wts[idx] = pw * sm_vs[wave][idx / REP];
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
     // ---- values
     {
 #pragma unroll
       for (int r = 0; r < REP; ++r)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[r][e] *= sm_corr[r];
+        for (int e = 0; e < 4; ++e) acc[r][e] *= sm_corr[wave][r];
       auto trip = [&](int i, bool first) {
         __builtin_amdgcn_wave_barrier();
         if (!first) att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, i), 8, R);
         if ((i & 7) == 0 && i + 8 < trips) fetch8(vcb, t0, i + 8);
-        const uint32_t tt = hw + STEP * (uint32_t)i;
         float w[REP];
 #pragma unroll
-        for (int r = 0; r < REP; ++r) w[r] = sm_w[tt * REP + r];
+        for (int r = 0; r < REP; ++r) w[r] = wts[(2 * i + half) * REP + r];
         const f32x4 v4 = att_sum<true>(R, 8);
 #pragma unroll
         for (int r = 0; r < REP; ++r)
@@ -587,44 +607,43 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       trip(0, true);
       for (int i = 1; i < trips; ++i) trip(i, false);
     }
-    __syncthreads();  // (the next block's scores overwrite the weights)
+    __builtin_amdgcn_wave_barrier();  // (the next block's scores overwrite the weights)
   }
 
-  // ---- the workgroup's sums: the halves of a wavefront by a lane swap, the wavefronts through LDS (the
-  // weights' memory), one query head at a time where it does not hold all
-  constexpr int AT_ONCE = ATT_BLOCK * REP / (ATT_WAVES * ATT_HD) < REP ? ATT_BLOCK * REP / (ATT_WAVES * ATT_HD) : REP;
-  static_assert(AT_ONCE >= 1 && REP % AT_ONCE == 0, "the block's scores hold one head's sums at least");
-  float *dst = a.part + ((int64_t)h * a.S + sp) * REP * ATT_PART;
+  // ---- the workgroup's sums: the halves of a wavefront by a lane swap, the wavefronts, each with its own
+  // maximum, through LDS (a wavefront's part of the weights' memory)
+  static_assert(BW >= ATT_HD, "a wavefront's weights leave room for its sums");
 #pragma unroll
-  for (int r0 = 0; r0 < REP; r0 += AT_ONCE) {
-    if (r0) __syncthreads();
+  for (int r = 0; r < REP; ++r)
 #pragma unroll
-    for (int r = r0; r < r0 + AT_ONCE; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const unsigned u = __float_as_uint(acc[r][e]);
-        const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-        if (half == 0) sm_w[((r - r0) * ATT_WAVES + wave) * ATT_HD + cv[e]] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-      }
-    __syncthreads();
-    for (int idx = tid; idx < AT_ONCE * ATT_HD; idx += NT) {
-      const int r = idx / ATT_HD, c = idx % ATT_HD;
-      float tot = 0.f;
-#pragma unroll
-      for (int w = 0; w < ATT_WAVES; ++w) tot += sm_w[(r * ATT_WAVES + w) * ATT_HD + c];
-      dst[(r0 + r) * ATT_PART + 2 + c] = tot;
+    for (int e = 0; e < 4; ++e) {
+      const unsigned u = __float_as_uint(acc[r][e]);
+      const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      if (half == 0) sm_w[(wave * REP + r) * BW + cv[e]] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
+  l_run = att_wave_reduce<REP>(l_run, att_add);
+  if (lane < REP) {
+    sm_m[wave][lane] = m_run;
+    sm_l[wave][lane] = l_run;
   }
-#pragma unroll
-  for (int o = 32; o >= REP; o >>= 1) l_run += __shfl_xor(l_run, o, 64);
-  if (lane < REP) sm_red[wave][lane] = l_run;
   __syncthreads();
-  if (tid < REP) {
-    float L = 0.f;
+  float *dst = a.part + ((int64_t)h * a.S + sp) * REP * ATT_PART;
+  for (int idx = tid; idx < REP * ATT_HD; idx += NT) {
+    const int r = idx / ATT_HD, c = idx % ATT_HD;
+    float M = sm_m[0][r], tot = 0.f, L = 0.f;
 #pragma unroll
-    for (int w = 0; w < ATT_WAVES; ++w) L += sm_red[w][tid];
-    dst[tid * ATT_PART] = m_run;
-    dst[tid * ATT_PART + 1] = L;
+    for (int w = 1; w < ATT_WAVES; ++w) M = fmaxf(M, sm_m[w][r]);
+#pragma unroll
+    for (int w = 0; w < ATT_WAVES; ++w) {
+      const float f = __builtin_amdgcn_exp2f(sm_m[w][r] - M);
+      tot = fmaf(sm_w[(w * REP + r) * BW + c], f, tot);
+      L = fmaf(sm_l[w][r], f, L);
+    }
+    dst[r * ATT_PART + 2 + c] = tot;
+    if (c == 0) {
+      dst[r * ATT_PART] = M;
+      dst[r * ATT_PART + 1] = L;
+    }
   }
 }
 
@@ -655,7 +674,7 @@ __global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__re
     ls[i] = s < S ? base[s * stride + 1] : 0.f;
     M = fmaxf(M, ms[i]);
   }
-  for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
+  M = att_wave_reduce<1>(M, att_max);
   if (lane == 0) red[wave][0] = M;
   __syncthreads();
 #pragma unroll
@@ -669,7 +688,7 @@ __global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__re
       L = fmaf(ls[i], w, L);
     }
   }
-  for (int o = 32; o > 0; o >>= 1) L += __shfl_xor(L, o, 64);
+  L = att_wave_reduce<1>(L, att_add);
   if (lane == 0) red[wave][1] = L;
   __syncthreads();
   float tot = 0.f;
