@@ -14,6 +14,8 @@
 // one takes each token's key and value together (attn_partial_kernel).  Either leaves one partial result per
 // (kv head, split of the cache), maximum, sum and weighted values in base 2, and a second small kernel
 // merges the splits.
+#include <type_traits>
+
 #include "rvq_internal.h"
 
 namespace {
@@ -43,6 +45,7 @@ struct AttnArgs {
   int64_t tps;              // tokens per split (a multiple of 8)
   int Hkv, S, depth, k_depth_used, v_depth_used, Kk, Kv;
   int kstd_dtype, vstd_dtype, k_strided, v_strided;
+  int alone;                // no CU has a second workgroup
   float scale_log2e;        // softmax scale times log2(e): scores are kept in base 2
 };
 
@@ -395,7 +398,12 @@ __device__ __forceinline__ float att_add(float a, float b) { return a + b; }
 // Everything from HBM passes through LDS: the 64 lanes fetch the codes of eight trips of both half-wavefronts, a
 // record each, and the 32 lanes of a token its tables, a piece each (per lane of use, 176 of a trip's 432
 // L1 accesses would repeat another lane's).  A wavefront's own areas: its LDS operations run in order.
+// Where every workgroup has a CU to itself and few trips to make, values are decoded along with the keys, both rows
+// in one round trip, and their sums stay in LDS until the weights are there: what is left is a chain of
+// round trips (1000 tokens x 8 kv heads, 4 queries each: 12.5 -> 11.9 us).  With a second workgroup on the CU to
+// fill the waits, phases are faster (2000 tokens 15.4 : 16.4).
 constexpr int ATT_BLOCK = 1024;
+constexpr int ATT_BRIEF = 4;  // trips
 template <int REP, bool KS, bool VS, int PK>
 __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const AttnArgs a) {
   constexpr int NT = 64 * ATT_WAVES;
@@ -406,6 +414,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
   __shared__ __align__(16) i32x4 sm_codes[2][ATT_WAVES][2][64];  // [K, V][eight trips, even / odd][half][trip][group]
   __shared__ float sm_std[ATT_WAVES][2][16];                  // [even / odd][half][trip]
   __shared__ __align__(16) float sm_tab[ATT_WAVES][2][ATT_HD];  // [half][64 cos, 64 sin]
+  __shared__ __align__(16) f32x4 sm_v[ATT_BRIEF][NT];         // value sums of a short block
   __shared__ float sm_vs[ATT_WAVES][BW];                      // the values' std
   __shared__ float sm_m[ATT_WAVES][REP], sm_l[ATT_WAVES][REP], sm_corr[ATT_WAVES][REP];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -465,6 +474,7 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
   for (uint32_t t0 = 0; t0 < span; t0 += ATT_BLOCK) {
     const uint32_t cnt = min(span - t0, (uint32_t)ATT_BLOCK);
     const int trips = (int)((cnt + STEP - 1) / STEP);  // >= 1
+    const bool brief = a.alone && trips <= ATT_BRIEF;
     // token of the block that is number j of this wavefront: half j & 1, trip j >> 1
     auto token = [&](uint32_t j) { return (uint32_t)wave * 2u + (j & 1u) + STEP * (j >> 1); };
     float *wts = sm_w + wave * BW * REP;
@@ -499,11 +509,12 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       cn = vn;
       store8(1, 0);
       __builtin_amdgcn_wave_barrier();
-      auto trip = [&](int i, f32x4 &tb) {
-        f32x4 R[8];
+      auto trip = [&](int i, f32x4 &tb, auto both) {
+        f32x4 R[8], Rv[8];
         __builtin_amdgcn_wave_barrier();
         att_issue<true, PK>(reinterpret_cast<const char *>(a.Ck), lane_off, a.Kk, codes_of(0, i), 8, R);
-        if ((i & 7) == 0 && i + 8 < trips) {
+        if constexpr (both) att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, i), 8, Rv);
+        if (!both && (i & 7) == 0 && i + 8 < trips) {
           fetch8(kcb, t0, i + 8);
           fetch_std(i + 8);
         }
@@ -549,14 +560,24 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
         }
         const float v = att_sum_token<REP>(s, lane);
         if (l32 < REP) wts[(2 * i + half) * REP + l32] = v;  // (beyond the end: overwritten with weight 0)
-        if ((i & 7) == 5 && i + 3 < trips) {
+        if constexpr (both) sm_v[i][tid] = att_sum<true>(Rv, 8);
+        if (!both && (i & 7) == 5 && i + 3 < trips) {
           store8(0, i + 3);
           store_std(i + 3);
         }
       };
-      for (int i = 0; i < trips; i += 2) {
-        trip(i, tabn);
-        if (i + 1 < trips) trip(i + 1, tabm);
+      if (brief) {
+        for (int i = 0; i < trips; ++i) {
+          trip(i, tabn, std::true_type());
+          const f32x4 t = tabn;
+          tabn = tabm;
+          tabm = t;
+        }
+      } else {
+        for (int i = 0; i < trips; i += 2) {
+          trip(i, tabn, std::false_type());
+          if (i + 1 < trips) trip(i + 1, tabm, std::false_type());
+        }
       }
     }
     // ---- weights
@@ -590,22 +611,28 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
       for (int r = 0; r < REP; ++r)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[r][e] *= sm_corr[wave][r];
-      auto trip = [&](int i, bool first) {
-        __builtin_amdgcn_wave_barrier();
-        if (!first) att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, i), 8, R);
-        if ((i & 7) == 0 && i + 8 < trips) fetch8(vcb, t0, i + 8);
+      auto add = [&](int i, const f32x4 v4) {
         float w[REP];
 #pragma unroll
         for (int r = 0; r < REP; ++r) w[r] = wts[(2 * i + half) * REP + r];
-        const f32x4 v4 = att_sum<true>(R, 8);
 #pragma unroll
         for (int r = 0; r < REP; ++r)
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(w[r], v4[e], acc[r][e]);
+      };
+      auto trip = [&](int i, bool first) {
+        __builtin_amdgcn_wave_barrier();
+        if (!first) att_issue<true, PK>(reinterpret_cast<const char *>(a.Cv), lane_off, a.Kv, codes_of(1, i), 8, R);
+        if ((i & 7) == 0 && i + 8 < trips) fetch8(vcb, t0, i + 8);
+        add(i, att_sum<true>(R, 8));
         if ((i & 7) == 5 && i + 3 < trips) store8(1, i + 3);
       };
-      trip(0, true);
-      for (int i = 1; i < trips; ++i) trip(i, false);
+      if (brief) {
+        for (int i = 0; i < trips; ++i) add(i, sm_v[i][tid]);
+      } else {
+        trip(0, true);
+        for (int i = 1; i < trips; ++i) trip(i, false);
+      }
     }
     __builtin_amdgcn_wave_barrier();  // (the next block's scores overwrite the weights)
   }
@@ -785,6 +812,7 @@ hipError_t rvq_launch_attn_decode(const rvq_ctx *kctx, const rvq_ctx *vctx, cons
       }
     }
   }
+  a.alone = (int64_t)a.S * Hkv <= kctx->num_cus;
   const dim3 grid((unsigned)((fast && a.S >= 8 ? (a.S + 7) / 8 * 8 : a.S) * Hkv)), block(64 * ATT_WAVES);
 #define RVQ_ATT_LAUNCH3(KERNEL, R, P)                                                                 \
   if (a.k_strided) {                                                                                 \
