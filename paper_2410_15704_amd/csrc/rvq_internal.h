@@ -38,11 +38,12 @@ struct rvq_ctx {
   uint16_t *C16;       // [depth][Kpad/32][2][64][8] fp16(-2 c), matrix-core A-operand order
   uint16_t *C16s;      // [depth][Kpad/16][64][8] the same values as 16-row A operands
   float *normp;        // [depth][Kpad/32][2][16] ||c||^2 minus the group's second-order error
-                       //   term, in accumulator-register order
-  float *groupA;       // [depth][Kpad/16] largest ||2c|| of each (tile, half) group
+                       //   term and the codeword's rounding term, in accumulator-register order
+  float *groupA;       // [depth][Kpad/16] of each (tile, half) group the largest ||2c|| (upper half of
+                       //   the word) and the largest rounding term (lower half)
   int32_t *perm;       // [depth][Kpad] codewords by norm (-1 for padding and in the places of repeats)
   uint16_t *perm16;    // position -> codeword index: the same without the repeats, 0xffff for padding
-  float *stats;        // [depth][8]: rounding-error bounds and scales of the fp16 operands
+  float *stats;        // [depth][8]: usable flag and scales of the fp16 operands
   float *rowmax;       // [depth][K] largest |2 c| of each codeword (infinity: not finite)
   int32_t num_cus;     // compute units of the device (persistent kernels launch one workgroup each)
   int32_t Kpad;
