@@ -708,6 +708,9 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   int bestk[SCR_DT];
   int done[SCR_DT];     // the codeword has already been subtracted from the residual
   int nc[SCR_DT];       // candidates found for the token (the list itself is in LDS)
+  // codebooks in pieces: the wavefront's tokens that window_search has settled, for their number of groups or for
+  // their candidates; counted at the end of the stage, because a token can be among them once per piece
+  unsigned long long wide_seen[SCR_DT] = {0, 0}, over_seen[SCR_DT] = {0, 0};
 
   // fp16 operands and error bounds of `stage` from the current residuals
   auto convert = [&](int stage) {
@@ -1119,11 +1122,8 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 #pragma unroll
           for (int k = 0; k < NDT; ++k) {
             const unsigned long long bal = __ballot(hard[k]);
-            const int wide = __popcll(__ballot(hard[k] && (nc[k] & 0x200)));
             order[k] = total + __popcll(bal & ((1ull << lane) - 1ull));
             total += __popcll(bal);
-            n_slow += wide;
-            n_over += __popcll(bal) - wide;
           }
           uint2 *meta = qM;
           unsigned long long *best = reinterpret_cast<unsigned long long *>(qM + 8);
@@ -1149,11 +1149,22 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 #pragma unroll
             for (int k = 0; k < NDT; ++k) {
               const int at = order[k] - base;
+              bool settled = false, wide = false;
               if (hard[k] && at >= 0 && at < 8) {
                 const unsigned bk = (unsigned)best[at];
                 // (no winner cannot happen; it would send the token to the wavefront search below)
+                settled = bk != 0xffffffffu;
+                wide = (nc[k] & 0x200) != 0;
                 lds_c[(wtok + k * 64 + lane) * SCR_CAND] = (uint16_t)bk;
-                nc[k] = bk == 0xffffffffu ? 0 : 1;
+                nc[k] = settled ? 1 : 0;
+              }
+              const unsigned long long w = __ballot(settled && wide), o = __ballot(settled && !wide);
+              if constexpr (single_chunk) {
+                n_slow += __popcll(w);
+                n_over += __popcll(o);
+              } else {
+                wide_seen[k] |= w;
+                over_seen[k] |= o;
               }
             }
           }
@@ -1173,8 +1184,14 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       bool any_slow = false;
 #pragma unroll
       for (int k = 0; k < NDT; ++k) {
-        if (!(bestd[k] < INFINITY)) slow[k] = 1;  // no candidate in any chunk
+        if (!(bestd[k] < INFINITY)) slow[k] = 1;  // no candidate in any piece
         any_slow = any_slow || slow[k];
+        if constexpr (!single_chunk) {  // a search is counted once, and as [0] if it was of both kinds
+          const unsigned long long wide = wide_seen[k] & ~__ballot(slow[k] != 0);
+          n_slow += __popcll(wide);
+          n_over += __popcll(over_seen[k] & ~wide & ~__ballot(slow[k] != 0));
+          wide_seen[k] = over_seen[k] = 0;
+        }
       }
       if (__any(any_slow)) {  // seldom: 0.02 % of the searches
 #pragma unroll 1

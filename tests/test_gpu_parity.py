@@ -711,6 +711,24 @@ def test_encode_screen_windows_of_many_groups(gpu_device, K, V):
         assert bool((got - d.min(1).values <= lim).all())
 
 
+@pytest.mark.parametrize("K, V", [(2048, 1024), (4096, 1024), (6100, 700)])
+def test_counters_count_a_search_once_whatever_the_pieces(gpu_device, K, V):
+    """A codebook in one tight cluster: every token has too many groups in its window, in every piece of the
+    codebook.  The statistics are of (token, stage) searches: no more of them than there are searches."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    C = torch.randn((1, 32), device="cuda", generator=gen) * (1.0 + 1e-3 * torch.randn((K, 32), device="cuda", generator=gen))
+    X = torch.randn((V, 32), device="cuda", generator=gen)
+    q = b.Quantizer(d=32, dhat=32, depth=2, K=K, scale=0, encode_path=b.PATH_SCREEN)
+    q.set_codebooks(torch.stack([C, C]).contiguous())
+    q.encode(X)
+    torch.cuda.synchronize()
+    cnt = b.rvq_get_counters(q.ctx)
+    q.close()
+    assert 9 * cnt["searches"] // 10 < cnt["slow_searches"] + cnt["group_exact_passes"] <= cnt["searches"], cnt
+
+
 def test_encode_screen_duplicate_zero_and_dead_codewords(gpu_device):
     """Exact duplicates (the smallest index must win), an all-zero stage and codewords far from
     every input (dead codes) on the matrix-core path."""
