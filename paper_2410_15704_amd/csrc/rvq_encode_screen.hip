@@ -249,13 +249,14 @@ typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 // The tokens' window is known, so a second sweep, of one tile of 16 tokens, marks every four rows whose
 // smallest score lies within it (v_mfma_f32_16x16x32_f16: a lane holds four rows of one token), and only
 // marked rows are scored exactly: sixteen times four rows per pass, of whichever tokens.  29 instructions a tile
-// of 32 codewords and 4 us a call; the scan of the whole stage by the wavefront that used to settle tokens
-// with too many groups fetches 256 KiB per token, 10 us while everyone in the workgroup waits.  How often: 0.02 %
+// of 32 codewords and 4 us a call where a token marks a few rows; the scan of the whole stage by the wavefront that
+// used to settle tokens with too many groups fetches 256 KiB per token, 10 us while everyone in the workgroup waits,
+// and is the shorter way where the window holds much of the stage (`most`).  How often: 0.02 %
 // of the searches of 1024-channel keys, 1 to 3 % in the first stage of heads of 128 channels with outliers (that
 // stage of 2^20 vectors, K = 2048: 807 -> 400 us, or 442 -> 337, or 323 -> 285, by the draw).
 // Kept out of line, as exact_scan is.
 __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds_cfloat *bounds, lds_cu16 *perm,
-                                           lds_cf32x4 *vec, lds_cuint2 *meta, lds_u64 *best, int ntiles_, int n_,
+                                           lds_cf32x4 *vec, lds_cuint2 *meta, lds_u64 *best, int ntiles_, int n_, int most,
                                            const float *__restrict__ Cs_, int K_, float Tscale, int lane) {
   // (arguments come in vector registers; these are the same in every lane)
   const int ntiles = __builtin_amdgcn_readfirstlane(ntiles_), n = __builtin_amdgcn_readfirstlane(n_);
@@ -319,6 +320,14 @@ __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds
       if (t0 + 4 > ntiles) m8 &= 0xfu;  // (the last pair has marked its rows before)
       marks[w] |= m8 << (2 * (t0 & 15));
     }
+  }
+  // A token with more than `most` marks is left to the search of the whole stage (no winner).
+  {
+    unsigned own = __popc(marks[0]) + __popc(marks[1]) + __popc(marks[2]) + __popc(marks[3]);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(own, own, false, false);
+    own = r16[0] + r16[1];
+    const auto r32 = __builtin_amdgcn_permlane32_swap(own, own, false, false);
+    if (r32[0] + r32[1] > (unsigned)most) marks[0] = marks[1] = marks[2] = marks[3] = 0;
   }
   // exact scores of the marked rows: a pass takes one mark of the first sixteen lanes that have any
   for (;;) {
@@ -1127,8 +1136,24 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
           }
           uint2 *meta = qM;
           unsigned long long *best = reinterpret_cast<unsigned long long *>(qM + 8);
+          bool all_wide = false;
+          // What a token may mark before the search of the whole stage is the shorter way: a pass of window_search
+          // scores 64 rows, one round trip after the other, where exact_scan has the next 128 under way.  With
+          // every row in every window (one cluster) exact_scan : passes, us, 200000 vectors K = 512 890 : 1749, K = 2048
+          // 2394 : 6963, 65536 vectors K = 4096 2182 : 7109: level at 0.5, 0.34 and 0.31 of the rows.  (Pieces at
+          // 3 / 2 ntiles: five clusters 2383 -> 2217, sixteen 812 -> 933.)
+          const int most = 2 * ntiles + (single_chunk ? 32 : 0);
 #pragma unroll 1
           for (int base = 0; base < total; base += 8) {
+            if (all_wide) {  // (eight tokens whose windows hold most of the codebook: so will the others')
+#pragma unroll
+              for (int k = 0; k < NDT; ++k)
+                if (hard[k] && order[k] >= base) {
+                  slow[k] = 1;
+                  nc[k] = 0;
+                }
+              break;
+            }
             if (lane < 8) best[lane] = ~0ull;
 #pragma unroll
             for (int k = 0; k < NDT; ++k) {
@@ -1143,21 +1168,23 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
             }
             __builtin_amdgcn_wave_barrier();
             window_search((lds_cuint2 *)lds_A, (lds_cfloat *)lds_n, (lds_cfloat *)lds_g, (lds_cu16 *)lds_p,
-                          (lds_cf32x4 *)qB, (lds_cuint2 *)meta, (lds_u64 *)best, ntiles, min(8, total - base),
+                          (lds_cf32x4 *)qB, (lds_cuint2 *)meta, (lds_u64 *)best, ntiles, min(8, total - base), most,
                           a.C32 + (int64_t)stage * a.K * 32, a.K, a.stats[stage * 8 + 4], lane);
             __builtin_amdgcn_wave_barrier();
+            int left = min(8, total - base) == 8 ? 8 : -1;
 #pragma unroll
             for (int k = 0; k < NDT; ++k) {
               const int at = order[k] - base;
               bool settled = false, wide = false;
               if (hard[k] && at >= 0 && at < 8) {
                 const unsigned bk = (unsigned)best[at];
-                // (no winner cannot happen; it would send the token to the wavefront search below)
                 settled = bk != 0xffffffffu;
                 wide = (nc[k] & 0x200) != 0;
                 lds_c[(wtok + k * 64 + lane) * SCR_CAND] = (uint16_t)bk;
                 nc[k] = settled ? 1 : 0;
+                if (!settled) slow[k] = 1;  // most of the codebook is in its window: the wavefront search takes it
               }
+              left -= __popcll(__ballot(hard[k] && at >= 0 && at < 8 && !settled));
               const unsigned long long w = __ballot(settled && wide), o = __ballot(settled && !wide);
               if constexpr (single_chunk) {
                 n_slow += __popcll(w);
@@ -1167,6 +1194,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
                 over_seen[k] |= o;
               }
             }
+            all_wide = left == 0;
           }
         }
       }

@@ -33,6 +33,21 @@ def _b():
     return binding
 
 
+def _best_ms(call, runs=7):
+    """The fastest of a few runs on the GPU, in ms, after one that warms up."""
+    torch = _torch()
+    call()
+    best = float("inf")
+    for _ in range(runs):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        call()
+        end.record()
+        end.synchronize()
+        best = min(best, begin.elapsed_time(end))
+    return best
+
+
 def _to_dev(arr, dtype):
     """numpy storage array -> device tensor of the matching torch dtype."""
     torch = _torch()
@@ -727,6 +742,59 @@ def test_counters_count_a_search_once_whatever_the_pieces(gpu_device, K, V):
     cnt = b.rvq_get_counters(q.ctx)
     q.close()
     assert 9 * cnt["searches"] // 10 < cnt["slow_searches"] + cnt["group_exact_passes"] <= cnt["searches"], cnt
+
+
+@pytest.mark.parametrize("K, V", [(64, 300), (320, 1500), (2048, 140000), (4096, 3000)])
+def test_encode_screen_windows_of_up_to_half_of_the_rows(gpu_device, K, V):
+    """Tight clusters of 1/8 to 1/2 of the codewords, with tokens near each: windows below and above the number of
+    rows at which a token is left to the search of the whole stage, both kinds in one wavefront, and
+    wavefronts that hold nothing else.  Nearest up to the rounding of two fp32 sums, 2 x 34 x 2^-24 (|r| + |c|)^2."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + V)
+    share = [K // 8, K // 5, K // 4, K // 4 + K // 32]
+    share.append(K - sum(share))
+    centres = torch.randn((5, 32), device="cuda", generator=gen)
+    member = torch.cat([torch.full((n,), i, device="cuda") for i, n in enumerate(share)])[torch.randperm(K, device="cuda", generator=gen)]
+    C = centres[member] * (1.0 + 1e-4 * torch.randn((K, 32), device="cuda", generator=gen))
+    near = torch.arange(V, device="cuda") % 5
+    near[: V // 4] = 3
+    X = 0.3 * torch.randn((V, 32), device="cuda", generator=gen) + centres[near]
+    q = b.Quantizer(d=32, dhat=32, depth=1, K=K, scale=0, encode_path=b.PATH_SCREEN)
+    q.set_codebooks(C[None].contiguous())
+    codes, _, _ = q.encode(X)
+    torch.cuda.synchronize()
+    cnt = b.rvq_get_counters(q.ctx)
+    q.close()
+    assert cnt["slow_searches"] + cnt["group_exact_passes"] > V // 2, cnt
+    codes = codes.view(-1).long()
+    for i in range(0, V, 4096):
+        x, c = X[i:i + 4096].double(), C.double()
+        d = torch.cdist(x, c, compute_mode="donot_use_mm_for_euclid_dist") ** 2
+        got = ((x - c[codes[i:i + 4096]]) ** 2).sum(1)
+        lim = 2 * 34 * 2.0 ** -24 * (x.norm(dim=1) + c.norm(dim=1).max()) ** 2
+        assert bool((got - d.min(1).values <= lim).all())
+
+
+@pytest.mark.parametrize("K, V", [(2048, 65536), (4096, 32768)])
+def test_encode_screen_one_cluster_costs_a_search_of_the_stage(gpu_device, K, V):
+    """All codewords in one tight cluster: every window holds the whole codebook.  That takes about as long as the
+    exact search of the stage for every token, which a codebook with an infinity gets."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    C = torch.randn((1, 32), device="cuda", generator=gen) * (1.0 + 1e-3 * torch.randn((K, 32), device="cuda", generator=gen))
+    X = torch.randn((V, 32), device="cuda", generator=gen)
+    time = []
+    for last in (0.0, float("inf")):
+        C[K - 1, 0] += last
+        q = b.Quantizer(d=32, dhat=32, depth=1, K=K, scale=0, encode_path=b.PATH_SCREEN)
+        q.set_codebooks(C[None].contiguous())
+        time.append(_best_ms(lambda: q.encode(X)))
+        cnt = b.rvq_get_counters(q.ctx)
+        assert cnt["slow_searches"] == cnt["searches"]
+        q.close()
+    assert time[0] < 1.5 * time[1], time
 
 
 def test_encode_screen_duplicate_zero_and_dead_codewords(gpu_device):
