@@ -9,15 +9,13 @@
 //     scores of ONE token per tile and reduces them without leaving its registers.  Per lane
 //     and tile only the smallest score is kept (v_min3 tree), tagged with the tile number in
 //     its low mantissa bits, and merged into the three smallest tile minima seen so far.
-//  2. Resolve.  In scaled numbers (a = S (-2 c), x = T r, both rounded to fp16) with dx = x - fp16(x),
-//     |screen(k) - exact(k)| <= e_k = g1 ||a_k|| + (kappa/8) ||a_k||^2 + E_k + g0 where
-//     g1 = ||dx|| + kappa ||fp16(x)|| and g0 = tau/2 ||fp16(x)||^2 depend on the token only and
-//     E_k = ||fp16(a_k) - a_k||^2 / (2 tau) on the codeword only (Cauchy-Schwarz on both
-//     rounding terms, see RVQ_BOUND_TAU; kappa covers fp32 accumulation and the tag bits; the terms
-//     of the codeword alone are taken off the stored norms).  Codewords are
-//     stored in order of their norm, so the 16 codewords of a (tile, lane half) group share a
-//     tight bound e_g; the quantity that is tracked per group is the lower bound
-//     LB_g = (smallest screened score of the group) - e_g + g0.  The exact winner lies in a group
+//  2. Resolve.  In scaled numbers (a = S (-2 c), x = T r, both rounded to fp16) with dx = x - fp16(x) and
+//     da = fp16(a) - a, |screen(k) - exact(k)| <= e_k = g1 ||a_k|| + ||fp16(x)|| ||da_k|| + (kappa/8) ||a_k||^2 where
+//     g1 = ||dx|| + kappa ||fp16(x)|| depends on the token only (Cauchy-Schwarz on both rounding terms, see
+//     rvq_bound_group; kappa covers fp32 accumulation and the tag bits; the last term is taken off the stored norms).
+//     Codewords are stored in order of their norm, so the 16 codewords of a (tile, lane half) group share
+//     a tight bound e_g; the quantity that is tracked per group is the lower bound
+//     LB_g = (smallest screened score of the group) - e_g.  The exact winner lies in a group
 //     with LB_g <= UB, UB = LB + 2 e of the group with the smallest LB.  Those few groups are
 //     re-scored from the same LDS copy with packed fp16 dot products (the best group of every
 //     token by its owner, the 3 % of further groups from a per-wavefront queue, four at a time
@@ -75,7 +73,7 @@ struct ScreenArgs {
   const float *C32;
   const uint4 *C16;
   const float *normp;
-  const float *groupA;
+  const uint32_t *groupA;
   const uint16_t *perm16;
   const float *stats;
   int16_t *codes;
@@ -111,8 +109,6 @@ __device__ __forceinline__ void halves32f(float v, float &h0, float &h1) {
   h0 = __uint_as_float(u0);
   h1 = __uint_as_float(u1);
 }
-// the rounding part E of a group's bound, the lower half of its word
-__device__ __forceinline__ float bound_of_rounding(float w) { return __uint_as_float(__float_as_uint(w) << 16); }
 // v of this lane + v of its partner, the same bits in both
 __device__ __forceinline__ float sum32(float v) {
   unsigned h0, h1;
@@ -244,7 +240,7 @@ typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 // Exact nearest codeword, among the operands that are in LDS, of up to eight tokens of a wavefront whose
 // candidates the common path cannot hold: more rows than the candidate list, more groups than the
 // three tracked per lane half, or a full queue.  `vec` holds their fp32 residuals, `meta` their window
-// (threshold, token part of the error bound); the winner of each is left in `best` as (distance bits,
+// (threshold, factor of the groups' bounds); the winner of each is left in `best` as (distance bits,
 // codeword), the largest value if there is none.
 // The tokens' window is known, so a second sweep, of one tile of 16 tokens, marks every four rows whose
 // smallest score lies within it (v_mfma_f32_16x16x32_f16: a lane holds four rows of one token), and only
@@ -279,7 +275,7 @@ __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds
     }
   }
   const u32x2 mt = meta[tok];
-  const float thr = mine ? __uint_as_float(mt.x) : -INFINITY, g1 = __uint_as_float(mt.y);
+  const float thr = mine ? __uint_as_float(mt.x) : -INFINITY, gx = __uint_as_float(mt.y);
   // operand rows m = lane & 15 of row half r: channels 8 c .. 8 c + 7 = piece pair (c & 1), lane half c >> 1
   const int piece0 = (c & 1) * 128 + (c >> 1) * 32;
   unsigned marks[4];
@@ -308,7 +304,7 @@ __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds
       unsigned m8 = 0;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float lim = fmaf(g1, bd[u], thr);
+        const float lim = fmaf(gx, bd[u], thr);
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
           const half8 a = __builtin_bit_cast(half8, make_uint4(q[u][2 * r].x, q[u][2 * r].y, q[u][2 * r + 1].x, q[u][2 * r + 1].y));
@@ -394,7 +390,7 @@ __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds
   tau##d = min3f(tau##d, tau##e, acc[15]);
 #define SWEEP_R2(tau, TT, tile_id, Agv)                      \
   tau = fminf(tau, tau##d);                                  \
-  tau = fmaf(-g1t[TT], Agv, tau); /* lower bound on the exact scores of the group */ \
+  tau = fmaf(-gt[TT], Agv, tau); /* lower bound on the exact scores of the group */ \
   tau = __uint_as_float((__float_as_uint(tau) & tag_mask_v) | (tile_id)); \
   m3[TT] = med3f(m2[TT], m3[TT], tau);                       \
   m2[TT] = med3f(m1[TT], m2[TT], tau);                       \
@@ -417,7 +413,7 @@ __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds
     cn[4] = w1_[0]; cn[5] = w1_[1]; cn[6] = w1_[2]; cn[7] = w1_[3];                             \
     cn[8] = w2_[0]; cn[9] = w2_[1]; cn[10] = w2_[2]; cn[11] = w2_[3];                           \
     cn[12] = w3_[0]; cn[13] = w3_[1]; cn[14] = w3_[2]; cn[15] = w3_[3];                         \
-    Ag = lds_g[(tile) * 2 + h];                                                                 \
+    Ag = rvq_bound_both(lds_g[(tile) * 2 + h]);                                                 \
   }
 // One tile of the sweep: A0 / A1 are its operands, N0 / N1 receive the next tile's.  Two
 // accumulator sets: A holds token tiles 0 and 2, B holds 1 and 3.  Every matrix-core
@@ -540,7 +536,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   extern __shared__ uint4 smem[];
   uint4 *lds_A = smem;                                              // SCR_KC * 4 chunks of 16 B
   float *lds_n = reinterpret_cast<float *>(smem + SCR_KC * 4);      // SCR_KC shifted norms
-  float *lds_g = lds_n + SCR_KC;                                    // SCR_KC / 16 group bounds
+  unsigned *lds_g = reinterpret_cast<unsigned *>(lds_n + SCR_KC);   // SCR_KC / 16 group bounds
   uint16_t *lds_p = reinterpret_cast<uint16_t *>(lds_g + SCR_KC / 16);  // position -> codeword
   uint16_t *lds_c = lds_p + SCR_KC;  // [token of the workgroup][SCR_CAND] candidate codewords
   // candidates found per token: two 16-bit counts per word; the owner keeps its count in a
@@ -710,8 +706,8 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
   // have changed places, which makes [0..7] the matrix-core B operands of token tile 2k (tokens
   // owned by lanes 0..31) and [8..15] those of token tile 2k + 1.
   unsigned Bw[SCR_DT][16];
-  float g1[SCR_DT];     // token parts of the error bound: e_k = g1 ||2c|| + k4 ||2c||^2 + E_k + g0
-  float g0[SCR_DT];
+  float g1[SCR_DT], nq[SCR_DT];  // token parts of the error bound: e_k = g1 ||a|| + nq ||da|| + k4 ||a||^2
+  auto gx = [&](int k) { return fmaxf(g1[k], RVQ_BOUND_RHO * nq[k]); };
   int slow[SCR_DT];     // token goes to the exact wavefront search
   float bestd[SCR_DT];  // exact distance and index of the best candidate scored so far
   int bestk[SCR_DT];
@@ -752,15 +748,14 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         s_q = __builtin_amdgcn_fdot2(pr, pr, s_q, false);
         Bw[k][j >> 1] = pw;
       }
-      const float nq = sqrtf(s_q) * 1.000001f;
-      const float nd = sqrtf(s_d) * 1.000001f;
-      g1[k] = (nd + 1.0005f * a.kappa * nq) * 1.000001f;  // (||fp16(a)|| <= (1 + 2^-11) ||a||)
-      g0[k] = 0.5f * RVQ_BOUND_TAU * 1.000001f * nq * nq;
-      // an element beyond the half range turns s_q into infinity (or the sum into a NaN)
+      nq[k] = sqrtf(s_q) * 1.000003f;
+      g1[k] = (sqrtf(s_d) * 1.000003f + 1.0005f * a.kappa * nq[k]) * 1.000001f;  // (||fp16(a)|| <= (1 + 2^-11) ||a||)
+      // an element beyond the half range turns s_q into infinity, one that is not finite s_d into a NaN (s_q need not
+      // show it: the comparison with `tiny` may go either way)
 #ifdef RVQ_FORCE_SLOW
       slow[k] = 1;
 #else
-      slow[k] = (!usable || (__float_as_uint(s_q) & 0x7fffffffu) >= 0x4f5693a4u /* 3.6e9f */) ? 1 : 0;
+      slow[k] = (!usable || (__float_as_uint(s_q + s_d) & 0x7fffffffu) >= 0x4f5693a4u /* 3.6e9f */) ? 1 : 0;
 #endif
     }
     PHASE_MARK(1);  // operand conversion
@@ -838,7 +833,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         // two token tiles (the halves of the one double tile): accumulator set A holds tile 0,
         // B tile 1, and a set is reduced two matrix instructions after it has been finished
         half8 B0[2], B1[2];
-        float g1t[2];
+        float gt[2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) swap_halves(Bw[0][j], Bw[0][8 + j]);
 #pragma unroll
@@ -848,7 +843,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
           B1[e] = __builtin_bit_cast(
               half8, make_uint4(Bw[0][8 * e + 4], Bw[0][8 * e + 5], Bw[0][8 * e + 6], Bw[0][8 * e + 7]));
         }
-        halves32f(g1[0], g1t[0], g1t[1]);
+        halves32f(gx(0), gt[0], gt[1]);
         f32x16 accA, accB, cn;
 #pragma unroll
         for (int e = 0; e < 16; ++e) { accA[e] = BIG; accB[e] = BIG; }
@@ -869,7 +864,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         static_assert(SCR_TT == 4 && SCR_DT == 2, "the sweep pipeline is written for four token tiles");
         // the matrix-core arrangement of the fp16 residuals and of the tokens' bound terms
         half8 B0[SCR_TT], B1[SCR_TT];
-        float g1t[SCR_TT];
+        float gt[SCR_TT];
 #pragma unroll
         for (int k = 0; k < NDT; ++k) {
 #pragma unroll
@@ -881,7 +876,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
             B1[2 * k + e] = __builtin_bit_cast(
                 half8, make_uint4(Bw[k][8 * e + 4], Bw[k][8 * e + 5], Bw[k][8 * e + 6], Bw[k][8 * e + 7]));
           }
-          halves32f(g1[k], g1t[2 * k], g1t[2 * k + 1]);
+          halves32f(gx(k), gt[2 * k], gt[2 * k + 1]);
         }
         f32x16 accA, accB, cn;
 #pragma unroll
@@ -922,7 +917,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       //
       // fp16 re-score of the 16 rows of group (tl, hh) for the token whose fp16 residual (owner's
       // arrangement) is Bx.  A row survives when its score minus the group's error bound is
-      // within the token's window: score <= tadj = thr + g1 A_g (the second-order part of the
+      // within the token's window: score <= tadj = thr + its bound (the second-order part of the
       // bound is already inside the stored norms).  Returns the survivors as a 16-bit mask:
       // bit 4 b + i stands for tile row 8 b + 4 hh + i.
       auto rescore = [&](int tl, int hh, const unsigned (&Bx)[16], float tadj, bool act) -> unsigned {
@@ -979,17 +974,24 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         return tl < 0 ? 0 : (tl >= ntiles ? ntiles - 1 : tl);
       };
       // the window of the lane's token in double tile k: thr = upper bound on the exact minimum,
-      // from the best group of either lane half (LB + 2 e_g, 2.5 % spare for the rounding of this sum); e0..e3 = the token's four
+      // from the best group of either lane half (its score + e_g, 5 % spare for the rounding of this sum); e0..e3 = the token's four
       // tracked groups, the best one first (the two best of half 0 and of half 1); pend = which of
       // them lie within the window
+      auto upper = [&](int k, float lb, unsigned w) {
+        const float A = rvq_bound_len(w), e = fmaf(g1[k], A, nq[k] * rvq_bound_rounding(w)), k4AA = k4 * A * A;
+        return fmaf(gx(k), rvq_bound_both(w), lb) + (1.05f * e + 2.05f * k4AA);
+      };
+      // thr + the bound of a group
+      auto within = [&](int k, float thr, unsigned w) {
+        return fmaf(g1[k], rvq_bound_len(w), fmaf(nq[k], rvq_bound_rounding(w), thr));
+      };
       struct Window { float thr, e0, e1, e2, e3; unsigned pend; bool afirst; };
       auto window = [&](int k) -> Window {
         Window w;
         const float a1 = ta[k][0], a2 = ta[k][1], a3 = ta[k][2];
         const float b1 = tb[k][0], b2 = tb[k][1], b3 = tb[k][2];
-        const float Aa = lds_g[tile_of(a1) * 2 + 0], Ab = lds_g[tile_of(b1) * 2 + 1];
-        const float ua = a1 + 2.05f * (g1[k] * Aa + k4 * Aa * Aa + bound_of_rounding(Aa) + g0[k]);
-        const float ub = b1 + 2.05f * (g1[k] * Ab + k4 * Ab * Ab + bound_of_rounding(Ab) + g0[k]);
+        const unsigned Wa = lds_g[tile_of(a1) * 2 + 0], Wb = lds_g[tile_of(b1) * 2 + 1];
+        const float ua = upper(k, a1, Wa), ub = upper(k, b1, Wb);
         w.thr = fminf(ua, ub);
         // a third group of one lane half inside the window: more groups than are tracked
         const bool wide = a3 <= w.thr || b3 <= w.thr;
@@ -1018,7 +1020,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
         {
           const int tl = tile_of(w.e0);
           const int hh = (w.afirst ? 0 : 1);
-          const float tadj = w.thr + g1[k] * lds_g[tl * 2 + hh];
+          const float tadj = within(k, w.thr, lds_g[tl * 2 + hh]);
           unsigned todo = rescore(tl, hh, Bw[k], tadj, (w.pend & 1u) != 0);
           // the surviving rows, as codeword indices, into the owner's list; a count beyond the
           // list marks the token for the group-wide exact pass below
@@ -1048,7 +1050,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 #pragma unroll
                 for (int c4 = 0; c4 < 4; ++c4)
                   qB[idx * 4 + c4] = make_uint4(Bw[k][4 * c4], Bw[k][4 * c4 + 1], Bw[k][4 * c4 + 2], Bw[k][4 * c4 + 3]);
-                qM[idx] = make_uint2(__float_as_uint(w.thr + g1[k] * lds_g[tl * 2 + hh]),
+                qM[idx] = make_uint2(__float_as_uint(within(k, w.thr, lds_g[tl * 2 + hh])),
                                      (unsigned)tok | ((unsigned)tl << 8) | ((unsigned)hh << 16));
               } else {
                 nc[k] |= 0x100;  // queue full: the group-wide exact pass takes the token
@@ -1163,7 +1165,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
 #pragma unroll
                 for (int c4 = 0; c4 < 8; ++c4)
                   dst[c4] = f32x4{r[k][4 * c4], r[k][4 * c4 + 1], r[k][4 * c4 + 2], r[k][4 * c4 + 3]};
-                meta[at] = make_uint2(__float_as_uint(thr[k]), __float_as_uint(g1[k]));
+                meta[at] = make_uint2(__float_as_uint(thr[k]), __float_as_uint(gx(k)));
               }
             }
             __builtin_amdgcn_wave_barrier();

@@ -11,9 +11,9 @@
 // Search, exact as in the other kernels (Algorithm 1: nearest codeword, smallest index on ties):
 //  1. Sweep.  v_mfma_f32_16x16x32_f16 on fp16(S (-2c)) and fp16(T r) gives a lane four scores of one
 //     token per instruction; per (32 codewords, lane) only the smallest of its eight is kept, in a
-//     register.  With the error bound of the fp16 screen (|score - exact| <= e = g1 A + k4 A^2 + E + g0,
-//     A the largest ||S 2c|| and E the largest rounding part of the wavefront's norm-sorted codewords; the stored
-//     norms have the group's own k4 A^2 and the codeword's own E taken off) the smallest score gives an upper bound on the exact minimum;
+//     register.  With the error bound of the fp16 screen (|score - exact| <= e = gx B + k4 A^2, B and A the largest
+//     of the wavefront's norm-sorted codewords, rvq_bound_group; the stored norms have the group's own k4 A^2
+//     taken off) the smallest score gives an upper bound on the exact minimum;
 //     the least over the wavefronts, found with lane exchanges and one LDS minimum per (wavefront,
 //     token), is the token's threshold.
 //  2. Pick.  A lane whose kept minimum reaches below its token's threshold marks those eight
@@ -64,7 +64,7 @@ struct ShareArgs {
   const float *C32;
   const uint16_t *C16s;
   const float *normp;
-  const float *groupA;
+  const uint32_t *groupA;
   const uint16_t *perm16;
   const float *stats;
   int16_t *codes;
@@ -87,7 +87,7 @@ __host__ __device__ inline ShareLds share_lds(int T, int piece) {
   ShareLds l;
   l.B = 0;                                   // [T / 16][64] 16-byte operands
   l.rs = l.B + (size_t)T * 64;               // [T][32] fp32 residuals
-  l.info = l.rs + (size_t)T * 128;           // [T] {threshold as ordered bits, added to it, error bound, -}
+  l.info = l.rs + (size_t)T * 128;           // [T] {threshold as ordered bits, added to it, gx, -}
   l.bits = l.info + (size_t)T * 16;          // [T][8] candidate groups, one bit each
   l.best = l.bits + (size_t)T * 32;          // [T] (distance bits, codeword) found so far
   l.slow = l.best + (size_t)T * 8;           // [T] tokens for the exact search
@@ -321,8 +321,9 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   // ---- this wavefront's share of a piece, in registers
   half8 A[2 * TPW];
   f32x4 nrm[2 * TPW];
-  float Ag = 0.f;  // largest ||S 2c|| of them (they are sorted by norm: all alike)
-  float Eg = 0.f;  // what the codewords' part of their bounds adds to a threshold
+  uint32_t Wg = 0;  // the bounds of one of the groups, on their way
+  float Bg = 0.f;   // the largest of the codewords' (they are sorted by norm: all alike)
+  float Eg = 0.f;   // what their part of the bounds adds to a threshold
   float2 normw = {0.f, 0.f};  // two norms and two entries of the position -> codeword map of the piece,
   uint32_t permw = 0;         // on their way to LDS
   // (buffer loads: the bases stay in scalar registers and a lane's part of an address is one register;
@@ -345,8 +346,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
     // once they have arrived)
     const int gi = lane & (2 * TPW - 1);
     const int t0 = piece * (16 * TPW) + wave * TPW + (gi >> 1);
-    Ag = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-        rsG, ((stage * ntc + min(t0, ntc - 1)) * 2 + (gi & 1)) * 4, 0, 0));
+    Wg = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rsG, ((stage * ntc + min(t0, ntc - 1)) * 2 + (gi & 1)) * 4, 0, 0);
 #pragma unroll
     for (int j = 0; j < TPW; ++j) {
       const int t = piece * (16 * TPW) + wave * TPW + j;
@@ -398,11 +398,11 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
         w.y = __float_as_int(-1e35f);  // below every score: no candidates are looked for
         if (valid) lds_slow[atomicAdd(&slow_n[stage & 1], 1)] = (uint16_t)tok;
       } else {
-        // 2.05 g0, and what the fp32 distances of two codewords can be off by rounding: 2 x 34 x 2^-24 of
+        // what the fp32 distances of two codewords can be off by rounding: 2 x 34 x 2^-24 of
         // (|r| + |c|)^2 <= 2 (|r|^2 + |c|^2), where S T |r|^2 = 2 nq^2 here (the |c|^2 part is
         // inside the spare third of the k4 term)
-        w.y = __float_as_int((2.05f * 0.5f * RVQ_BOUND_TAU + 2e-5f) * nq * nq);
-        w.z = __float_as_int((nd + 1.0005f * a.kappa * nq) * 1.000001f);
+        w.y = __float_as_int(2e-5f * nq * nq);
+        w.z = __float_as_int(fmaxf((nd + 1.0005f * a.kappa * nq) * 1.000001f, RVQ_BOUND_RHO * nq));
       }
       lds_i[tok] = w;
     }
@@ -464,10 +464,9 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
   for (int stage = a.stage_begin; stage < a.stage_end; ++stage) {
     const uint16_t *perm = nullptr;
     for (int piece = 0; piece < pieces; ++piece) {
-      // (both halves of the groups' words; the word itself, read as a float, is the first of them)
-      Eg = max8(__uint_as_float(__float_as_uint(Ag) << 16));
-      Ag = max8(Ag);
-      Eg = fmaf(k4u * Ag, Ag, 2.05f * Eg);
+      Bg = max8(rvq_bound_both(Wg));
+      Eg = max8(rvq_bound_len(Wg));
+      Eg = k4u * Eg * Eg;
       // (double buffers: the other half may still be read by a slower wavefront)
       float *nbuf = lds_nrm + buf * PIECE;
       uint16_t *pbuf = lds_perm + buf * PIECE;
@@ -514,10 +513,10 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
             ub1 = __builtin_fminf(ub1, mm[1][j]);
             __builtin_amdgcn_sched_barrier(0);  // (results of one step at a time: registers)
           }
-          // the exact minimum is at most score + e + k4 A^2 + E (the token's part is added in `pick`), with
-          // 2.5 % spare, for the rounding of this sum, on the 2 e above the scores' lower bound, score - g1 A
-          ub1 = min_rows16(fmaf(Ag, 1.05f * g1, ub1 + Eg));
-          ub0 = min_rows16(fmaf(Ag, 1.05f * g0, ub0 + Eg));
+          // the exact minimum is at most score + e + k4 A^2 (what the distances' rounding adds is added in `pick`),
+          // with 2.5 % spare, for the rounding of this sum, on the 2 e above the scores' lower bound, score - e
+          ub1 = min_rows16(fmaf(Bg, 1.05f * g1, ub1 + Eg));
+          ub0 = min_rows16(fmaf(Bg, 1.05f * g0, ub0 + Eg));
           if (lane < 32) atomicMin(&lds_i[tile0 * 16 + lane].x, order_bits(__float_as_int(lane < 16 ? ub0 : ub1)));
         } else {
 #pragma unroll
@@ -528,7 +527,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
             mm[1][j] = SHR_BIG;
             ub0 = __builtin_fminf(ub0, mm[0][j]);
           }
-          ub0 = min_rows16(fmaf(Ag, 1.05f * g0, ub0 + Eg));
+          ub0 = min_rows16(fmaf(Bg, 1.05f * g0, ub0 + Eg));
           if (lane < 16) atomicMin(&lds_i[tile0 * 16 + lane].x, order_bits(__float_as_int(ub0)));
         }
       };
@@ -541,7 +540,7 @@ __global__ __launch_bounds__(SHR_THREADS) void encode_share_kernel(const ShareAr
           if (u == 0 || tile < ntiles) {
             const int tok = tile * 16 + tcol;
             const int4 w = lds_i[tok];
-            const float tadj = fmaf(__int_as_float(w.z), Ag, __int_as_float(order_bits(w.x)) + __int_as_float(w.y));
+            const float tadj = fmaf(__int_as_float(w.z), Bg, __int_as_float(order_bits(w.x)) + __int_as_float(w.y));
             float best = mm[u][0];
 #pragma unroll
             for (int j = 1; j < TPW; ++j) best = __builtin_fminf(best, mm[u][j]);

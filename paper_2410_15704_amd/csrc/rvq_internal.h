@@ -10,15 +10,6 @@
 // polls of a wait between wavefronts before it gives up (a poll takes some 300 clocks)
 constexpr uint32_t RVQ_WAIT_POLLS_DEFAULT = 1u << 22;
 
-// The fp16 codeword a16 = a + da (a = S (-2 c)) meets the fp16 residual x16: its rounding moves a score by
-// da . x16, at most |da| |x16| <= (|da|^2 / tau + tau |x16|^2) / 2 for any tau > 0.  The first half is a
-// number of the codeword, taken off its stored norm, the second one of the token, so the bound of a token
-// and a codeword holds that codeword's own rounding error and not the stage's largest (1.9e-4 of |a| typically,
-// 4.7e-4 where one channel outweighs the others: the bound is 0.63 to 0.73 of what it was with that).  The two
-// halves are equal, and equal to the product, at tau = |da| / |x16| = 4 rho |c| / |r| (S = 2 T); 2^-11 is
-// that for rho = 1.95e-4, the mean of fp16 rounding, and |c| = 0.63 |r|.
-constexpr float RVQ_BOUND_TAU = 4.8828125e-4f;
-
 // largest channel-pair table (bytes) the LDS decode path keeps resident: depth * K * 8
 constexpr size_t RVQ_SPLIT_MAX_LDS = 144 * 1024;
 
@@ -38,9 +29,9 @@ struct rvq_ctx {
   uint16_t *C16;       // [depth][Kpad/32][2][64][8] fp16(-2 c), matrix-core A-operand order
   uint16_t *C16s;      // [depth][Kpad/16][64][8] the same values as 16-row A operands
   float *normp;        // [depth][Kpad/32][2][16] ||c||^2 minus the group's second-order error
-                       //   term and the codeword's rounding term, in accumulator-register order
-  float *groupA;       // [depth][Kpad/16] of each (tile, half) group the largest ||2c|| (upper half of
-                       //   the word) and the largest rounding term (lower half)
+                       //   term, in accumulator-register order
+  uint32_t *groupA;    // [depth][Kpad/16] of each (tile, half) group the largest ||2c|| and the largest rounding
+                       //   error of a codeword, see rvq_bound_group
   int32_t *perm;       // [depth][Kpad] codewords by norm (-1 for padding and in the places of repeats)
   uint16_t *perm16;    // position -> codeword index: the same without the repeats, 0xffff for padding
   float *stats;        // [depth][8]: usable flag and scales of the fp16 operands
@@ -180,6 +171,28 @@ __device__ __forceinline__ float rvq_row_std(const void *__restrict__ X, int64_t
 inline bool rvq_rows_vectorizable(const void *dX, int64_t ldx, int d, int in_dtype) {
   const int esz = in_dtype == RVQ_F32 ? 4 : 2;
   return (reinterpret_cast<uintptr_t>(dX) % 16) == 0 && (ldx * esz) % 16 == 0 && (d * esz) % 16 == 0;
+}
+
+// ---- what the fp16 score of a token and a codeword can be off by: with a = S (-2 c), x = T r, da and dx the rounding
+// of either, |da . x16 + a . dx| <= ||da|| ||x16|| + ||a|| ||dx||.  Both products are relative to the token AND to the
+// codeword, so the bound shrinks with a short residual (a zero vector has none) as with a short codeword.  The
+// bound of a token and a group of codewords (A, D: the largest ||a|| and ||da||) is g1 A + nq D, g1 = ||dx|| +
+// kappa ||x16||, nq = ||x16||.  Where there is one instruction for it, max(g1, rho nq) (A + D / rho) is used, which
+// is no smaller for any rho, and the same where both roundings are rho of the whole, which they are about: rho is
+// the mean of fp16 rounding with kappa.  (As one dot product of halves, 32768 rows take 4 % longer.)
+// A group's word holds A + D / rho (upper half, so that the word itself read as a float is that, a little larger)
+// and D, both as bf16 rounded up.  (D of the group and not the stage's largest ratio: 1.9e-4 of ||a|| typically,
+// 4.7e-4 where one channel outweighs the others.)
+constexpr float RVQ_BOUND_RHO = 2.1e-4f;
+__device__ __forceinline__ uint32_t rvq_bound_group(float A, float D) {
+  const uint32_t d = (__float_as_uint(D) + 0xffffu) & 0xffff0000u;
+  const float both = A * 1.000001f + __uint_as_float(d) * (1.000002f / RVQ_BOUND_RHO);
+  return ((__float_as_uint(both) + 0xffffu) & 0xffff0000u) | (d >> 16);
+}
+__device__ __forceinline__ float rvq_bound_both(uint32_t w) { return __uint_as_float(w); }          // A + D / rho
+__device__ __forceinline__ float rvq_bound_rounding(uint32_t w) { return __uint_as_float(w << 16); }  // D
+__device__ __forceinline__ float rvq_bound_len(uint32_t w) {                                         // A
+  return fmaf(-1.0f / RVQ_BOUND_RHO, rvq_bound_rounding(w), rvq_bound_both(w));
 }
 
 // ---- derived data of one codeword (dhat == 32), by 32 lanes, channel j = lane & 31 in each: the squared norm

@@ -8,12 +8,10 @@
 //   C16    : fp16(-2 c) of the codeword at each position, laid out exactly as the A operand of
 //            v_mfma_f32_32x32x16_f16 is read, so the kernel copies it into LDS linearly and a
 //            lane's operand is one 16-byte LDS read
-//   groupA : for every (tile, lane half) group of 16 rows, the largest ||S 2c|| (upper half of the word) and the
-//            largest share of the codewords' rounding in the error bound (lower half), both as bf16
-//            rounded up; the whole word read as a float is the first of them, a little larger
-//   normp  : S T ||c||^2 - kappa/8 * groupA^2 - ||fp16(S a) - S a||^2 / (2 tau), a = -2c, in the order a lane's 16
-//            accumulator registers want (the first term taken off bounds the accumulation error of the
-//            group's scores, the second is the codeword's half of the bound on its rounding, RVQ_BOUND_TAU)
+//   groupA : for every (tile, lane half) group of 16 rows, the largest A = ||S 2c|| and the largest rounding error
+//            ||fp16(S 2c) - S 2c||, in one word (rvq_bound_group)
+//   normp  : S T ||c||^2 - kappa/8 * A^2, in the order a lane's 16 accumulator registers want (the term taken off
+//            bounds the accumulation error of the group's scores)
 //   stats  : per stage 8 floats: [1] usable flag (finite codebook); [3] S and [4] T, the powers of two the
 //            codebook and the residuals are scaled by before rounding to fp16 (chosen so that the largest
 //            |S a| lies in [2^13, 2^14) and T = S / 2); [5] the largest |a|
@@ -35,9 +33,6 @@ __global__ void norms_kernel(const float *__restrict__ C, float *__restrict__ no
   for (int j = 0; j < dhat; ++j) acc += (double)c[j] * (double)c[j];
   norms[first + i] = (float)acc;
 }
-
-// v >= 0 as bf16, rounded up
-__device__ __forceinline__ uint32_t bf16_up(float v) { return (__float_as_uint(v) + 0xffffu) >> 16; }
 
 // dhat == 32, one lane per (codeword, channel); ema_finish32_kernel does the same for the codewords it makes
 __global__ __launch_bounds__(256) void prep_rows32_kernel(const float *__restrict__ C, int stage_begin, int stage_end,
@@ -142,7 +137,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     const float *__restrict__ rowmax, int K, int Kpad, int stage_begin, float kappa,
     uint16_t *__restrict__ C16, uint16_t *__restrict__ C16s, uint16_t *__restrict__ perm16,
     float *__restrict__ normp,
-    float *__restrict__ groupA, float *__restrict__ stats) {
+    uint32_t *__restrict__ groupA, float *__restrict__ stats) {
   __shared__ float red[16];
   __shared__ int wave_held[16], here[32];  // codewords of the tile's rows, -1: none
   __shared__ float nrm[32], len[32], rnd[32];
@@ -181,7 +176,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
   __syncthreads();
   mxa = red[0];
   for (int i = 1; i < 16; ++i) mxa = fmaxf(mxa, red[i]);
-  const bool finite = mxa <= 3.0e38f;
+  const bool finite = mxa <= 1.0e30f;  // (and S at its best, see below)
   // S: power of two that brings the stage's largest |2c| into [2^13, 2^14); T = S / 2
   int ex = 0;
   if (mxa > 0.f && finite) (void)frexpf(mxa, &ex);  // mxa = f * 2^ex, f in [0.5, 1)
@@ -220,7 +215,7 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     if (k >= 0) {
       nrm[m] = (float)(a2 * 0.25 * ((double)T / (double)S));  // S T ||c||^2
       len[m] = (float)(sqrt(a2) * (1.0 + 1e-6));              // ||S 2c||, rounded up
-      rnd[m] = (float)(e2 * (0.5 / RVQ_BOUND_TAU) * (1.0 + 1e-6));
+      rnd[m] = (float)(sqrt(e2) * (1.0 + 1e-6));
     } else {
       nrm[m] = 1e30f;  // padding can never come near the minimum
       len[m] = 0.f;
@@ -232,18 +227,17 @@ __global__ __launch_bounds__(1024) void screen_tile_kernel(
     // group hh of the tile: rows 8 b + 4 hh + i, b, i = 0..3, which are the 16 accumulator
     // registers rr = 4 b + i of the lanes of half hh
     const int hh = threadIdx.x >> 4, rr = threadIdx.x & 15;
-    float A = 0.f, E = 0.f;
+    float A = 0.f, D = 0.f;
     for (int r2 = 0; r2 < 16; ++r2) {
       const int row = 8 * (r2 >> 2) + 4 * hh + (r2 & 3);
       A = fmaxf(A, len[row]);
-      E = fmaxf(E, rnd[row]);
+      D = fmaxf(D, rnd[row]);
     }
     // kappa * (S T ||c||^2) = kappa / 4 * (T / S) * ||S 2c||^2 = kappa / 8 * A^2
     const float shift = 0.125f * kappa * A * A * 1.000001f;
     const int mm = 8 * (rr >> 2) + 4 * hh + (rr & 3);
-    normp[(int64_t)stage * Kpad + (int64_t)t * 32 + hh * 16 + rr] = nrm[mm] - (shift + rnd[mm]);
-    if (rr == 0)
-      groupA[(int64_t)stage * (Kpad / 16) + t * 2 + hh] = __uint_as_float((bf16_up(A) << 16) | bf16_up(E));
+    normp[(int64_t)stage * Kpad + (int64_t)t * 32 + hh * 16 + rr] = nrm[mm] - shift;
+    if (rr == 0) groupA[(int64_t)stage * (Kpad / 16) + t * 2 + hh] = finite ? rvq_bound_group(A, D) : 0u;
   }
 }
 

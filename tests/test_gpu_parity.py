@@ -776,6 +776,43 @@ def test_encode_screen_windows_of_up_to_half_of_the_rows(gpu_device, K, V):
         assert bool((got - d.min(1).values <= lim).all())
 
 
+@pytest.mark.parametrize("K, V", [(2048, 16384), (4096, 16384), (2048, 140000), (4096, 140000), (2048, 300000)])
+@pytest.mark.parametrize("kind", ["zero vectors", "short codewords"])
+def test_encode_screen_window_follows_vector_and_codewords(gpu_device, K, V, kind):
+    """The fp16 screen's window is relative to the vector and to the codewords: zero vectors (padding) have almost
+    none, and neither have long vectors among short codewords in a stage that a few long ones scale.  Few more codewords
+    are scored exactly than one (kernel of vectors per lane) or one group of eight (shared codebook) per piece, and
+    few searches go further.  Nearest up to the rounding of two fp32 sums, 2 x 34 x 2^-24 (|r| + |c|)^2."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + V)
+    C = torch.randn((K, 32), device="cuda", generator=gen)
+    X = torch.zeros((V, 32), device="cuda")
+    if kind == "short codewords":
+        X = 4.0 * (2.0 * torch.rand((V, 32), device="cuda", generator=gen) - 1.0)
+        X[:, :4] *= 0.2
+        C *= 0.003
+        C[::16] = 0.0
+        C[::16, :4] = 3.0 * torch.randn((len(C[::16]), 4), device="cuda", generator=gen)
+    q = b.Quantizer(d=32, dhat=32, depth=1, K=K, scale=0)
+    q.set_codebooks(C[None].contiguous())
+    codes, _, _ = q.encode(X)
+    torch.cuda.synchronize()
+    cnt = b.rvq_get_counters(q.ctx)
+    q.close()
+    scored = (K + 2047) // 2048 * (8 if V < 100000 else 1)
+    assert cnt["exact_rescored"] <= 2 * scored * cnt["searches"], cnt  # (all zero vectors are alike: one more each)
+    assert cnt["slow_searches"] + cnt["group_exact_passes"] < 0.05 * cnt["searches"], cnt
+    codes = codes.view(-1).long()
+    step = 2 ** 23 // K
+    for i in range(0, V, step):
+        x, c = X[i:i + step].double(), C.double()
+        d = torch.cdist(x, c, compute_mode="donot_use_mm_for_euclid_dist") ** 2
+        got = ((x - c[codes[i:i + step]]) ** 2).sum(1)
+        lim = 2 * 34 * 2.0 ** -24 * (x.norm(dim=1) + c.norm(dim=1).max()) ** 2
+        assert bool((got - d.min(1).values <= lim).all())
+
+
 @pytest.mark.parametrize("K, V", [(2048, 65536), (4096, 32768)])
 def test_encode_screen_one_cluster_costs_a_search_of_the_stage(gpu_device, K, V):
     """All codewords in one tight cluster: every window holds the whole codebook.  That takes about as long as the
@@ -792,7 +829,9 @@ def test_encode_screen_one_cluster_costs_a_search_of_the_stage(gpu_device, K, V)
         q.set_codebooks(C[None].contiguous())
         time.append(_best_ms(lambda: q.encode(X)))
         cnt = b.rvq_get_counters(q.ctx)
-        assert cnt["slow_searches"] == cnt["searches"]
+        # (the window's width is relative to the vector: 5e-4 |r| |c| on scores spread over 2e-3 |r| |c| cos(r, c), which
+        # a few vectors in ten thousand, long and nearly parallel to the cluster, exceed at its edge)
+        assert cnt["slow_searches"] >= 0.999 * cnt["searches"]
         q.close()
     assert time[0] < 1.5 * time[1], time
 
