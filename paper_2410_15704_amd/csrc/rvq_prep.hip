@@ -23,6 +23,8 @@
 
 namespace {
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 // one thread per codeword; the norm is summed in double and rounded once to float
 __global__ void norms_kernel(const float *__restrict__ C, float *__restrict__ norms, int dhat,
                              int64_t first, int64_t count) {
@@ -50,12 +52,14 @@ __global__ __launch_bounds__(256) void prep_rows32_kernel(const float *__restric
 // read once for all of them.
 // Codewords of equal norm are mostly repeats of each other (dead ones are all zero), so a codeword is
 // compared with the first one of its norm, in one round trip, and with the others only where that row differs.
+// (One after the other, codebooks on the unit sphere, hundreds of codewords to a norm, took 372 us for eight
+// stages of 2048, of -1 and 1 835; now 47 and 99.)
 // (Compared by the threads that met the equal norm, element after element, each pair cost 32 round trips one
 // after the other: 23 us for a stage of 2048 with some zero codewords, 4.8 now; eight
 // stages 50 -> 15 us, of 4096 codewords 215 -> 38.)
 constexpr int RANK_CW = 4;
-__global__ __launch_bounds__(64 * RANK_CW) void rank_kernel(const float *__restrict__ C,
-                                                            const float *__restrict__ norms, int K, int Kpad,
+__global__ __launch_bounds__(64 * RANK_CW) void rank_kernel(const float *__restrict__ C, const float *__restrict__ norms,
+                                                            const float *__restrict__ rowmax, int K, int Kpad,
                                                             int stage_begin, int32_t *__restrict__ perm) {
   __shared__ int cnt_s[RANK_CW][RANK_CW], tie_s[RANK_CW][RANK_CW];  // [wavefront][codeword]
   const int per_stage = (K + RANK_CW - 1) / RANK_CW;
@@ -106,17 +110,33 @@ __global__ __launch_bounds__(64 * RANK_CW) void rank_kernel(const float *__restr
     const float *Cs = C + (int64_t)stage * K * 32;
     const float c = Cs[(int64_t)k * 32 + (lane & 31)];
     found = __all(Cs[(int64_t)first * 32 + (lane & 31)] == c);
-    if (!found) {
-      // (seldom: equal norms of different rows)
-      const float nw = n[k];
-      for (int j0 = first + 1; j0 < k && !found; j0 += 64) {
-        unsigned long long m = __ballot(j0 + lane < k && n[min(j0 + lane, K - 1)] == nw);
-        while (m && !found) {
-          const int j = j0 + __ffsll((long long)m) - 1;
-          m &= m - 1;
-          found = __all(Cs[(int64_t)j * 32 + (lane & 31)] == c);
+    // Different rows of equal norm (codebooks on a sphere, of few values): every later one of the norm that has the
+    // same largest element too, a candidate per lane, until a piece of it differs.
+    const float *m = rowmax + (int64_t)stage * K;
+    const float nw = n[k], mw = m[k];
+    const f32x4 *rows = reinterpret_cast<const f32x4 *>(Cs);
+    constexpr int U = 4;
+    for (int j0 = first + 1 + lane; !found && __any(j0 < k); j0 += 64 * U) {
+      bool same[U], any = false;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = min(j0 + 64 * u, K - 1);
+        same[u] = n[j] == nw && m[j] == mw && j0 + 64 * u < k;
+        any = any || same[u];
+      }
+      for (int p = 0; p < 8 && __any(any); ++p) {
+        const f32x4 own = rows[(int64_t)k * 8 + p];
+        f32x4 c4[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c4[u] = rows[(int64_t)(same[u] ? j0 + 64 * u : k) * 8 + p];
+        any = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          same[u] = same[u] && c4[u][0] == own[0] && c4[u][1] == own[1] && c4[u][2] == own[2] && c4[u][3] == own[3];
+          any = any || same[u];
         }
       }
+      found = __any(any);
     }
   }
   if (lane == 0) perm[(int64_t)stage * Kpad + pos] = found ? -1 : k;
@@ -258,7 +278,7 @@ hipError_t rvq_launch_prepare_codebook(const rvq_ctx *ctx, int stage_begin, int 
     hipLaunchKernelGGL(prep_rows32_kernel, dim3((unsigned)((ns * K + 7) / 8)), dim3(256), 0, s, ctx->C,
                        stage_begin, stage_end, rvq_rows32(ctx));
   hipLaunchKernelGGL(rank_kernel, dim3((unsigned)(ns * ((K + RANK_CW - 1) / RANK_CW))), dim3(64 * RANK_CW), 0, s,
-                     ctx->C, ctx->norms, (int)K, ctx->Kpad, stage_begin, ctx->perm);
+                     ctx->C, ctx->norms, ctx->rowmax, (int)K, ctx->Kpad, stage_begin, ctx->perm);
   hipLaunchKernelGGL(screen_tile_kernel, dim3((unsigned)(ns * (ctx->Kpad / 32))), dim3(1024), 0, s,
                      ctx->C, ctx->perm, ctx->rowmax, (int)K, ctx->Kpad, stage_begin, ctx->kappa,
                      ctx->C16, ctx->C16s, ctx->perm16, ctx->normp, ctx->groupA, ctx->stats);

@@ -500,6 +500,43 @@ def test_repeats_among_codewords_of_equal_norm(gpu_device, K, repeats):
     assert got[0][2] == got[1][2]
 
 
+@pytest.mark.parametrize("K, repeats", [(259, 2), (700, 50), (2112, 60), (4096, 32)])
+def test_repeats_among_many_codewords_of_equal_norm(gpu_device, K, repeats):
+    """Codewords of -1 and 1, all of one norm and largest element, and the last ones repeats of codewords in all
+    parts of the stage.  Left out of the search they change neither codes nor statistics (both sizes pad alike)."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    m = K - repeats
+    C = torch.randint(0, 2, (K, 32), device="cuda", generator=gen).float() * 2.0 - 1.0
+    C[m:] = C[torch.linspace(1, m - 1, repeats, device="cuda").long()]
+    X = torch.randn((3000, 32), device="cuda", generator=gen)
+    got = []
+    for n in (K, m):
+        q = b.Quantizer(d=32, dhat=32, depth=1, K=n, scale=0, encode_path=b.PATH_SCREEN)
+        q.set_codebooks(C[None, :n].contiguous())
+        codes, _, res = q.encode(X, want_residual=True)
+        torch.cuda.synchronize()
+        got.append((codes, res, b.rvq_get_counters(q.ctx)))
+        q.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2] == got[1][2]
+
+
+@pytest.mark.parametrize("K", [1024, 4096])
+def test_preparation_of_codebooks_on_a_sphere(gpu_device, K):
+    """Codewords of unit norm: the rounded norms take a few values only, hundreds of codewords each.  Preparing them
+    takes about as long as preparing codewords of any norm."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    C = torch.randn((8, K, 32), device="cuda", generator=gen)
+    q = b.Quantizer(d=32, dhat=32, depth=8, K=K, scale=0)
+    time = [_best_ms(lambda: q.set_codebooks(c)) for c in (C, C / C.norm(dim=2, keepdim=True))]
+    q.close()
+    assert time[1] < 2.5 * time[0], time
+
+
 @pytest.mark.parametrize("V, K, d, residual", [(1, 64, 32, True), (512, 256, 32, True), (513, 2048, 32, False),
                                                (131073, 320, 32, True), (262145, 2048, 32, True), (70001, 1024, 96, True)])
 def test_one_stage_rows_requested_ahead(gpu_device, V, K, d, residual):
