@@ -46,6 +46,7 @@ struct AttnArgs {
   int Hkv, S, depth, k_depth_used, v_depth_used, Kk, Kv;
   int kstd_dtype, vstd_dtype, k_strided, v_strided;
   int alone;                // no CU has a second workgroup
+  int per_xcd;              // workgroups per XCD
   float scale_log2e;        // softmax scale times log2(e): scores are kept in base 2
 };
 
@@ -393,8 +394,9 @@ __device__ __forceinline__ float att_add(float a, float b) { return a + b; }
 //    that is resident at once stay roughly in the same phase;
 //  - a phase's rows take half the registers, so the next token's rows travel while this token's are worked on;
 //  - a token's weight is computed once, not by its 32 lanes, and nothing is rescaled per token.
-// The workgroups of the kv heads of one split sit on one XCD (ids eight apart): rotary tables and the cache
-// lines that several heads' codes share are fetched by one L2.
+// The workgroups of the kv heads of one split sit on one XCD, or on two: rotary tables and the cache
+// lines that several heads' codes share are fetched by one L2.  Every XCD gets as many workgroups as the next,
+// whatever the numbers of heads and splits.
 // Everything from HBM passes through LDS: the 64 lanes fetch the codes of eight trips of both half-wavefronts, a
 // record each, and the 32 lanes of a token its tables, a piece each (per lane of use, 176 of a trip's 432
 // L1 accesses would repeat another lane's).  A wavefront's own areas: its LDS operations run in order.
@@ -419,9 +421,11 @@ __global__ __launch_bounds__(64 * ATT_WAVES, 2) void attn_phases_kernel(const At
   __shared__ float sm_m[ATT_WAVES][REP], sm_l[ATT_WAVES][REP], sm_corr[ATT_WAVES][REP];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, g = (lane >> 3) & 3, q8 = lane & 7;
-  // id = (split % xcds) + xcds * (head + Hkv * (split / xcds)), xcds = 8, or 1 with fewer than eight splits
-  const int id = blockIdx.x, rest = a.S >= 8 ? id >> 3 : id, h = rest % a.Hkv;
-  const int sp = a.S >= 8 ? (id & 7) + 8 * (rest / a.Hkv) : rest / a.Hkv;
+  // An XCD (ids equal modulo eight) has every eighth split, or, if their number is no multiple of eight, an eighth of
+  // the list of all (split, head).  Heads run fastest.
+  const bool whole = (a.S & 7) == 0;
+  const int xcd = blockIdx.x & 7, num = (whole ? 0 : xcd * a.per_xcd) + (int)(blockIdx.x >> 3);
+  const int h = num % a.Hkv, sp = whole ? xcd + 8 * (num / a.Hkv) : num / a.Hkv;
   if (sp >= a.S) return;
   const int64_t nbeg = (int64_t)sp * a.tps;
   const int64_t nend = nbeg + a.tps < a.N ? nbeg + a.tps : a.N;
@@ -740,7 +744,8 @@ __global__ __launch_bounds__(ATT_MERGE) void attn_merge_kernel(const float *__re
 }  // namespace
 
 // splits of a cache of N tokens over Hkv kv heads; the same rule sizes the workspace.  A long
-// cache: enough workgroups to fill the chip several times, at least 128 tokens each.  A short
+// cache: enough workgroups to fill the chip several times, at least 128 tokens each (attn_phases_kernel then
+// takes fewer, see below).  A short
 // one is a matter of latency (a wavefront's trips are a chain of dependent loads): splits down to
 // 32 tokens, four trips of a workgroup, as long as that makes no more than 512 workgroups
 // (measured: 2048 tokens x 8 heads 32 -> 19 us; with 2048 workgroups of 32 tokens at 8192 tokens
@@ -799,28 +804,46 @@ hipError_t rvq_launch_attn_decode(const rvq_ctx *kctx, const rvq_ctx *vctx, cons
   const bool fast = a.depth == 8 && k_depth_used == 8 && v_depth_used == 8 && dCos && dKStd && dVStd &&
                     a.kstd_dtype == RVQ_F16 && a.vstd_dtype == RVQ_F16;
   if (fast) {
-    // Two workgroups per CU, resident at once, so that their phases stay together; whole multiples of the XCDs,
-    // so that no CU has a third.  131072 tokens x 8 kv heads, 4 queries each: one workgroup per CU 463 us, two
-    // 338, one and a half 464, two and a half 450, three 377 (blocks of 512), four 368.
-    int64_t cap = 2 * (int64_t)(kctx->num_cus > 0 ? kctx->num_cus : 1) / Hkv;
-    if (cap >= 8) cap = cap / 8 * 8;
-    if (cap >= 1 && a.S > cap) {
-      const int64_t longer = ((N + cap - 1) / cap + 7) / 8 * 8;
-      if (longer * Hkv * ATT_G * 16 < (int64_t)1 << 32) {  // (codes of a split are addressed with 32 bits)
+    // Two workgroups per CU, resident at once, so that their phases stay together.  131072 tokens x 8 kv heads, 4
+    // queries each: one workgroup per CU 463 us, two 338, one and a half 464, two and a half 450, three 377
+    // (blocks of 512), four 368: a CU's workgroups take the time of two, 338 / 256 of the whole per pair, an odd one
+    // 463 / 512, and a few percent more where pairs follow each other.  Heads that do not divide two per CU well
+    // (a kv head is the least a workgroup can have) get the number of rounds that leaves the least idle: 2^20 (token,
+    // head), one query each, 36 heads 573 -> 322 us, 40 517 -> 328, 300 573 -> 317 (8: 309).
+    const int64_t cus = kctx->num_cus > 0 ? kctx->num_cus : 1;
+    if ((int64_t)a.S * Hkv > 2 * cus) {
+      int64_t best = 0;
+      double least = 0.0;
+      for (int m = 2; m <= 8; ++m) {
+        int64_t sm = m * cus / Hkv;
+        if (sm < 1 || sm > a.S) continue;
+        if (sm / 8 * 8 * 25 >= sm * 24) sm = sm / 8 * 8;  // (whole splits per XCD: 20 heads, 25 splits 346 us, 24 328)
+        const double t = (338.0 * m + (m & 1 ? 125.0 : 0.0)) * (1.0 + 0.045 * (m - 2)) / (double)(sm * Hkv);
+        if (best == 0 || t < least) {
+          best = sm;
+          least = t;
+        }
+      }
+      const int64_t longer = best > 0 ? ((N + best - 1) / best + 7) / 8 * 8 : 0;
+      if (longer > 0 && longer * Hkv * ATT_G * 16 < (int64_t)1 << 32) {  // (codes of a split are addressed with 32 bits)
         a.tps = longer;
         a.S = (int)((N + longer - 1) / longer);
       }
     }
   }
   a.alone = (int64_t)a.S * Hkv <= kctx->num_cus;
-  const dim3 grid((unsigned)((fast && a.S >= 8 ? (a.S + 7) / 8 * 8 : a.S) * Hkv)), block(64 * ATT_WAVES);
+  a.per_xcd = (a.S * Hkv + 7) / 8;
+  const dim3 grid((unsigned)(fast ? 8 * a.per_xcd : a.S * Hkv)), block(64 * ATT_WAVES);
+  // (one and two queries per kv head leave room for a third workgroup on a CU: 10 KiB of LDS keep it out.  2^20 (token,
+  // head), 200 heads 350 -> 319 us, 300 343 -> 317)
+  const size_t lds = fast && rep <= 2 ? 10240 : 0;
 #define RVQ_ATT_LAUNCH3(KERNEL, R, P)                                                                 \
   if (a.k_strided) {                                                                                 \
-    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, true, true, P>), grid, block, 0, s, a);           \
-    else hipLaunchKernelGGL((KERNEL<R, true, false, P>), grid, block, 0, s, a);                      \
+    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, true, true, P>), grid, block, lds, s, a);           \
+    else hipLaunchKernelGGL((KERNEL<R, true, false, P>), grid, block, lds, s, a);                      \
   } else {                                                                                           \
-    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, false, true, P>), grid, block, 0, s, a);          \
-    else hipLaunchKernelGGL((KERNEL<R, false, false, P>), grid, block, 0, s, a);                     \
+    if (a.v_strided) hipLaunchKernelGGL((KERNEL<R, false, true, P>), grid, block, lds, s, a);          \
+    else hipLaunchKernelGGL((KERNEL<R, false, false, P>), grid, block, lds, s, a);                     \
   }
 #define RVQ_ATT_LAUNCH2(KERNEL, R)                   \
   if (packed_bytes == 11) {                          \

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
-from test_gpu_parity import _b, _torch
+from test_gpu_parity import _b, _best_ms, _torch
 
 pytestmark = pytest.mark.gpu
 
@@ -125,6 +125,36 @@ def test_attn_decode_blocks_and_splits(gpu_device, N, Hkv, rep, kg, vg):
     """Splits of more tokens than a block holds, with queries sharp enough that the running maximum moves between
     blocks, and both orders of workgroups; the bar is the other tests'."""
     _check(_case(2000 + N, N, Hkv, rep, 8, 512, 256, kg, vg, sharp=4.0))
+
+
+@pytest.mark.parametrize("N, Hkv, rep", [(3000, 36, 1), (1700, 20, 4), (700, 300, 1), (1500, 5, 8), (40, 3, 2)])
+def test_attn_decode_heads_that_do_not_divide_the_chip(gpu_device, N, Hkv, rep):
+    """Numbers of heads and splits whose workgroups are no multiple of the XCDs: splits that two XCDs share, several
+    rounds of workgroups, fewer workgroups than XCDs; the bar is the other tests'."""
+    _check(_case(3000 + N, N, Hkv, rep, 8, 512, 256, oracle.STRIDED, oracle.CONTIGUOUS))
+
+
+@pytest.mark.parametrize("Hkv", [22, 24, 36, 40, 48, 257, 300])
+def test_attn_decode_of_any_number_of_heads_fills_the_chip(gpu_device, Hkv):
+    """The time of a long cache follows (token, kv head) pairs, whatever the number of heads: within 30 % of that
+    of 8 heads, which divide the chip's workgroups evenly."""
+    torch, b = _torch(), _b()
+    time = []
+    for heads in (8, Hkv):
+        N = 2 ** 20 // heads
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(heads)
+        q = b.Quantizer(d=HD, dhat=32, depth=8, K=2048, grouping=b.STRIDED)
+        q.set_codebooks(torch.randn((8, 2048, 32), device="cuda", generator=gen))
+        codes = torch.randint(0, 2048, (N * heads, G, 8), dtype=torch.int16, device="cuda", generator=gen)
+        std = torch.ones(N * heads, device="cuda").half()
+        cos, sin, query, out = (torch.ones(s, device="cuda") for s in ((N, 64), (N, 64), (heads, HD), (heads, HD)))
+        n = b.rvq_attn_workspace_bytes(N, heads, heads)
+        ws = torch.empty(n // 4, device="cuda")
+        time.append(_best_ms(lambda: b.rvq_attn_decode(q.ctx, q.ctx, query, heads, heads, codes, std, codes, std, N, cos, sin,
+                                                       0.01, out, ws, n)))
+        q.close()
+    assert time[1] < 1.3 * time[0], time
 
 
 def test_attn_decode_equals_decode_then_attention_on_the_gpu(gpu_device):
