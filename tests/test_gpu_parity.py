@@ -537,6 +537,31 @@ def test_preparation_of_codebooks_on_a_sphere(gpu_device, K):
     assert time[1] < 2.5 * time[0], time
 
 
+@pytest.mark.parametrize("K", [7, 64])
+def test_update_of_a_small_codebook(gpu_device, K):
+    """A small codebook's partial sums are many: adding them up does not make the update of 5000 vectors much
+    longer than that of 300, which has none."""
+    torch, b = _torch(), _b()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    q = b.Quantizer(d=32, dhat=32, depth=1, K=K, scale=0)
+    C = torch.randn((1, K, 32), device="cuda", generator=gen)
+    q.set_codebooks(C)
+    time = []
+    for M in (300, 5000):
+        R = torch.randn((M, 32), device="cuda", generator=gen)
+        codes = torch.randint(0, K, (M,), dtype=torch.int16, device="cuda", generator=gen)
+        cs, es = torch.full((K,), 1000.0, device="cuda"), 1000.0 * C[0]
+
+        def some():
+            for _ in range(20):
+                b.rvq_ema_update(q.ctx, 0, R, codes, 1, M, 0.99, 1e-5, cs, es)
+
+        time.append(_best_ms(some))
+    q.close()
+    assert time[1] < 1.35 * time[0], time
+
+
 @pytest.mark.parametrize("V, K, d, residual", [(1, 64, 32, True), (512, 256, 32, True), (513, 2048, 32, False),
                                                (131073, 320, 32, True), (262145, 2048, 32, True), (70001, 1024, 96, True)])
 def test_one_stage_rows_requested_ahead(gpu_device, V, K, d, residual):
