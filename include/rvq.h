@@ -263,8 +263,8 @@ int rvq_ema_update(rvq_ctx *ctx, int32_t stage, const float *dR, const int16_t *
  * Statistics of the matrix-core encode path, accumulated since rvq_create (diagnostics; this
  * call synchronizes the device).  host_out is HOST memory, 5 values:
  *   [0] (token, stage) searches with more candidate groups than the kernel keeps track of, or whose residual
- *       does not fit fp16 (those are redone exactly in fp32 over the whole stage), [1] codewords re-scored exactly in fp32, [2] 16-codeword groups
- *       re-scored from LDS, [3] all (token, stage) searches (padding lanes of the last
+ *       does not fit fp16, or near which most of the codebook lies (the latter two are redone exactly in fp32 over the
+ *       whole stage), [1] codewords re-scored exactly in fp32, [2] 16-codeword groups re-scored from LDS, [3] all (token, stage) searches (padding lanes of the last
  *       workgroup included), [4] searches with more candidates than the kernel's list holds,
  *       settled, as the first kind of [0], by scoring every codeword near enough exactly.
  * These are the counts of the kernel of RVQ_PATH_SCREEN.  In calls that the kernel whose wavefronts

@@ -521,7 +521,7 @@ constexpr int SCR_WTOK = 64 * SCR_DT;  // tokens per wavefront
 // PRE (with HALF, fp32 rows in 16-byte pieces, calls of one stage): a chunk's rows are requested a chunk ahead.  A
 // call of one stage reads 128 bytes, sweeps once and writes 128 bytes per vector; nobody waits for operands, so
 // the loads are what a wavefront stands still for, and there are registers for them with one token per
-// lane (242 of 256) and not with two.
+// lane (232 of 256) and not with two.
 // HALF: every lane owns one token instead of two (chunks of 512 vectors).  A stage then takes
 // about 0.6 of the time and a call with fewer chunks than CUs spreads over twice as many of them:
 // the instantiation for calls between the few rows of encode_small_kernel and a full chip.
@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
           const float tadj = within(k, w.thr, lds_g[tl * 2 + hh]);
           unsigned todo = rescore(tl, hh, Bw[k], tadj, (w.pend & 1u) != 0);
           // the surviving rows, as codeword indices, into the owner's list; a count beyond the
-          // list marks the token for the group-wide exact pass below
+          // list leaves the token to window_search below
           while (__any(todo != 0)) {
             const bool has = todo != 0;
             const int rr = has ? __ffs(todo) - 1 : 0;
@@ -1053,7 +1053,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
                 qM[idx] = make_uint2(__float_as_uint(within(k, w.thr, lds_g[tl * 2 + hh])),
                                      (unsigned)tok | ((unsigned)tl << 8) | ((unsigned)hh << 16));
               } else {
-                nc[k] |= 0x100;  // queue full: the group-wide exact pass takes the token
+                nc[k] |= 0x100;  // queue full: window_search takes the token
               }
             }
             qn = min(SCR_QCAP, qn + (int)__popcll(bal));
@@ -1200,7 +1200,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
           }
         }
       }
-      PHASE_MARK(7);  // resolve: group-wide exact passes
+      PHASE_MARK(7);  // resolve: window_search
     }
   };
 
@@ -1223,7 +1223,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
           wide_seen[k] = over_seen[k] = 0;
         }
       }
-      if (__any(any_slow)) {  // seldom: 0.02 % of the searches
+      if (__any(any_slow)) {  // seldom: a residual outside fp16, or a window that holds most of the codebook
 #pragma unroll 1
         for (int k = 0; k < NDT; ++k) {
           // double tile k is picked with selects, so that the common path never moves the
