@@ -18,11 +18,11 @@
 //     LB_g = (smallest screened score of the group) - e_g.  The exact winner lies in a group
 //     with LB_g <= UB, UB = LB + 2 e of the group with the smallest LB.  Those few groups are
 //     re-scored from the same LDS copy with packed fp16 dot products (the best group of every
-//     token by its owner, the 3 % of further groups from a per-wavefront queue, four at a time
+//     token by its owner, further groups (2.4 % of the searches) from a per-wavefront queue, four at a time
 //     with 16 lanes per group), and
 //     every codeword whose lower bound is <= UB is scored exactly (fp32, direct form
 //     sum (r - c)^2, fp32 codebook), ties going to the smallest index.  A token with a single
-//     candidate (97 %) needs no score at all: the row is fetched once and subtracted.  A token
+//     candidate (98 %) needs no score at all: the row is fetched once and subtracted.  A token
 //     with more candidates than its list holds, or more groups in a lane than the three tracked
 //     ones, is settled by a second sweep that marks the rows near enough (window_search); one
 //     whose residual does not fit fp16 is searched exactly over the whole codebook.
@@ -247,8 +247,8 @@ typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 // marked rows are scored exactly: sixteen times four rows per pass, of whichever tokens.  29 instructions a tile
 // of 32 codewords and 4 us a call where a token marks a few rows; the scan of the whole stage by the wavefront that
 // used to settle tokens with too many groups fetches 256 KiB per token, 10 us while everyone in the workgroup waits,
-// and is the shorter way where the window holds much of the stage (`most`).  How often: 0.02 %
-// of the searches of 1024-channel keys, 1 to 3 % in the first stage of heads of 128 channels with outliers (that
+// and is the shorter way where the window holds much of the stage (`most`).  How often: 0.2 %
+// of the searches of 1024-channel keys (too many groups 0.01 %, the rest a full list), 1 to 3 % in the first stage of heads of 128 channels with outliers (that
 // stage of 2^20 vectors, K = 2048: 807 -> 400 us, or 442 -> 337, or 323 -> 285, by the draw).
 // Kept out of line, as exact_scan is.
 __device__ __noinline__ void window_search(lds_cuint2 *A, lds_cfloat *norms, lds_cfloat *bounds, lds_cu16 *perm,
@@ -1007,7 +1007,7 @@ __global__ __launch_bounds__(64 * SCR_WAVES) void encode_screen_kernel(const Scr
       };
 
       // Pass A, per double tile: the best group of every token is re-scored by its owner and the
-      // surviving rows go to the token's candidate list; its other groups inside the window (3 %
+      // surviving rows go to the token's candidate list; its other groups inside the window (2.4 %
       // of the tokens have one) are queued, so that they are re-scored together afterwards
       // instead of one extra pass per double tile.
       int qn = 0;  // queue entries of this wavefront (wave-uniform)
